@@ -676,244 +676,344 @@ k_gcr_fused_update(const cpx<T>* W, size_t wstride, cpx<T>* w, cpx<T>* r, cpx<T>
     }
 }
 
-// ---- Gram-form GCR step (short restart cycles: the smoother's and the coarsest solve's).
-// With w_i = A p_i kept as computed (not orthogonalised) and r0 the cycle's starting
-// residual, step j's minimal residual over span(p_0..p_j) is r_{j+1} = r0 - sum_{i<=j} y_i w_i
-// with G y = b, G_il = <w_i, w_l>, b_i = <w_i, r0> (the normal equations of the same
-// least-squares problem GCR solves by orthogonalising).  The multi-dot of step j gives G's
-// new row and b_j.  Its finaliser is one workgroup per column: wave q adds the partials of
-// quantity q, then one thread solves the (j+1)-square system by Cholesky in FP64 registers
-// (a pivot that is not positive drops that direction: its y is zero) and stores G's row,
-// b_j, y, the new residual norm and the stop flag.  A streaming pass then writes
-// r_{j+1}, the next direction (k_gcr_gram_step), or at the cycle's last step adds the
-// correction to x and leaves r_{j+1} in P_0 (k_gcr_gram_last); no orthogonalised direction
-// and no running residual is written.
-constexpr int kGramPartials = 1024;   // multi-dot blocks per column (partials per finaliser wave)
-template <int j>
-__global__ void __launch_bounds__(64 * (2 * kGramMax + 1)) k_fin_gram(RedWork rw, int nb, const int* stop_in,
-                                                                     int* stop_out, GcrDev g, double tol2, int last) {
-    constexpr int m = j + 1;
-    constexpr int NQ = 2 * j + 3;
-    static_assert(64 * NQ <= 1024, "one wave per inner product in one workgroup");
-    // G's rows and b of the cycle's earlier steps, one value per thread: D's j x j block
-    // (only the lower triangle is used), |w_i|^2, <w_i, r0>
-    constexpr int ND = 2 * j * j;
-    constexpr int NOLD = ND + 3 * j;
-    static_assert(NOLD <= 64 * NQ, "one earlier value per thread");
-    __shared__ double tq[NQ];
-    __shared__ double old[NOLD > 0 ? NOLD : 1];
-    const int col = blockIdx.x;
-    const int t = threadIdx.x;
-    const int lane = t & 63, q = t >> 6;   // one wave per quantity
-    const size_t kb = (size_t)col * g.kmax;
-    // every load is issued before the first wait: the stop flag, the partials (added
-    // whether or not the column has stopped: a stopped column's sums go unused) and the
-    // earlier rows.  The flag and the column's scalars are read by vector loads (an offset
-    // the compiler cannot see is zero), which complete in order with the partials' loads
-    // instead of holding them back in a wait shared with the kernel arguments.
-    int zoff;
-    asm volatile("v_mov_b32 %0, 0" : "=v"(zoff));
-    const int sflag = stop_in[col + zoff];
-    const double rr0 = g.rr[col + zoff];
-    const int it0 = g.it[col + zoff];
-    double ov = 0.0;
-    if (t < NOLD) {   // (the address by selects: one load, no branches between the loads)
-        const double* src = t < ND ? g.D + ((kb + t / (2 * j)) * g.kmax + (t % (2 * j)) / 2) * 2 + (t & 1)
-                                   : (t < ND + j ? g.nn + kb + (t - ND) : g.wr + 2 * kb + (t - ND - j));
-        ov = *src;
-    }
-    {
-        const double* part = rw.partial + (size_t)col * rw.max_q * rw.nblk + (size_t)q * rw.nblk;
-        double sq = 0.0;
-#pragma unroll 8
-        for (int b = lane; b < nb; b += 64) sq += part[b];
-        sq = wave_sum(sq);
-        if (lane == 0) tq[q] = sq;
-    }
-    if (t < NOLD) old[t] = ov;
-    __syncthreads();
-    if (t != 0) return;
-    if (sflag != 0) {
-        for (int l = 0; l < j; ++l) {
-            g.D[((kb + j) * g.kmax + l) * 2] = 0.0;
-            g.D[((kb + j) * g.kmax + l) * 2 + 1] = 0.0;
-        }
-        g.nn[kb + j] = 0.0;
-        g.wr[2 * (kb + j)] = 0.0;
-        g.wr[2 * (kb + j) + 1] = 0.0;
-        // the coefficients of the step the column stopped at stay (a stopped step's own is
-        // zero), so that the cycle's solution update adds that step's minimal residual correction
-        g.gam[2 * (kb + j)] = 0.0;
-        g.gam[2 * (kb + j) + 1] = 0.0;
-        stop_out[col] = sflag;
-        return;
-    }
-    // G (lower triangle: G_il = conj <w_l, w_i>, l < i) and b
-    cpx<double> G[m][m], b[m];
-#pragma unroll
-    for (int i = 0; i < j; ++i) {
-#pragma unroll
-        for (int l = 0; l < i; ++l) G[i][l] = {old[i * 2 * j + 2 * l], -old[i * 2 * j + 2 * l + 1]};
-        G[i][i] = {old[ND + i], 0.0};
-        b[i] = {old[ND + j + 2 * i], old[ND + j + 2 * i + 1]};
-    }
-#pragma unroll
-    for (int l = 0; l < j; ++l) G[j][l] = {tq[3 + 2 * l], -tq[4 + 2 * l]};
-    G[j][j] = {tq[0], 0.0};
-    b[j] = {tq[1], tq[2]};
-    // Cholesky G = L L^H in place (lower triangle), inv[i] = 1 / L_ii or 0 for a dropped direction
-    double inv[m];
-#pragma unroll
-    for (int i = 0; i < m; ++i) {
-#pragma unroll
-        for (int l = 0; l <= i; ++l) {
-            cpx<double> acc = G[i][l];
-#pragma unroll
-            for (int qq = 0; qq < l; ++qq) {   // - L_iq conj(L_lq)
-                acc.re -= G[i][qq].re * G[l][qq].re + G[i][qq].im * G[l][qq].im;
-                acc.im -= G[i][qq].im * G[l][qq].re - G[i][qq].re * G[l][qq].im;
-            }
-            if (l == i) {
-                const bool ok = acc.re > 0.0 && finite(acc.re);
-                inv[i] = ok ? 1.0 / sqrt(acc.re) : 0.0;
-                G[i][i] = {ok ? sqrt(acc.re) : 0.0, 0.0};
-            } else {
-                G[i][l] = {acc.re * inv[l], acc.im * inv[l]};
-            }
-        }
-    }
-    cpx<double> u[m], y[m];
-#pragma unroll
-    for (int i = 0; i < m; ++i) {   // L u = b
-        cpx<double> acc = b[i];
-#pragma unroll
-        for (int qq = 0; qq < i; ++qq) {
-            acc.re -= G[i][qq].re * u[qq].re - G[i][qq].im * u[qq].im;
-            acc.im -= G[i][qq].re * u[qq].im + G[i][qq].im * u[qq].re;
-        }
-        u[i] = {acc.re * inv[i], acc.im * inv[i]};
-    }
-#pragma unroll
-    for (int i = m - 1; i >= 0; --i) {   // L^H y = u, (L^H)_iq = conj(L_qi)
-        cpx<double> acc = u[i];
-#pragma unroll
-        for (int qq = i + 1; qq < m; ++qq) {
-            acc.re -= G[qq][i].re * y[qq].re + G[qq][i].im * y[qq].im;
-            acc.im -= G[qq][i].re * y[qq].im - G[qq][i].im * y[qq].re;
-        }
-        y[i] = {acc.re * inv[i], acc.im * inv[i]};
-    }
-#pragma unroll
-    for (int l = 0; l < j; ++l) {
-        g.D[((kb + j) * g.kmax + l) * 2] = tq[3 + 2 * l];
-        g.D[((kb + j) * g.kmax + l) * 2 + 1] = tq[4 + 2 * l];
-    }
-    g.nn[kb + j] = tq[0];
-    g.wr[2 * (kb + j)] = tq[1];
-    g.wr[2 * (kb + j) + 1] = tq[2];
-    // |r_{j+1}|^2 = |r0|^2 - Re <b, y> (the minimal residual), the cycle's |r0|^2 in g.rr
-    double by = 0.0;
-#pragma unroll
-    for (int i = 0; i < m; ++i) {
-        g.gam[2 * (kb + i)] = y[i].re;
-        g.gam[2 * (kb + i) + 1] = y[i].im;
-        by += b[i].re * y[i].re + b[i].im * y[i].im;
-    }
-    double rr = rr0 - by;
-    if (rr < 0.0) rr = 0.0;
-    if (last) g.rr[col] = rr;
-    g.it[col] = it0 + 1;
-    int f = 0;
-    if (!(finite(tq[0]) && finite(tq[1]) && finite(tq[2]) && finite(rr))) f = 2;
-    else if (rr <= tol2 * g.bb[col]) f = 1;
-    stop_out[col] = f;
-}
+// ---- s-step GCR cycle (cycles of at most kSsMax steps: the smoother's and the coarsest
+// solve's).  The cycle's minimal residual lies in r0 - span{A p : p in K_k(A, r0)}, whatever
+// basis spans the Krylov space, so the directions need no inner product while they are built:
+// P_0 = r0, P_{i+1} = A P_i / c - P_i (the stencil's epilogue; a shift to the middle of the
+// spectrum keeps them well apart), hence A P_i = c v_i with v_i = P_{i+1} + P_i.  One pass
+// forms H_ab = <P_a, P_b>, one workgroup per column solves G y = b, G_il = <v_i, v_l>,
+// b_i = <v_i, r0>, and one pass updates x += sum y_i P_i / c and
+// P_0 = r0 - sum y_i v_i.  HBM-bound: K + 1 vectors read for the products and K + 2 read and 2
+// written for the update, where a form that orthogonalises or minimises at every step reads
+// j + 2 and j + 2 vectors and writes one at each step j and needs three launches there.
+// 256^2 x 16 FP32, 5 steps: 73 vector passes and 25 launches a cycle before (with the
+// stencils), 42 passes and 13 launches now.
+namespace {
+constexpr int ss_nq(int k) { return (k + 1) * (k + 1); }   // real sums of a (k+1)^2 Hermitian H
+// complex entries of one 16-byte word, and their sum over a word
+template <typename T> struct Word;
+template <> struct Word<float> {
+    typedef float type __attribute__((ext_vector_type(4)));
+    static constexpr int E = 2;
+    static __device__ __forceinline__ cpx<double> at(const type& w, int e) { return {(double)w[2 * e], (double)w[2 * e + 1]}; }
+    static __device__ __forceinline__ void put(type& w, int e, cpx<double> v) { w[2 * e] = (float)v.re; w[2 * e + 1] = (float)v.im; }
+};
+template <> struct Word<double> {
+    typedef double type __attribute__((ext_vector_type(2)));
+    static constexpr int E = 1;
+    static __device__ __forceinline__ cpx<double> at(const type& w, int) { return {w[0], w[1]}; }
+    static __device__ __forceinline__ void put(type& w, int, cpx<double> v) { w[0] = v.re; w[1] = v.im; }
+};
+// offset of H_ab (a < b, two reals) behind the k + 1 diagonal entries
+constexpr int ss_off(int k, int a, int b) { return (k + 1) + 2 * (a * (2 * k + 1 - a) / 2 + (b - a - 1)); }
 
-template <typename T, int j>
-__global__ void __launch_bounds__(kBlock)
-k_gcr_gram_step(const cpx<T>* W, size_t wstride, const cpx<T>* r0, cpx<T>* out, size_t n, const int* stop_in,
-                GcrDev g) {
-    constexpr int m = j + 1;
-    const int col = blockIdx.y;
-    const size_t o = (size_t)col * n;
-    // the coefficients are loaded with the stop flag, one wait for both (the empty asm
-    // statements take them before the branch; the compiler would otherwise move the
-    // coefficient loads below it, a second round trip)
-    const double* gam = g.gam + 2 * (size_t)col * g.kmax;
-    double gv[2 * m];
+// Sum v[0..NP) over the 64 lanes by halving: lanes that differ in one bit exchange half of their
+// values each, so NP sums take NP - 1 exchanges instead of 6 NP.  The total of value i ends in
+// v[0] of the lanes whose bits 0.. hold i (log2 NP of them, most significant bit of i first).
+template <int NP>
+__device__ __forceinline__ void reduce_scatter(double* v, int lane) {
+    int bit = 1;
 #pragma unroll
-    for (int i = 0; i < 2 * m; ++i) gv[i] = gam[i];
-    const int sflag = stop_in[col];
+    for (int h = NP / 2; h >= 1; h >>= 1, bit <<= 1) {
+        const bool up = lane & bit;
 #pragma unroll
-    for (int i = 0; i < 2 * m; ++i) asm volatile("" ::"s"(gv[i]));
-    cpx<T> c[m];
-#pragma unroll
-    for (int i = 0; i < m; ++i) c[i] = {(T)gv[2 * i], (T)gv[2 * i + 1]};
-    if (sflag != 0) {   // (block-uniform) a stopped column's later directions are zero; r0 is kept
-        if (out != r0) GRID_STRIDE(e, n) out[o + e] = cpx<T>{(T)0, (T)0};
-        return;
-    }
-    constexpr int U = gcr_unroll<T>(j);
-    const size_t stride = (size_t)gridDim.x * blockDim.x;
-    auto step = [&](size_t i0, cpx<T> re, const cpx<T>* Wt) {
-#pragma unroll
-        for (int i = 0; i < m; ++i) {
-            re.re -= c[i].re * Wt[i].re - c[i].im * Wt[i].im;
-            re.im -= c[i].re * Wt[i].im + c[i].im * Wt[i].re;
+        for (int i = 0; i < h; ++i) {
+            const double keep = up ? v[i + h] : v[i], give = up ? v[i] : v[i + h];
+            v[i] = keep + __shfl_xor(give, bit, 64);
         }
-        out[i0] = re;
-    };
-    size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (; e + (U - 1) * stride < n; e += U * stride) {
-        cpx<T> rv[U], Wv[U][m];
-#pragma unroll
-        for (int u2 = 0; u2 < U; ++u2) {
-            rv[u2] = r0[o + e + u2 * stride];
-#pragma unroll
-            for (int i = 0; i < m; ++i) Wv[u2][i] = W[(size_t)i * wstride + o + e + u2 * stride];
-        }
-#pragma unroll
-        for (int u2 = 0; u2 < U; ++u2) step(o + e + u2 * stride, rv[u2], Wv[u2]);
     }
-    for (; e < n; e += stride) {
-        cpx<T> Wt[m];
-#pragma unroll
-        for (int i = 0; i < m; ++i) Wt[i] = W[(size_t)i * wstride + o + e];
-        step(o + e, r0[o + e], Wt);
-    }
+    for (; bit < 64; bit <<= 1) v[0] += __shfl_xor(v[0], bit, 64);
 }
+// the value whose total lane `lane` holds after reduce_scatter<NP>
+template <int NP>
+__device__ __forceinline__ int scatter_index(int lane) {
+    int i = 0, bit = 1;
+#pragma unroll
+    for (int h = NP / 2; h >= 1; h >>= 1, bit <<= 1) i |= (lane & bit) ? h : 0;
+    return i;
+}
+}  // namespace
 
-// The last Gram-form step of a cycle together with the cycle's solution update: with
-// P_0 = r0 (the cycle's starting residual, the first direction), x += sum_{i<K} y_i P_i and
-// P_0 = r0 - sum_{i<K} y_i W_i (the next cycle's starting residual) in one pass, element
-// by element in place.
 template <typename T, int K>
-__global__ void __launch_bounds__(kBlock)
-k_gcr_gram_last(cpx<T>* P, const cpx<T>* W, size_t stride_v, cpx<T>* x, size_t n, const int* stop_src, GcrDev g,
-                int ncol) {
+__global__ void __launch_bounds__(kBlock, 2) k_ss_dots(SsVecs<T> P, size_t nw, RedWork rw) {
+    using W = Word<T>;
+    typedef typename W::type word;
+    constexpr int NQ = ss_nq(K);
+    // sums in one group of a power of two up to 64, and a second small one where that fits better
+    constexpr int N1 = NQ <= 4 ? 4 : (NQ <= 16 ? 16 : (NQ <= 36 ? 32 : 64));
+    constexpr int N2 = NQ <= N1 ? 0 : (NQ - N1 <= 4 ? 4 : 32);
+    static_assert(NQ <= N1 + N2, "two groups hold every sum");
+    __shared__ double sh[kWaves][N1 + N2];
     const int col = blockIdx.y;
-    const size_t o = (size_t)col * n;
-    if (stop_src != g.stop && blockIdx.x == 0 && blockIdx.y == 0)
-        for (int cc = threadIdx.x; cc < ncol; cc += blockDim.x) g.stop[cc] = stop_src[cc];
-    const double* gam = g.gam + 2 * (size_t)col * g.kmax;
-    cpx<double> c[K];
+    const size_t o = (size_t)col * nw;
+    const word* p[K + 1];
 #pragma unroll
-    for (int i = 0; i < K; ++i) c[i] = {gam[2 * i], gam[2 * i + 1]};
-    GRID_STRIDE(e, n) {
-        cpx<double> acc = {(double)x[o + e].re, (double)x[o + e].im};
-        cpx<T> rn = P[o + e];
+    for (int a = 0; a <= K; ++a) p[a] = reinterpret_cast<const word*>(P.p[a]) + o;
+    double v[N1 + (N2 > 0 ? N2 : 1)];
 #pragma unroll
-        for (int i = 0; i < K; ++i) {
-            const cpx<double> p = up(P[(size_t)i * stride_v + o + e]);
-            acc.re += c[i].re * p.re - c[i].im * p.im;
-            acc.im += c[i].re * p.im + c[i].im * p.re;
-            const cpx<T> wv = W[(size_t)i * stride_v + o + e];
-            const cpx<T> ci = {(T)c[i].re, (T)c[i].im};
-            rn.re -= ci.re * wv.re - ci.im * wv.im;
-            rn.im -= ci.re * wv.im + ci.im * wv.re;
+    for (int q = 0; q < N1 + N2; ++q) v[q] = 0.0;
+    auto add = [&](const word* w) {
+#pragma unroll
+        for (int e = 0; e < W::E; ++e) {
+            cpx<double> z[K + 1];
+#pragma unroll
+            for (int a = 0; a <= K; ++a) z[a] = W::at(w[a], e);
+#pragma unroll
+            for (int a = 0; a <= K; ++a) {
+                v[a] += z[a].re * z[a].re + z[a].im * z[a].im;
+#pragma unroll
+                for (int b = a + 1; b <= K; ++b) {
+                    const int q = ss_off(K, a, b);
+                    v[q] += z[a].re * z[b].re + z[a].im * z[b].im;
+                    v[q + 1] += z[a].re * z[b].im - z[a].im * z[b].re;
+                }
+            }
         }
-        x[o + e] = {(T)acc.re, (T)acc.im};
-        P[o + e] = rn;
+    };
+    // U words of every vector are loaded together (bounded by the registers beside the sums)
+    constexpr int U = K <= 3 ? 4 : (K <= 5 || (K == 6 && W::E == 1) ? 2 : 1);
+    const size_t stride = (size_t)gridDim.x * kBlock;
+    size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    for (; e + (U - 1) * stride < nw; e += U * stride) {
+        word w[U][K + 1];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int a = 0; a <= K; ++a) w[u][a] = p[a][e + u * stride];
+#pragma unroll
+        for (int u = 0; u < U; ++u) add(w[u]);
+    }
+    for (; e < nw; e += stride) {
+        word w[K + 1];
+#pragma unroll
+        for (int a = 0; a <= K; ++a) w[a] = p[a][e];
+        add(w);
+    }
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    reduce_scatter<N1>(v, lane);
+    if (lane < N1) sh[wid][scatter_index<N1>(lane)] = v[0];
+    if constexpr (N2 > 0) {
+        reduce_scatter<N2>(v + N1, lane);
+        if (lane < N2) sh[wid][N1 + scatter_index<N2>(lane)] = v[N1];
+    }
+    __syncthreads();
+    // partials block by block, the sums of one block side by side
+    double* part = rw.partial + (size_t)col * rw.max_q * rw.nblk + (size_t)blockIdx.x * NQ;
+    for (int q = threadIdx.x; q < NQ; q += kBlock) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) t += sh[w][q];
+        part[q] = t;
+    }
+}
+
+// One workgroup per column: wave w adds the partials of blocks w, w + 16, ... (lane = sum), then
+// wave 0 factors G by Cholesky with lane i holding row i.  The residual norm after step k is
+// |r0|^2 - sum_{i<=k} |u_i|^2 (u = L^-1 b), so a tolerance met inside the cycle ends it at that
+// step: the coefficients are those of its leading block.  A pivot within rounding of zero
+// against its direction's own norm drops that direction.
+constexpr int kSsFinWaves = 16;
+constexpr double kSsPivot = 1e-13;
+template <int K>
+__global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb, GcrDev g, double tol2, double inv_c,
+                                                            int first) {
+    constexpr int NQ = ss_nq(K);
+    constexpr int NR = (NQ + 63) / 64;
+    __shared__ double sp[kSsFinWaves][NQ];
+    __shared__ double H[NQ];
+    __shared__ cpx<double> sL[K][K];
+    const int col = blockIdx.x;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const double* part = rw.partial + (size_t)col * rw.max_q * rw.nblk;
+    const int flag0 = first ? 0 : g.stop[col];
+    const int it0 = first ? 0 : g.it[col];
+    const double bb0 = first ? -1.0 : g.bb[col];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int q = r * 64 + lane;
+        const bool on = q < NQ;
+        double s = 0.0;
+#pragma unroll 8
+        for (int b = wid; b < nb; b += kSsFinWaves) s += part[(size_t)b * NQ + (on ? q : 0)];
+        if (on) sp[wid][q] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x < NQ) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < kSsFinWaves; ++w) s += sp[w][threadIdx.x];
+        H[threadIdx.x] = s;
+    }
+    __syncthreads();
+    if (wid != 0) return;
+    double* coef = g.tot + (size_t)col * kGcrTot;   // y_i / c (2 K), then P_0's change (2 K + 2), then the live flag
+    bool sane = true;
+#pragma unroll
+    for (int a = 0; a <= K; ++a) sane = sane && finite(H[a]);
+    const double rr0 = H[0];
+    const double bb = bb0 < 0.0 ? rr0 : bb0;
+    int flag = flag0;
+    if (flag == 0 && !sane) flag = 2;
+    if (flag == 0 && rr0 == 0.0) flag = 1;
+    if (flag != 0) {   // the column takes no update
+        if (lane == 0) {
+            coef[kGcrTot - 1] = 0.0;
+            g.stop[col] = flag;
+            g.it[col] = it0;
+            g.bb[col] = bb;
+        }
+        return;
+    }
+    auto h = [&](int a, int b) -> cpx<double> {
+        if (a == b) return {H[a], 0.0};
+        const int q = a < b ? ss_off(K, a, b) : ss_off(K, b, a);
+        return {H[q], a < b ? H[q + 1] : -H[q + 1]};
+    };
+    const int i = lane < K ? lane : K - 1;   // (lanes past the last row repeat it)
+    cpx<double> G[K], bi = h(i + 1, 0) + h(i, 0);
+    double dg = 0.0;
+#pragma unroll
+    for (int l = 0; l < K; ++l) {
+        G[l] = h(i + 1, l + 1) + h(i + 1, l) + h(i, l + 1) + h(i, l);
+        if (l == i) dg = G[l].re;
+    }
+    // value of lane l, the same for the whole wave
+    auto bcast = [](double x, int l) {
+        const int lo = __builtin_amdgcn_readlane(__double2loint(x), l), hi = __builtin_amdgcn_readlane(__double2hiint(x), l);
+        return __hiloint2double(hi, lo);
+    };
+    double rr = rr0, inv[K];
+    cpx<double> u[K];
+    int kend = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        inv[k] = 0.0;
+        u[k] = {0.0, 0.0};
+        if (flag == 0) {   // (uniform)
+            const double d = bcast(G[k].re, k), d0 = bcast(dg, k);
+            const bool ok = d > kSsPivot * d0 && finite(d);
+            inv[k] = ok ? 1.0 / sqrt(d) : 0.0;
+            u[k] = {bcast(bi.re, k) * inv[k], bcast(bi.im, k) * inv[k]};
+            const cpx<double> lk = {G[k].re * inv[k], G[k].im * inv[k]};   // L_ik of this lane's row
+            if (lane < K) sL[i][k] = lk;
+#pragma unroll
+            for (int l = k + 1; l < K; ++l) {   // G_il -= L_ik conj(L_lk)
+                const cpx<double> ll = {bcast(lk.re, l), bcast(lk.im, l)};
+                G[l].re -= lk.re * ll.re + lk.im * ll.im;
+                G[l].im -= lk.im * ll.re - lk.re * ll.im;
+            }
+            bi.re -= lk.re * u[k].re - lk.im * u[k].im;
+            bi.im -= lk.re * u[k].im + lk.im * u[k].re;
+            rr -= u[k].re * u[k].re + u[k].im * u[k].im;
+            kend = k + 1;
+            if (!finite(rr)) flag = 2;
+            else if (rr <= tol2 * bb) flag = 1;
+        }
+    }
+    if (lane != 0) return;
+    cpx<double> y[K + 1];
+    y[K] = {0.0, 0.0};
+#pragma unroll
+    for (int k = K - 1; k >= 0; --k) {   // L^H y = u over the steps taken
+        cpx<double> acc = u[k];
+#pragma unroll
+        for (int l = k + 1; l < K; ++l) {
+            if (l < kend) {
+                const cpx<double> t = cjmul(sL[l][k], y[l]);
+                acc.re -= t.re;
+                acc.im -= t.im;
+            }
+        }
+        y[k] = {acc.re * inv[k], acc.im * inv[k]};
+        if (k >= kend || flag == 2) y[k] = {0.0, 0.0};
+    }
+    double* e = coef + 2 * K;
+#pragma unroll
+    for (int k = 0; k <= K; ++k) {
+        const cpx<double> prev = k > 0 ? y[k - 1] : cpx<double>{0.0, 0.0};
+        e[2 * k] = -(y[k].re + prev.re);
+        e[2 * k + 1] = -(y[k].im + prev.im);
+        if (k < K) {
+            coef[2 * k] = y[k].re * inv_c;
+            coef[2 * k + 1] = y[k].im * inv_c;
+        }
+    }
+    coef[kGcrTot - 1] = flag == 2 ? 0.0 : 1.0;
+    g.stop[col] = flag;
+    g.it[col] = it0 + kend;
+    g.bb[col] = bb;
+}
+
+template <typename T, int K>
+__global__ void __launch_bounds__(kBlock) k_ss_update(SsVecs<T> P, cpx<T>* x, size_t nw, GcrDev g) {
+    using W = Word<T>;
+    typedef typename W::type word;
+    const int col = blockIdx.y;
+    const double* coef = g.tot + (size_t)col * kGcrTot;
+    cpx<double> y[K], d[K + 1];
+#pragma unroll
+    for (int k = 0; k < K; ++k) y[k] = ld2(coef + 2 * k);
+#pragma unroll
+    for (int k = 0; k <= K; ++k) d[k] = ld2(coef + 2 * K + 2 * k);
+    if (coef[kGcrTot - 1] == 0.0) return;   // a column that takes no update (its vectors may be anything)
+    const size_t o = (size_t)col * nw;
+    word* xw = reinterpret_cast<word*>(x) + o;
+    word* p0 = reinterpret_cast<word*>(P.p[0]) + o;
+    auto step = [&](size_t e, const word* w, word xv) {
+        word r;
+#pragma unroll
+        for (int c = 0; c < W::E; ++c) {
+            cpx<double> xa = W::at(xv, c), ra = W::at(w[0], c);
+#pragma unroll
+            for (int k = 0; k <= K; ++k) {
+                const cpx<double> z = W::at(w[k], c);
+                if (k < K) {
+                    xa.re += y[k].re * z.re - y[k].im * z.im;
+                    xa.im += y[k].re * z.im + y[k].im * z.re;
+                }
+                ra.re += d[k].re * z.re - d[k].im * z.im;
+                ra.im += d[k].re * z.im + d[k].im * z.re;
+            }
+            W::put(xv, c, xa);
+            W::put(r, c, ra);
+        }
+        xw[e] = xv;
+        p0[e] = r;
+    };
+    constexpr int U = K <= 6 ? 2 : 1;
+    const size_t stride = (size_t)gridDim.x * kBlock;
+    size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    for (; e + (U - 1) * stride < nw; e += U * stride) {
+        word w[U][K + 1], xv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int k = 0; k <= K; ++k) w[u][k] = reinterpret_cast<const word*>(P.p[k])[o + e + u * stride];
+            xv[u] = xw[e + u * stride];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) step(e + u * stride, w[u], xv[u]);
+    }
+    for (; e < nw; e += stride) {
+        word w[K + 1];
+#pragma unroll
+        for (int k = 0; k <= K; ++k) w[k] = reinterpret_cast<const word*>(P.p[k])[o + e];
+        step(e, w, xw[e]);
+    }
+}
+
+// start of a device-driven s-step solve: P_0 = b, x = 0, and the columns' state (|b|^2 not known yet)
+template <typename T>
+__global__ void k_ss_begin(const cpx<T>* b, cpx<T>* P0, cpx<T>* x, size_t n, int ncol, GcrDev g) {
+    if (blockIdx.x == 0)
+        for (int c = threadIdx.x; c < ncol; c += blockDim.x) {
+            g.stop[c] = 0;
+            g.it[c] = 0;
+            g.bb[c] = -1.0;
+        }
+    GRID_STRIDE(i, n) {
+        P0[i] = b[i];
+        x[i] = cpx<T>{T(0), T(0)};
     }
 }
 
@@ -1067,43 +1167,28 @@ hipError_t gcr_fused_step(const cpx<T>* W, size_t wstride, int j, cpx<T>* w, cpx
     return hipGetLastError();
 }
 template <typename T>
-hipError_t gcr_gram_step(const cpx<T>* W, size_t wstride, int j, const cpx<T>* r0, cpx<T>* out, size_t n, int ncol,
-                         double tol2, const int* stop_in, int* stop_out, const GcrDev& g, const RedWork& rw,
-                         hipStream_t st) {
-    if (j < 0 || j >= kGramMax || 2 * j + 3 > kGcrTot || 2 * j + 3 > rw.max_q || j >= g.kmax) return hipErrorInvalidValue;
-    // at most kGramPartials multi-dot blocks: the finaliser's waves each add that many partials
-    dim3 grid = red_grid(n, ncol, rw);
-    grid.x = std::min(grid.x, (unsigned)kGramPartials);
-    auto launch = [&](auto jc) {
-        constexpr int J = decltype(jc)::value;
-        hipLaunchKernelGGL((k_gcr_dots<T, J>), grid, dim3(kBlock), 0, st, W, wstride, W + (size_t)J * wstride, r0, n,
-                           stop_in, rw);
-        hipLaunchKernelGGL(k_fin_gram<J>, dim3(ncol), dim3(64 * (2 * J + 3)), 0, st, rw, (int)grid.x, stop_in, stop_out,
-                           g, tol2, 0);
-        hipLaunchKernelGGL((k_gcr_gram_step<T, J>), ew_grid(n, ncol), dim3(kBlock), 0, st, W, wstride, r0, out, n,
-                           stop_in, g);
-    };
-    with_j(j, launch, std::make_integer_sequence<int, kGramMax>{});
+hipError_t ss_begin(const cpx<T>* b, cpx<T>* P0, cpx<T>* x, size_t n, int ncol, const GcrDev& g, hipStream_t st) {
+    hipLaunchKernelGGL(k_ss_begin<T>, ew_grid(n * ncol, 1), dim3(kBlock), 0, st, b, P0, x, n * ncol, ncol, g);
     return hipGetLastError();
 }
 template <typename T>
-hipError_t gcr_gram_last(cpx<T>* P, const cpx<T>* W, size_t stride_v, int k, cpx<T>* x, size_t n, int ncol,
-                         double tol2, const int* stop_in, int* stop_out, const GcrDev& g, const RedWork& rw,
-                         hipStream_t st) {
-    const int j = k - 1;
-    if (j < 0 || j >= kGramMax || 2 * j + 3 > kGcrTot || 2 * j + 3 > rw.max_q || j >= g.kmax) return hipErrorInvalidValue;
-    dim3 grid = red_grid(n, ncol, rw);
-    grid.x = std::min(grid.x, (unsigned)kGramPartials);
-    auto launch = [&](auto jc) {
-        constexpr int J = decltype(jc)::value;
-        hipLaunchKernelGGL((k_gcr_dots<T, J>), grid, dim3(kBlock), 0, st, W, stride_v, W + (size_t)J * stride_v, P, n,
-                           stop_in, rw);
-        hipLaunchKernelGGL(k_fin_gram<J>, dim3(ncol), dim3(64 * (2 * J + 3)), 0, st, rw, (int)grid.x, stop_in, stop_out,
-                           g, tol2, 1);
-        hipLaunchKernelGGL((k_gcr_gram_last<T, J + 1>), ew_grid(n, ncol), dim3(kBlock), 0, st, P, W, stride_v, x, n,
-                           stop_out, g, ncol);
+hipError_t ss_finish(const SsVecs<T>& P, int k, cpx<T>* x, size_t n, int ncol, double c, double tol2, bool first,
+                     const GcrDev& g, const RedWork& rw, hipStream_t st) {
+    if (k < 1 || k > kSsMax || 4 * k + 3 > kGcrTot || n % Word<T>::E) return hipErrorInvalidValue;
+    const size_t nw = n / Word<T>::E;
+    // blocks per column: two words per thread at least, two workgroups per CU over all columns
+    // (a block's sums cost as much as streaming several words, and one workgroup adds them all)
+    long long nb = (long long)((nw + 2 * kBlock - 1) / (2 * kBlock));
+    nb = std::min<long long>(nb, std::max(kSsBlocks / ncol, 64));
+    nb = std::max<long long>(std::min<long long>(nb, (long long)rw.max_q * rw.nblk / ss_nq(k)), 1);
+    auto launch = [&](auto kc) {
+        constexpr int K = decltype(kc)::value + 1;
+        hipLaunchKernelGGL((k_ss_dots<T, K>), dim3((unsigned)nb, ncol), dim3(kBlock), 0, st, P, nw, rw);
+        hipLaunchKernelGGL(k_ss_fin<K>, dim3(ncol), dim3(64 * kSsFinWaves), 0, st, rw, (int)nb, g, tol2, 1.0 / c,
+                           first ? 1 : 0);
+        hipLaunchKernelGGL((k_ss_update<T, K>), ew_grid(nw, ncol), dim3(kBlock), 0, st, P, x, nw, g);
     };
-    with_j(j, launch, std::make_integer_sequence<int, kGramMax>{});
+    with_j(k - 1, launch, std::make_integer_sequence<int, kSsMax>{});
     return hipGetLastError();
 }
 template <typename T>
@@ -1211,10 +1296,10 @@ template hipError_t gcr_xupdate<double, double>(const cpx<double>*, size_t, int,
 template hipError_t gcr_xupdate<float, double>(const cpx<float>*, size_t, int, cpx<double>*, size_t, int, bool, const GcrDev&, hipStream_t);
 template hipError_t gcr_solve_xupdate<float, float>(const cpx<float>*, size_t, int, cpx<float>*, size_t, int, bool, const GcrDev&, hipStream_t);
 template hipError_t gcr_solve_xupdate<double, double>(const cpx<double>*, size_t, int, cpx<double>*, size_t, int, bool, const GcrDev&, hipStream_t);
-template hipError_t gcr_gram_step<float>(const cpx<float>*, size_t, int, const cpx<float>*, cpx<float>*, size_t, int, double, const int*, int*, const GcrDev&, const RedWork&, hipStream_t);
-template hipError_t gcr_gram_step<double>(const cpx<double>*, size_t, int, const cpx<double>*, cpx<double>*, size_t, int, double, const int*, int*, const GcrDev&, const RedWork&, hipStream_t);
-template hipError_t gcr_gram_last<float>(cpx<float>*, const cpx<float>*, size_t, int, cpx<float>*, size_t, int, double, const int*, int*, const GcrDev&, const RedWork&, hipStream_t);
-template hipError_t gcr_gram_last<double>(cpx<double>*, const cpx<double>*, size_t, int, cpx<double>*, size_t, int, double, const int*, int*, const GcrDev&, const RedWork&, hipStream_t);
+template hipError_t ss_begin<float>(const cpx<float>*, cpx<float>*, cpx<float>*, size_t, int, const GcrDev&, hipStream_t);
+template hipError_t ss_begin<double>(const cpx<double>*, cpx<double>*, cpx<double>*, size_t, int, const GcrDev&, hipStream_t);
+template hipError_t ss_finish<float>(const SsVecs<float>&, int, cpx<float>*, size_t, int, double, double, bool, const GcrDev&, const RedWork&, hipStream_t);
+template hipError_t ss_finish<double>(const SsVecs<double>&, int, cpx<double>*, size_t, int, double, double, bool, const GcrDev&, const RedWork&, hipStream_t);
 template hipError_t gcr_solve_xupdate_restart<float>(cpx<float>*, size_t, int, cpx<float>*, size_t, int, const cpx<float>*, const int*, const GcrDev&, hipStream_t);
 template hipError_t gcr_solve_xupdate_restart<double>(cpx<double>*, size_t, int, cpx<double>*, size_t, int, const cpx<double>*, const int*, const GcrDev&, hipStream_t);
 

@@ -22,7 +22,8 @@ template <typename L, typename T, int N, bool DAG, bool WIL>
 __global__ void __launch_bounds__(256)
 coarse_kernel(const L* __restrict__ links, const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out,
               const int* __restrict__ skip, int skip_stride, int Lx, int Ly, int Ls, int nsites,
-              typename acc_of<L>::type cdiag, typename acc_of<L>::type mwrap) {
+              typename acc_of<L>::type cdiag, typename acc_of<L>::type mwrap, const cpx<T>* __restrict__ eb, T ealpha,
+              T ebeta) {
     using A = typename acc_of<L>::type;
     constexpr int P = (N <= 64) ? (64 / N) : 1;   // partitions of the inner index
     constexpr int MAXS = 8;                       // slices accumulated per pass
@@ -118,7 +119,13 @@ coarse_kernel(const L* __restrict__ links, const cpx<T>* __restrict__ in, cpx<T>
                     v.re += f * (A)h.re;
                     v.im += f * (A)h.im;
                 }
-                dst[((size_t)s * nsites + site) * N + i] = {(T)v.re, (T)v.im};
+                const size_t oi = ((size_t)s * nsites + site) * N + i;
+                cpx<T> o = {(T)v.re, (T)v.im};
+                if (eb) {   // beta eb + alpha (operator in)
+                    const cpx<T> b = eb[(size_t)col * Ls * nsites * N + oi];
+                    o = {ealpha * o.re + ebeta * b.re, ealpha * o.im + ebeta * b.im};
+                }
+                dst[oi] = o;
             }
         }
         if (P > 1) __syncthreads();   // scr is rewritten by the next pass
@@ -129,7 +136,8 @@ namespace {
 
 template <typename L, typename T, int N>
 hipError_t launch_n(const void* links, const cpx<T>* in, cpx<T>* out, const CoarseGeom& g, int ncol,
-                    double m, double M5, bool dagger, bool wil, double wmass, const int* skip, int sks, hipStream_t st) {
+                    double m, double M5, bool dagger, bool wil, double wmass, const int* skip, int sks, hipStream_t st,
+                    const Epi<T>& epi) {
     using A = typename acc_of<L>::type;
     const int nsites = g.Lx * g.Ly;
     size_t per_wave_bytes = (size_t)coarse_lds_per_wave(N, g.Ls) * sizeof(cpx<A>);
@@ -142,27 +150,28 @@ hipError_t launch_n(const void* links, const cpx<T>* in, cpx<T>* out, const Coar
     const A cd = wil ? (A)wmass : (A)(M5 + 1.0);
     const A mw = (A)(-m);
     if (wil) {
-        if (dagger) hipLaunchKernelGGL((coarse_kernel<L, T, N, true, true>), grid, block, shm, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw);
-        else        hipLaunchKernelGGL((coarse_kernel<L, T, N, false, true>), grid, block, shm, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw);
+        if (dagger) hipLaunchKernelGGL((coarse_kernel<L, T, N, true, true>), grid, block, shm, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw, epi.b, (T)epi.alpha, (T)epi.beta);
+        else        hipLaunchKernelGGL((coarse_kernel<L, T, N, false, true>), grid, block, shm, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw, epi.b, (T)epi.alpha, (T)epi.beta);
     } else {
-        if (dagger) hipLaunchKernelGGL((coarse_kernel<L, T, N, true, false>), grid, block, shm, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw);
-        else        hipLaunchKernelGGL((coarse_kernel<L, T, N, false, false>), grid, block, shm, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw);
+        if (dagger) hipLaunchKernelGGL((coarse_kernel<L, T, N, true, false>), grid, block, shm, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw, epi.b, (T)epi.alpha, (T)epi.beta);
+        else        hipLaunchKernelGGL((coarse_kernel<L, T, N, false, false>), grid, block, shm, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw, epi.b, (T)epi.alpha, (T)epi.beta);
     }
     return hipGetLastError();
 }
 
 template <typename L, typename T>
 hipError_t launch_l(const void* links, const cpx<T>* in, cpx<T>* out, const CoarseGeom& g, int ncol,
-                    double m, double M5, bool dagger, bool wil, double wmass, const int* skip, int sks, hipStream_t st) {
+                    double m, double M5, bool dagger, bool wil, double wmass, const int* skip, int sks, hipStream_t st,
+                    const Epi<T>& epi) {
     switch (g.n) {
-        case 4:  return launch_n<L, T, 4>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st);
-        case 8:  return launch_n<L, T, 8>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st);
-        case 12: return launch_n<L, T, 12>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st);
-        case 16: return launch_n<L, T, 16>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st);
-        case 24: return launch_n<L, T, 24>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st);
-        case 32: return launch_n<L, T, 32>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st);
-        case 48: return launch_n<L, T, 48>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st);
-        case 64: return launch_n<L, T, 64>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st);
+        case 4:  return launch_n<L, T, 4>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 8:  return launch_n<L, T, 8>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 12: return launch_n<L, T, 12>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 16: return launch_n<L, T, 16>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 24: return launch_n<L, T, 24>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 32: return launch_n<L, T, 32>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 48: return launch_n<L, T, 48>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 64: return launch_n<L, T, 64>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
         default: return hipErrorInvalidValue;
     }
 }
@@ -172,20 +181,21 @@ hipError_t launch_l(const void* links, const cpx<T>* in, cpx<T>* out, const Coar
 template <typename T>
 hipError_t coarse_apply(const void* links, int link_prec, const cpx<T>* in, cpx<T>* out,
                         const CoarseGeom& g, int ncol, double m, double M5, bool dagger,
-                        bool wilson_mode, double wilson_mass, const int* skip, int sks, hipStream_t st) {
+                        bool wilson_mode, double wilson_mass, const int* skip, int sks, hipStream_t st,
+                        const Epi<T>& epi) {
     if (g.Ls < 1 || g.Ls > kMaxCoarseLs) return hipErrorInvalidValue;
     if (!wilson_mode && coarse_mfma_supported(g.n, link_prec))
-        return coarse_apply_mfma<T>(links, link_prec, in, out, g, ncol, m, M5, dagger, skip, sks, st);
+        return coarse_apply_mfma<T>(links, link_prec, in, out, g, ncol, m, M5, dagger, skip, sks, st, epi);
     switch (link_prec) {
-        case P_F64: return launch_l<cpx<double>, T>(links, in, out, g, ncol, m, M5, dagger, wilson_mode, wilson_mass, skip, sks, st);
-        case P_F32: return launch_l<cpx<float>, T>(links, in, out, g, ncol, m, M5, dagger, wilson_mode, wilson_mass, skip, sks, st);
-        case P_BF16: return launch_l<cbf16, T>(links, in, out, g, ncol, m, M5, dagger, wilson_mode, wilson_mass, skip, sks, st);
-        case P_F16: return launch_l<cf16, T>(links, in, out, g, ncol, m, M5, dagger, wilson_mode, wilson_mass, skip, sks, st);
+        case P_F64: return launch_l<cpx<double>, T>(links, in, out, g, ncol, m, M5, dagger, wilson_mode, wilson_mass, skip, sks, st, epi);
+        case P_F32: return launch_l<cpx<float>, T>(links, in, out, g, ncol, m, M5, dagger, wilson_mode, wilson_mass, skip, sks, st, epi);
+        case P_BF16: return launch_l<cbf16, T>(links, in, out, g, ncol, m, M5, dagger, wilson_mode, wilson_mass, skip, sks, st, epi);
+        case P_F16: return launch_l<cf16, T>(links, in, out, g, ncol, m, M5, dagger, wilson_mode, wilson_mass, skip, sks, st, epi);
         default: return hipErrorInvalidValue;
     }
 }
 
-template hipError_t coarse_apply<float>(const void*, int, const cpx<float>*, cpx<float>*, const CoarseGeom&, int, double, double, bool, bool, double, const int*, int, hipStream_t);
-template hipError_t coarse_apply<double>(const void*, int, const cpx<double>*, cpx<double>*, const CoarseGeom&, int, double, double, bool, bool, double, const int*, int, hipStream_t);
+template hipError_t coarse_apply<float>(const void*, int, const cpx<float>*, cpx<float>*, const CoarseGeom&, int, double, double, bool, bool, double, const int*, int, hipStream_t, const Epi<float>&);
+template hipError_t coarse_apply<double>(const void*, int, const cpx<double>*, cpx<double>*, const CoarseGeom&, int, double, double, bool, bool, double, const int*, int, hipStream_t, const Epi<double>&);
 
 }  // namespace dwf

@@ -105,11 +105,12 @@ __device__ __forceinline__ void load4(const cpx<T>* p, float (&re)[4], float (&i
 
 }  // namespace
 
-template <bool F16, typename TI, typename TO, int N, bool DAG, int TW>
+// (EPI: out = eb beta + alpha times the operator, in the output's precision)
+template <bool F16, typename TI, typename TO, int N, bool DAG, int TW, bool EPI>
 __global__ void __launch_bounds__(256)
 coarse_mfma_kernel(const u32x4* __restrict__ links, const cpx<TI>* __restrict__ in, cpx<TO>* __restrict__ out,
                    const int* __restrict__ skip, int sks, int Lx, int Ly, int Ls, int nsites, int ncol,
-                   float cdiag, float mwrap, int tpb) {
+                   float cdiag, float mwrap, int tpb, const cpx<TO>* __restrict__ eb, TO ealpha, TO ebeta) {
     using HF = Half<F16>;
     constexpr int MT = N / 16;                    // row tiles = waves per site
     constexpr int SPB = 1;                        // sites per block (measured: one is best)
@@ -271,9 +272,19 @@ coarse_mfma_kernel(const u32x4* __restrict__ links, const cpx<TI>* __restrict__ 
                 load4<TI>(in + ((uint32_t)(rhs * Ls + so) * nsites + nb[0]) * N + i0, hr, hi);
             }
         };
+        // the epilogue's second operand, by the lanes that write
+        cpx<TO> eo[4] = {};
+        const uint32_t oidx = ((uint32_t)cl * nsites + nb[0]) * N + i0;
+        auto load_epi = [&]() {
+            if (EPI && q < TW) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) eo[e] = eb[oidx + e];
+            }
+        };
         if (TW < 8) {
             load_links();
             load_local();
+            load_epi();
         }
         // keep the uses below (the ballot first) from being scheduled above the loads
         __builtin_amdgcn_sched_barrier(0);
@@ -380,16 +391,22 @@ coarse_mfma_kernel(const u32x4* __restrict__ links, const cpx<TI>* __restrict__ 
         for (int e = 0; e < 4; ++e) p[e] = __shfl_xor(acc[e], 8, 64);
         const bool wr = valid_site && !imag_col && col_ok(cbase + (q & 7));
         if (wr) {
-            cpx<TO>* dst = out + ((uint32_t)cl * nsites + site) * N + i0;
+            cpx<TO>* dst = out + oidx;
             const float u = unscale * osg;
             if (TW == 8) {   // several tiles: the site-local terms are loaded here, by the writing lanes
                 load_local();
+                load_epi();
+            }
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    dst[e] = {(TO)(acc[e] * u + cdiag * cr[e] + f * hr[e]), (TO)(p[e] * u + cdiag * ci[e] + f * hi[e])};
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) dst[e] = {(TO)(acc[e] * u), (TO)(p[e] * u)};
+            for (int e = 0; e < 4; ++e) {
+                float re = acc[e] * u, im = p[e] * u;
+                if (TW == 8) {
+                    re = acc[e] * u + cdiag * cr[e] + f * hr[e];
+                    im = p[e] * u + cdiag * ci[e] + f * hi[e];
+                }
+                cpx<TO> v = {(TO)re, (TO)im};
+                if (EPI) v = {ealpha * v.re + ebeta * eo[e].re, ealpha * v.im + ebeta * eo[e].im};
+                dst[e] = v;
             }
         }
         __syncthreads();   // sB and smax are rewritten for the next column tile
@@ -400,7 +417,8 @@ namespace {
 
 template <bool F16, typename TI, typename TO, int N>
 hipError_t launch_n(const void* links, const cpx<TI>* in, cpx<TO>* out, const CoarseGeom& g, int ncol, double m,
-                    double M5, bool dagger, const int* skip, int sks, int tw, int tpb, hipStream_t st) {
+                    double M5, bool dagger, const int* skip, int sks, int tw, int tpb, hipStream_t st,
+                    const Epi<TO>& epi = {}) {
     constexpr int MT = N / 16;
     constexpr int SPB = 1;
     const int nsites = g.Lx * g.Ly;
@@ -416,28 +434,32 @@ hipError_t launch_n(const void* links, const cpx<TI>* in, cpx<TO>* out, const Co
     const double vec_bytes = (double)g.Ls * ncol * nsites * N * std::max(sizeof(cpx<TI>), sizeof(cpx<TO>));
     const double link_bytes = (double)nsites * 3 * N * N * 4;
     if (vec_bytes >= 4294967296.0 || link_bytes >= 4294967296.0) return hipErrorInvalidValue;
-#define DWF_COARSE_LAUNCH(TWV)                                                                                        \
-    do {                                                                                                              \
-        if (dagger) hipLaunchKernelGGL((coarse_mfma_kernel<F16, TI, TO, N, true, TWV>), grid, block, 0, st, lk, in,  \
-                                       out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, ncol, cd, mw, tpb);                  \
-        else        hipLaunchKernelGGL((coarse_mfma_kernel<F16, TI, TO, N, false, TWV>), grid, block, 0, st, lk, in, \
-                                       out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, ncol, cd, mw, tpb);                  \
-    } while (0)
-    if (tw == 2) DWF_COARSE_LAUNCH(2);        // one tile of 2 columns (one rhs on 2 coarse slices)
-    else if (tw == 4) DWF_COARSE_LAUNCH(4);   // one tile of 4 columns
-    else DWF_COARSE_LAUNCH(8);                // tiles of 8 columns, tpb of them per workgroup
-#undef DWF_COARSE_LAUNCH
+    const TO ea = (TO)epi.alpha, ebt = (TO)epi.beta;
+    auto go = [&](auto twc, auto dagc, auto epc) {
+        hipLaunchKernelGGL((coarse_mfma_kernel<F16, TI, TO, N, decltype(dagc)::value, decltype(twc)::value,
+                                               decltype(epc)::value>),
+                           grid, block, 0, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, ncol, cd, mw, tpb,
+                           epi.b, ea, ebt);
+    };
+    auto with_tw = [&](auto twc) {
+        if (epi.b) { if (dagger) go(twc, std::true_type{}, std::true_type{}); else go(twc, std::false_type{}, std::true_type{}); }
+        else       { if (dagger) go(twc, std::true_type{}, std::false_type{}); else go(twc, std::false_type{}, std::false_type{}); }
+    };
+    if (tw == 2) with_tw(std::integral_constant<int, 2>{});        // one tile of 2 columns (one rhs on 2 coarse slices)
+    else if (tw == 4) with_tw(std::integral_constant<int, 4>{});   // one tile of 4 columns
+    else with_tw(std::integral_constant<int, 8>{});                // tiles of 8 columns, tpb of them per workgroup
     return hipGetLastError();
 }
 
 template <bool F16, typename TI, typename TO>
 hipError_t launch_p(const void* links, const cpx<TI>* in, cpx<TO>* out, const CoarseGeom& g, int ncol, double m,
-                    double M5, bool dagger, const int* skip, int sks, int tw, int tpb, hipStream_t st) {
+                    double M5, bool dagger, const int* skip, int sks, int tw, int tpb, hipStream_t st,
+                    const Epi<TO>& epi = {}) {
     switch (g.n) {
-        case 16: return launch_n<F16, TI, TO, 16>(links, in, out, g, ncol, m, M5, dagger, skip, sks, tw, tpb, st);
-        case 32: return launch_n<F16, TI, TO, 32>(links, in, out, g, ncol, m, M5, dagger, skip, sks, tw, tpb, st);
-        case 48: return launch_n<F16, TI, TO, 48>(links, in, out, g, ncol, m, M5, dagger, skip, sks, tw, tpb, st);
-        case 64: return launch_n<F16, TI, TO, 64>(links, in, out, g, ncol, m, M5, dagger, skip, sks, tw, tpb, st);
+        case 16: return launch_n<F16, TI, TO, 16>(links, in, out, g, ncol, m, M5, dagger, skip, sks, tw, tpb, st, epi);
+        case 32: return launch_n<F16, TI, TO, 32>(links, in, out, g, ncol, m, M5, dagger, skip, sks, tw, tpb, st, epi);
+        case 48: return launch_n<F16, TI, TO, 48>(links, in, out, g, ncol, m, M5, dagger, skip, sks, tw, tpb, st, epi);
+        case 64: return launch_n<F16, TI, TO, 64>(links, in, out, g, ncol, m, M5, dagger, skip, sks, tw, tpb, st, epi);
         default: return hipErrorInvalidValue;
     }
 }
@@ -537,21 +559,23 @@ bool coarse_mfma_supported(int n, int link_prec) {
 
 template <typename TI, typename TO>
 hipError_t coarse_apply_mfma_io(const void* links, int link_prec, const cpx<TI>* in, cpx<TO>* out, const CoarseGeom& g,
-                                int ncol, double m, double M5, bool dagger, const int* skip, int sks, hipStream_t st) {
+                                int ncol, double m, double M5, bool dagger, const int* skip, int sks, hipStream_t st,
+                                const Epi<TO>& epi) {
     if (link_prec == P_F16) {
         const int c = choose_cfg<true, TI, TO>(links, in, out, g, ncol, m, M5, dagger, st);
         return launch_p<true, TI, TO>(links, in, out, g, ncol, m, M5, dagger, skip, sks, c / kTpbStride,
-                                      c % kTpbStride, st);
+                                      c % kTpbStride, st, epi);
     }
     const int c = choose_cfg<false, TI, TO>(links, in, out, g, ncol, m, M5, dagger, st);
     return launch_p<false, TI, TO>(links, in, out, g, ncol, m, M5, dagger, skip, sks, c / kTpbStride, c % kTpbStride,
-                                   st);
+                                   st, epi);
 }
 
 template <typename T>
 hipError_t coarse_apply_mfma(const void* links, int link_prec, const cpx<T>* in, cpx<T>* out, const CoarseGeom& g,
-                             int ncol, double m, double M5, bool dagger, const int* skip, int sks, hipStream_t st) {
-    return coarse_apply_mfma_io<T, T>(links, link_prec, in, out, g, ncol, m, M5, dagger, skip, sks, st);
+                             int ncol, double m, double M5, bool dagger, const int* skip, int sks, hipStream_t st,
+                             const Epi<T>& epi) {
+    return coarse_apply_mfma_io<T, T>(links, link_prec, in, out, g, ncol, m, M5, dagger, skip, sks, st, epi);
 }
 
 bool coarse_mfma_config(int link_prec, int vec_prec, const CoarseGeom& g, int ncol, bool dagger, int* tw, int* tpb) {
@@ -610,9 +634,9 @@ hipError_t convert_links_fragment16(const cpx<double>* in, void* out, int link_p
     return hipGetLastError();
 }
 
-template hipError_t coarse_apply_mfma<float>(const void*, int, const cpx<float>*, cpx<float>*, const CoarseGeom&, int, double, double, bool, const int*, int, hipStream_t);
-template hipError_t coarse_apply_mfma_io<double, float>(const void*, int, const cpx<double>*, cpx<float>*, const CoarseGeom&, int, double, double, bool, const int*, int, hipStream_t);
-template hipError_t coarse_apply_mfma_io<float, double>(const void*, int, const cpx<float>*, cpx<double>*, const CoarseGeom&, int, double, double, bool, const int*, int, hipStream_t);
-template hipError_t coarse_apply_mfma<double>(const void*, int, const cpx<double>*, cpx<double>*, const CoarseGeom&, int, double, double, bool, const int*, int, hipStream_t);
+template hipError_t coarse_apply_mfma<float>(const void*, int, const cpx<float>*, cpx<float>*, const CoarseGeom&, int, double, double, bool, const int*, int, hipStream_t, const Epi<float>&);
+template hipError_t coarse_apply_mfma_io<double, float>(const void*, int, const cpx<double>*, cpx<float>*, const CoarseGeom&, int, double, double, bool, const int*, int, hipStream_t, const Epi<float>&);
+template hipError_t coarse_apply_mfma_io<float, double>(const void*, int, const cpx<float>*, cpx<double>*, const CoarseGeom&, int, double, double, bool, const int*, int, hipStream_t, const Epi<double>&);
+template hipError_t coarse_apply_mfma<double>(const void*, int, const cpx<double>*, cpx<double>*, const CoarseGeom&, int, double, double, bool, const int*, int, hipStream_t, const Epi<double>&);
 
 }  // namespace dwf

@@ -130,16 +130,25 @@ __device__ __forceinline__ void store_out(spinor<double>* p, const spinor<double
     }
 }
 
-// out = D psi  (RESID: out = b - D psi).  DW selects the domain-wall operator
+// beta b + alpha v (one rounding each for alpha = -1, beta = 1: b - v exactly as a subtraction)
+template <typename R>
+__device__ __forceinline__ spinor<R> axpby(R alpha, const spinor<R>& v, R beta, const spinor<R>& b) {
+    spinor<R> r;
+    r.c0 = {alpha * v.c0.re + beta * b.c0.re, alpha * v.c0.im + beta * b.c0.im};
+    r.c1 = {alpha * v.c1.re + beta * b.c1.re, alpha * v.c1.im + beta * b.c1.im};
+    return r;
+}
+
+// out = D psi  (AXPBY: out = beta b + alpha D psi; alpha = -1, beta = 1 is the residual).  DW selects the domain-wall operator
 // (diagonal D_W(M5)+1 plus the fifth-dimension hop); otherwise a stack of
 // independent 2-d Wilson fields D_W(M).  `diag` = d + M5 + 1 or d + M,
 // `mwrap` = -m (the corner blocks of eq. DWoperator).
-template <typename R, bool DAG, bool DW, bool RESID, bool NT>
+template <typename R, bool DAG, bool DW, bool AXPBY, bool NT>
 __global__ void __launch_bounds__(kBlock)
 fine_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in,
             spinor<R>* __restrict__ out, const spinor<R>* __restrict__ b,
             const int* __restrict__ skip, int skip_stride, int Lx, int Ly, int Ls, int nchunk, int cs,
-            int nsb, R diag, R mwrap) {
+            int nsb, R diag, R mwrap, R alpha, R beta) {
     // logical workgroup -> (column, block of 2-d sites, slice chunk), chunk fastest: the chunks of
     // one block of sites share their boundary slices, and on one XCD (xcd_block) they run side by
     // side, so those slices come from L2 rather than being fetched again
@@ -198,11 +207,7 @@ fine_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in,
             res.c1 = diag * cur.c1 - a1;
         }
         const size_t o = colbase + (size_t)s * V + site;
-        if (RESID) {
-            const spinor<R> bb = b[o];
-            res.c0 = bb.c0 - res.c0;
-            res.c1 = bb.c1 - res.c1;
-        }
+        if (AXPBY) res = axpby(alpha, res, beta, b[o]);
         store_out<NT>(out + o, res);
         if (DW) { prv = cur; cur = nxt; }
     }
@@ -216,11 +221,11 @@ fine_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in,
 // barrier, read the four neighbours, evaluate, store.  The buffer written at
 // slice s was last read at slice s-2, before the barrier of slice s-1, so one
 // barrier per slice suffices.  Requires Lx % TX == 0 and Ly % TY == 0.
-template <typename R, bool DAG, bool RESID, int TX, int TY, bool NT>
+template <typename R, bool DAG, bool AXPBY, int TX, int TY, bool NT>
 __global__ void __launch_bounds__(TX * TY)
 fine_tile_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in, spinor<R>* __restrict__ out,
                  const spinor<R>* __restrict__ b, const int* __restrict__ skip, int skip_stride, int Lx, int Ly,
-                 int Ls, int nchunk, int cs, int ntile, R diag, R mwrap) {
+                 int Ls, int nchunk, int cs, int ntile, R diag, R mwrap, R alpha, R beta) {
     static_assert(TX >= 2 && TY >= 2, "the ring needs two distinct edges per direction");
     __shared__ spinor<R> tile[2][TY + 2][TX + 2];
     const unsigned lb = xcd_block(blockIdx.x, gridDim.x);
@@ -270,16 +275,19 @@ fine_tile_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in,
     typedef typename vec4_of<R>::type vec4;
     vec4 hv = {};
     if (ring) hv = load4(src + (size_t)s0 * V + hsite);
+    vec4 bv = {};   // b of the slice, loaded one slice ahead like the ring
+    if (AXPBY) bv = load4(b + colbase + (size_t)s0 * V + site);
     for (int s = s0; s < s1; ++s) {
         spinor<R>(*bf)[TX + 2] = tile[s & 1];
         bf[ly + 1][lx + 1] = cur;
         if (ring) *reinterpret_cast<vec4*>(&bf[0][0] + hlds) = hv;
-        vec4 nn = {};
+        vec4 nn = {}, bn = {};
         if (s + 1 < s1) {   // the same for the whole workgroup
             const int sn = (s + 1 == Ls) ? 0 : s + 1;
             const int s2 = (s + 2 >= Ls) ? s + 2 - Ls : s + 2;
             nn = load4(src + (size_t)s2 * V + site);
             if (ring) hv = load4(src + (size_t)sn * V + hsite);
+            if (AXPBY) bn = load4(b + colbase + (size_t)(s + 1) * V + site);
         }
         __syncthreads();
         const spinor<R> fx = bf[ly + 1][lx + 2], bx = bf[ly + 1][lx], fy = bf[ly + 2][lx + 1], by = bf[ly][lx + 1];
@@ -287,15 +295,12 @@ fine_tile_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in,
         if (s + 1 == Ls) { nx.c0 = mwrap * nx.c0; nx.c1 = mwrap * nx.c1; }
         spinor<R> res = dw_site<R, DAG>(fx, bx, fy, by, cur, prv, nx, hu0, hu0m, hu1, hu1m, diag);
         const size_t o = colbase + (size_t)s * V + site;
-        if (RESID) {
-            const spinor<R> bb = b[o];
-            res.c0 = bb.c0 - res.c0;
-            res.c1 = bb.c1 - res.c1;
-        }
+        if (AXPBY) res = axpby(alpha, res, beta, unpack4<R>(bv));
         store_out<NT>(out + o, res);
         prv = cur;
         cur = nxt;
         nxt = unpack4<R>(nn);
+        bv = bn;
     }
 }
 
@@ -327,7 +332,7 @@ static inline int pick_cfg(int Lx, int Ly, int Ls, int ncol) {
 template <typename R>
 static hipError_t launch_fine(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, const cpx<R>* b, int Lx, int Ly,
                               int Ls, int ncol, double m, double M5, bool dagger, const int* skip, int skip_stride,
-                              int cfg, hipStream_t st);
+                              int cfg, hipStream_t st, double alpha = -1.0, double beta = 1.0);
 
 // Launch configuration of the fine stencil (kernel shape and chunk length),
 // chosen by timing the candidates once per lattice shape, column count,
@@ -424,21 +429,21 @@ bool set_fine_config(int shape, int chunk) {
 template <typename R>
 static hipError_t fine_dw_impl(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, const cpx<R>* b, int Lx, int Ly,
                                int Ls, int ncol, double m, double M5, bool dagger, const int* skip, int skip_stride,
-                               hipStream_t st, bool may_time) {
+                               hipStream_t st, bool may_time, double alpha = -1.0, double beta = 1.0) {
     const int pin = g_fine_pin.load(std::memory_order_relaxed);
     int cfg;
     if (pin >= 0 && (pin / kCfgStride == 0 || tile_fits(pin / kCfgStride, Lx, Ly)))
         cfg = (pin / kCfgStride) * kCfgStride + std::min(pin % kCfgStride, Ls);
     else
         cfg = tuned_cfg<R>(U, in, out, Lx, Ly, Ls, ncol, m, M5, dagger, st, may_time);
-    return launch_fine<R>(U, in, out, b, Lx, Ly, Ls, ncol, m, M5, dagger, skip, skip_stride, cfg, st);
+    return launch_fine<R>(U, in, out, b, Lx, Ly, Ls, ncol, m, M5, dagger, skip, skip_stride, cfg, st, alpha, beta);
 }
 
 template <typename R>
 hipError_t fine_dw(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, const cpx<R>* b,
                    int Lx, int Ly, int Ls, int ncol, double m, double M5, bool dagger,
-                   const int* skip, int skip_stride, hipStream_t st) {
-    return fine_dw_impl<R>(U, in, out, b, Lx, Ly, Ls, ncol, m, M5, dagger, skip, skip_stride, st, true);
+                   const int* skip, int skip_stride, hipStream_t st, double alpha, double beta) {
+    return fine_dw_impl<R>(U, in, out, b, Lx, Ly, Ls, ncol, m, M5, dagger, skip, skip_stride, st, true, alpha, beta);
 }
 
 template <typename R>
@@ -450,7 +455,7 @@ hipError_t fine_dw_untimed(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, int L
 template <typename R, int TX, int TY>
 static hipError_t launch_tile(const cpx<R>* U, const spinor<R>* si, spinor<R>* so, const spinor<R>* sb, int Lx,
                               int Ly, int Ls, int ncol, R diag, R mwrap, bool dagger, const int* skip,
-                              int skip_stride, int cs, hipStream_t st) {
+                              int skip_stride, int cs, hipStream_t st, R alpha, R beta) {
     if (Lx % TX || Ly % TY) return hipErrorInvalidValue;
     const int nt = (double)Lx * Ly * Ls * ncol * sizeof(spinor<R>) >= kStreamStoreBytes ? 1 : 0;
     const int nchunk = (Ls + cs - 1) / cs;
@@ -458,11 +463,11 @@ static hipError_t launch_tile(const cpx<R>* U, const spinor<R>* si, spinor<R>* s
     const long long nblocks = (long long)ntile * nchunk * ncol;
     if (nblocks > 0x7fffffffLL) return hipErrorInvalidValue;
     dim3 grid((unsigned)nblocks), block(TX * TY);
-    auto go = [&](auto dag, auto resid, auto ntc) {
-        hipLaunchKernelGGL((fine_tile_kernel<R, decltype(dag)::value, decltype(resid)::value, TX, TY,
+    auto go = [&](auto dag, auto axpbyc, auto ntc) {
+        hipLaunchKernelGGL((fine_tile_kernel<R, decltype(dag)::value, decltype(axpbyc)::value, TX, TY,
                                              decltype(ntc)::value>),
                            grid, block, 0, st, U, si, so, sb, skip, skip_stride, Lx, Ly, Ls, nchunk, cs, ntile, diag,
-                           mwrap);
+                           mwrap, alpha, beta);
     };
     using T_ = std::true_type;
     using F_ = std::false_type;
@@ -479,7 +484,7 @@ static hipError_t launch_tile(const cpx<R>* U, const spinor<R>* si, spinor<R>* s
 template <typename R>
 static hipError_t launch_fine(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, const cpx<R>* b, int Lx, int Ly,
                               int Ls, int ncol, double m, double M5, bool dagger, const int* skip, int skip_stride,
-                              int cfg, hipStream_t st) {
+                              int cfg, hipStream_t st, double alpha, double beta) {
     const int shape = cfg / kCfgStride, cs = cfg % kCfgStride;
     if (cs < 1 || shape < 0 || shape > kNumTiles) return hipErrorInvalidValue;
     const R diag = R(2.0 + M5 + 1.0), mwrap = R(-m);
@@ -488,9 +493,9 @@ static hipError_t launch_fine(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, co
     auto* sb = reinterpret_cast<const spinor<R>*>(b);
     static_assert(kNumTiles == 3, "one case per tile shape");
     switch (shape) {
-        case 1: return launch_tile<R, kTiles[0].tx, kTiles[0].ty>(U, si, so, sb, Lx, Ly, Ls, ncol, diag, mwrap, dagger, skip, skip_stride, cs, st);
-        case 2: return launch_tile<R, kTiles[1].tx, kTiles[1].ty>(U, si, so, sb, Lx, Ly, Ls, ncol, diag, mwrap, dagger, skip, skip_stride, cs, st);
-        case 3: return launch_tile<R, kTiles[2].tx, kTiles[2].ty>(U, si, so, sb, Lx, Ly, Ls, ncol, diag, mwrap, dagger, skip, skip_stride, cs, st);
+        case 1: return launch_tile<R, kTiles[0].tx, kTiles[0].ty>(U, si, so, sb, Lx, Ly, Ls, ncol, diag, mwrap, dagger, skip, skip_stride, cs, st, R(alpha), R(beta));
+        case 2: return launch_tile<R, kTiles[1].tx, kTiles[1].ty>(U, si, so, sb, Lx, Ly, Ls, ncol, diag, mwrap, dagger, skip, skip_stride, cs, st, R(alpha), R(beta));
+        case 3: return launch_tile<R, kTiles[2].tx, kTiles[2].ty>(U, si, so, sb, Lx, Ly, Ls, ncol, diag, mwrap, dagger, skip, skip_stride, cs, st, R(alpha), R(beta));
         default: break;
     }
     const int nchunk = (Ls + cs - 1) / cs;
@@ -499,10 +504,10 @@ static hipError_t launch_fine(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, co
     if (nblocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const int nt = (double)Lx * Ly * Ls * ncol * sizeof(spinor<R>) >= kStreamStoreBytes ? 1 : 0;
     dim3 grid((unsigned)nblocks), block(kBlock);
-    auto go = [&](auto dag, auto resid, auto ntc) {
-        hipLaunchKernelGGL((fine_kernel<R, decltype(dag)::value, true, decltype(resid)::value, decltype(ntc)::value>),
+    auto go = [&](auto dag, auto axpbyc, auto ntc) {
+        hipLaunchKernelGGL((fine_kernel<R, decltype(dag)::value, true, decltype(axpbyc)::value, decltype(ntc)::value>),
                            grid, block, 0, st, U, si, so, sb, skip, skip_stride, Lx, Ly, Ls, nchunk, cs, nsb, diag,
-                           mwrap);
+                           mwrap, R(alpha), R(beta));
     };
     using T_ = std::true_type;
     using F_ = std::false_type;
@@ -531,11 +536,11 @@ static hipError_t launch_fine(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, co
 // at step k-1, both before step k-1's barrier.  Every site evaluates the same expressions
 // as the two separate stencil kernels (dw_site), in the same order.
 // Requires Lx % TX == 0 and Ly % TY == 0.
-template <typename R, int TX, int TY, bool NTS>
+template <typename R, int TX, int TY, bool AXPBY, bool NTS>
 __global__ void __launch_bounds__(TX * TY)
 fine_a_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in, spinor<R>* __restrict__ out,
-              const int* __restrict__ skip, int skip_stride, int Lx, int Ly, int Ls, int nchunk, int cs, int ntile,
-              R diag, R mdw, R mpv) {
+              const spinor<R>* __restrict__ b, const int* __restrict__ skip, int skip_stride, int Lx, int Ly, int Ls,
+              int nchunk, int cs, int ntile, R diag, R mdw, R mpv, R alpha, R beta) {
     constexpr int NTH = TX * TY;
     constexpr int BX = TX + 4, BY = TY + 4;                            // psi box: two-site margin
     constexpr int EX = TX + 2, EY = TY + 2;                            // t tile: one-site margin
@@ -650,6 +655,8 @@ fine_a_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in, sp
         vec4 a[2] = {};
         const bool pre = k + 2 <= s1 + 1;
         if (pre) load_box(k + 2, a);
+        vec4 bv = {};
+        if (AXPBY && k - 1 >= s0) bv = load4(b + colbase + (size_t)(k - 1) * V + site);
         tn = t_at(k, lx, ly, hu0, hu0m, hu1, hu1m);
         spinor<R>(*tw)[EX] = tb[k & 1];
         tw[ly + 1][lx + 1] = tn;
@@ -660,8 +667,9 @@ fine_a_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in, sp
             spinor<R> prv = tp, nxt = tn;
             if (so == 0) { prv.c0 = mpv * prv.c0; prv.c1 = mpv * prv.c1; }
             if (so == Ls - 1) { nxt.c0 = mpv * nxt.c0; nxt.c1 = mpv * nxt.c1; }
-            const spinor<R> res = dw_site<R, true>(q[ly + 1][lx + 2], q[ly + 1][lx], q[ly + 2][lx + 1], q[ly][lx + 1],
-                                                   tc, prv, nxt, hu0, hu0m, hu1, hu1m, diag);
+            spinor<R> res = dw_site<R, true>(q[ly + 1][lx + 2], q[ly + 1][lx], q[ly + 2][lx + 1], q[ly][lx + 1], tc,
+                                             prv, nxt, hu0, hu0m, hu1, hu1m, diag);
+            if (AXPBY) res = axpby(alpha, res, beta, unpack4<R>(bv));
             store_out<NTS>(out + colbase + (size_t)so * V + site, res);
         }
         if (pre) put_box(k + 2, a);
@@ -692,7 +700,7 @@ static bool a_tile_fits(int shape, int Lx, int Ly) {
 template <typename R, int TX, int TY>
 static hipError_t launch_a_tile(const cpx<R>* U, const spinor<R>* si, spinor<R>* so, int Lx, int Ly, int Ls,
                                 int ncol, R diag, R mdw, R mpv, const int* skip, int skip_stride, int cs,
-                                hipStream_t st) {
+                                hipStream_t st, const Epi<R>& epi) {
     if constexpr (!a_tile_lds_ok<R>(TX, TY)) {
         return hipErrorInvalidValue;
     } else {
@@ -703,12 +711,14 @@ static hipError_t launch_a_tile(const cpx<R>* U, const spinor<R>* si, spinor<R>*
         const long long nblocks = (long long)ntile * nchunk * ncol;
         if (nblocks > 0x7fffffffLL) return hipErrorInvalidValue;
         dim3 grid((unsigned)nblocks), block(TX * TY);
-        if (nt)
-            hipLaunchKernelGGL((fine_a_kernel<R, TX, TY, true>), grid, block, 0, st, U, si, so, skip, skip_stride,
-                               Lx, Ly, Ls, nchunk, cs, ntile, diag, mdw, mpv);
-        else
-            hipLaunchKernelGGL((fine_a_kernel<R, TX, TY, false>), grid, block, 0, st, U, si, so, skip, skip_stride,
-                               Lx, Ly, Ls, nchunk, cs, ntile, diag, mdw, mpv);
+        auto* sb = reinterpret_cast<const spinor<R>*>(epi.b);
+        auto go = [&](auto axpbyc, auto ntc) {
+            hipLaunchKernelGGL((fine_a_kernel<R, TX, TY, decltype(axpbyc)::value, decltype(ntc)::value>), grid, block,
+                               0, st, U, si, so, sb, skip, skip_stride, Lx, Ly, Ls, nchunk, cs, ntile, diag, mdw, mpv,
+                               R(epi.alpha), R(epi.beta));
+        };
+        if (sb) { if (nt) go(std::true_type{}, std::true_type{}); else go(std::true_type{}, std::false_type{}); }
+        else    { if (nt) go(std::false_type{}, std::true_type{}); else go(std::false_type{}, std::false_type{}); }
         return hipGetLastError();
     }
 }
@@ -716,14 +726,14 @@ static hipError_t launch_a_tile(const cpx<R>* U, const spinor<R>* si, spinor<R>*
 template <typename R>
 static hipError_t launch_a(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* tmp, int Lx, int Ly, int Ls,
                            int ncol, double m, double M5, const int* skip, int skip_stride, int cfg, hipStream_t st,
-                           bool may_time) {
+                           bool may_time, const Epi<R>& epi = {}) {
     const int shape = cfg / kCfgStride, cs = cfg % kCfgStride;
     if (shape == 0) {
         hipError_t e = fine_dw_impl<R>(U, in, tmp, nullptr, Lx, Ly, Ls, ncol, m, M5, false, skip, skip_stride, st,
                                        may_time);
         if (e != hipSuccess) return e;
-        return fine_dw_impl<R>(U, tmp, out, nullptr, Lx, Ly, Ls, ncol, 1.0, M5, true, skip, skip_stride, st,
-                               may_time);
+        return fine_dw_impl<R>(U, tmp, out, epi.b, Lx, Ly, Ls, ncol, 1.0, M5, true, skip, skip_stride, st, may_time,
+                               epi.alpha, epi.beta);
     }
     if (cs < 1 || !a_tile_fits<R>(shape, Lx, Ly)) return hipErrorInvalidValue;
     const R diag = R(2.0 + M5 + 1.0), mdw = R(-m), mpv = R(-1.0);
@@ -731,9 +741,9 @@ static hipError_t launch_a(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R
     auto* so = reinterpret_cast<spinor<R>*>(out);
     static_assert(kNumATiles == 3, "one case per fused tile shape");
     switch (shape) {
-        case 1: return launch_a_tile<R, kATiles[0].tx, kATiles[0].ty>(U, si, so, Lx, Ly, Ls, ncol, diag, mdw, mpv, skip, skip_stride, cs, st);
-        case 2: return launch_a_tile<R, kATiles[1].tx, kATiles[1].ty>(U, si, so, Lx, Ly, Ls, ncol, diag, mdw, mpv, skip, skip_stride, cs, st);
-        case 3: return launch_a_tile<R, kATiles[2].tx, kATiles[2].ty>(U, si, so, Lx, Ly, Ls, ncol, diag, mdw, mpv, skip, skip_stride, cs, st);
+        case 1: return launch_a_tile<R, kATiles[0].tx, kATiles[0].ty>(U, si, so, Lx, Ly, Ls, ncol, diag, mdw, mpv, skip, skip_stride, cs, st, epi);
+        case 2: return launch_a_tile<R, kATiles[1].tx, kATiles[1].ty>(U, si, so, Lx, Ly, Ls, ncol, diag, mdw, mpv, skip, skip_stride, cs, st, epi);
+        case 3: return launch_a_tile<R, kATiles[2].tx, kATiles[2].ty>(U, si, so, Lx, Ly, Ls, ncol, diag, mdw, mpv, skip, skip_stride, cs, st, epi);
         default: return hipErrorInvalidValue;
     }
 }
@@ -814,14 +824,14 @@ static int tuned_a_cfg(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* t
 
 template <typename R>
 hipError_t fine_a(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* tmp, int Lx, int Ly, int Ls, int ncol,
-                  double m, double M5, const int* skip, int skip_stride, hipStream_t st) {
+                  double m, double M5, const int* skip, int skip_stride, hipStream_t st, const Epi<R>& epi) {
     const int pin = g_a_pin.load(std::memory_order_relaxed);
     int cfg;
     if (pin >= 0 && (pin / kCfgStride == 0 || (a_tile_fits<R>(pin / kCfgStride, Lx, Ly) && Ls >= 2)))
         cfg = pin / kCfgStride == 0 ? 0 : (pin / kCfgStride) * kCfgStride + std::min(pin % kCfgStride, Ls);
     else
         cfg = tuned_a_cfg<R>(U, in, out, tmp, Lx, Ly, Ls, ncol, m, M5, st, true);
-    return launch_a<R>(U, in, out, tmp, Lx, Ly, Ls, ncol, m, M5, skip, skip_stride, cfg, st, true);
+    return launch_a<R>(U, in, out, tmp, Lx, Ly, Ls, ncol, m, M5, skip, skip_stride, cfg, st, true, epi);
 }
 
 bool fine_a_chosen(int prec_bytes, int Lx, int Ly, int Ls, int ncol, int* shape, int* chunk) {
@@ -851,19 +861,19 @@ hipError_t wilson2d(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, int Lx, int 
     dim3 grid((unsigned)nblocks), block(kBlock);
     auto go = [&](auto dag, auto ntc) {
         hipLaunchKernelGGL((fine_kernel<R, decltype(dag)::value, false, false, decltype(ntc)::value>), grid, block, 0,
-                           st, U, si, so, nullptr, nullptr, 1, Lx, Ly, Ls, nchunk, cs, nsb, diag, mwrap);
+                           st, U, si, so, nullptr, nullptr, 1, Lx, Ly, Ls, nchunk, cs, nsb, diag, mwrap, R(0), R(0));
     };
     if (dagger) { if (nt) go(std::true_type{}, std::true_type{}); else go(std::true_type{}, std::false_type{}); }
     else        { if (nt) go(std::false_type{}, std::true_type{}); else go(std::false_type{}, std::false_type{}); }
     return hipGetLastError();
 }
 
-template hipError_t fine_dw<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, const cpx<float>*, int, int, int, int, double, double, bool, const int*, int, hipStream_t);
-template hipError_t fine_dw<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, const cpx<double>*, int, int, int, int, double, double, bool, const int*, int, hipStream_t);
+template hipError_t fine_dw<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, const cpx<float>*, int, int, int, int, double, double, bool, const int*, int, hipStream_t, double, double);
+template hipError_t fine_dw<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, const cpx<double>*, int, int, int, int, double, double, bool, const int*, int, hipStream_t, double, double);
 template hipError_t fine_dw_untimed<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, int, int, int, int, double, double, bool, hipStream_t);
 template hipError_t fine_dw_untimed<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, int, int, int, int, double, double, bool, hipStream_t);
-template hipError_t fine_a<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, cpx<float>*, int, int, int, int, double, double, const int*, int, hipStream_t);
-template hipError_t fine_a<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, cpx<double>*, int, int, int, int, double, double, const int*, int, hipStream_t);
+template hipError_t fine_a<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, cpx<float>*, int, int, int, int, double, double, const int*, int, hipStream_t, const Epi<float>&);
+template hipError_t fine_a<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, cpx<double>*, int, int, int, int, double, double, const int*, int, hipStream_t, const Epi<double>&);
 template hipError_t wilson2d<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, int, int, int, double, bool, hipStream_t);
 template hipError_t wilson2d<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, int, int, int, double, bool, hipStream_t);
 

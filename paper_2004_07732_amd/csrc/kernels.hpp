@@ -37,10 +37,18 @@ struct CgScal {
 struct GcrScal;  // defined in blas.hip
 
 // ------------------------------------------------------------ fine operators
+// what an operator's last kernel stores: with b set, beta b + alpha (operator in) instead of
+// operator in (b may be the operator's input, not its output)
+template <typename R>
+struct Epi {
+    const cpx<R>* b = nullptr;
+    double alpha = 1.0, beta = 0.0;
+};
+// out = D in, or with b set beta b + alpha D in (by default the residual b - D in)
 template <typename R>
 hipError_t fine_dw(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, const cpx<R>* b,
                    int Lx, int Ly, int Ls, int ncol, double m, double M5, bool dagger,
-                   const int* skip, int skip_stride, hipStream_t st);
+                   const int* skip, int skip_stride, hipStream_t st, double alpha = -1.0, double beta = 1.0);
 // the same operator without the autotuner's timing runs (a pinned or previously
 // tuned configuration, else the heuristic one): no synchronisation, no events
 template <typename R>
@@ -54,7 +62,7 @@ bool set_fine_config(int shape, int chunk);
 // (tmp then untouched), whichever the timed choice or the pin selects
 template <typename R>
 hipError_t fine_a(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* tmp, int Lx, int Ly, int Ls, int ncol,
-                  double m, double M5, const int* skip, int skip_stride, hipStream_t st);
+                  double m, double M5, const int* skip, int skip_stride, hipStream_t st, const Epi<R>& epi = {});
 // pin the fine A's configuration: shape -1 timed choice, 0 two launches, k >= 1 fused tile
 // shape k with the given slice chunk; false for an unknown shape or chunk
 bool set_fine_a_config(int shape, int chunk);
@@ -84,14 +92,15 @@ template <typename T>
 hipError_t coarse_apply(const void* links, int link_prec, const cpx<T>* in, cpx<T>* out,
                         const CoarseGeom& g, int ncol, double m, double M5, bool dagger,
                         bool wilson_mode, double wilson_mass, const int* skip, int skip_stride,
-                        hipStream_t st);
+                        hipStream_t st, const Epi<T>& epi = {});
 
 // Matrix-core path (BF16 or FP16 links stored in MFMA fragment order per
 // site, n a multiple of 16); coarse_apply dispatches to it by itself for such levels.
 bool coarse_mfma_supported(int n, int link_prec);
 template <typename T>
 hipError_t coarse_apply_mfma(const void* links, int link_prec, const cpx<T>* in, cpx<T>* out, const CoarseGeom& g,
-                             int ncol, double m, double M5, bool dagger, const int* skip, int sks, hipStream_t st);
+                             int ncol, double m, double M5, bool dagger, const int* skip, int sks, hipStream_t st,
+                             const Epi<T>& epi = {});
 hipError_t convert_links_fragment16(const cpx<double>* in, void* out, int link_prec, int nsites, int n,
                                     hipStream_t st);
 // launch configuration the matrix-core path uses for this shape (the tuned one
@@ -102,7 +111,8 @@ bool coarse_mfma_config(int link_prec, int vec_prec, const CoarseGeom& g, int nc
 // accumulation is FP32, so an FP32 intermediate holds exactly what an FP64 one would)
 template <typename TI, typename TO>
 hipError_t coarse_apply_mfma_io(const void* links, int link_prec, const cpx<TI>* in, cpx<TO>* out, const CoarseGeom& g,
-                                int ncol, double m, double M5, bool dagger, const int* skip, int sks, hipStream_t st);
+                                int ncol, double m, double M5, bool dagger, const int* skip, int sks, hipStream_t st,
+                                const Epi<TO>& epi = {});
 // complex 16-bit entries of that storage: the site term and the two forward hops
 // (the backward hops are the sigma_3-adjoints of the neighbours' forward hops)
 size_t links_fragment16_entries(int nsites, int n);
@@ -190,26 +200,23 @@ template <typename T>
 hipError_t gcr_fused_step(const cpx<T>* W, size_t wstride, int j, cpx<T>* w, cpx<T>* r, cpx<T>* copy, size_t n,
                           int ncol, double tol2, const int* stop_in, int* stop_out, const GcrDev& g,
                           const RedWork& rw, hipStream_t st);
-// Gram-form GCR step j (restart cycles of at most kGramMax steps), three launches: the
-// multi-dot of w_j = W_j against W_0..W_{j-1} and r0, a finaliser that solves
-// G y = b (G_il = <W_i, W_l>, b_i = <W_i, r0>, i, l <= j) once per column, and one pass
-// out = r0 - sum_{i<=j} y_i W_i.  Keeps G's rows in g.D / g.nn, b in g.wr and y in g.gam; the
-// new residual norm |r0|^2 - Re <b, y> (g.rr holds the cycle's |r0|^2) decides the stop flag
-// in stop_out (1 at or below tol2 |b|^2, 2 if not finite); a stopped column's directions are
-// zero and its coefficients stay those of the step it stopped at.
-constexpr int kGramMax = 7;   // (the finaliser runs one wave per inner product: 2 j + 3 <= 16 waves)
+// s-step GCR cycle of k <= kSsMax steps: the directions P_0 = r0, P_{i+1} = A P_i / c - P_i are
+// built without an inner product (c: a shift inside the spectrum of A), then three launches take
+// the minimal residual over r0 - span{A P_0 .. A P_{k-1}}: the products <P_a, P_b>, a finaliser
+// that solves for the coefficients once per column, and one pass x += sum y_i P_i,
+// P_0 = the new residual (the next cycle's start).  The residual norm of every step of the cycle
+// follows from the same factorisation: a column whose norm falls to tol2 |b|^2 at step j takes
+// that step's correction and stops (stop 1; 2 if a value is not finite), and g.it counts the
+// steps it took.  A stopped column takes no update.  `first` starts the column state afresh
+// (|b|^2 = |P_0|^2); otherwise ss_begin (P_0 = b, x = 0) or the previous cycle left it.
+constexpr int kSsMax = 8;
+constexpr int kSsBlocks = 512;
+template <typename T> struct SsVecs { cpx<T>* p[kSsMax + 1]; };
 template <typename T>
-hipError_t gcr_gram_step(const cpx<T>* W, size_t wstride, int j, const cpx<T>* r0, cpx<T>* out, size_t n, int ncol,
-                         double tol2, const int* stop_in, int* stop_out, const GcrDev& g, const RedWork& rw,
-                         hipStream_t st);
-// The last Gram-form step (j = k - 1) of a cycle whose starting residual is P_0, fused with
-// the cycle's solution update: multi-dot and finaliser as in gcr_gram_step (g.rr becomes the
-// next cycle's |r0|^2), then one pass x += sum_{i<k} y_i P_i, P_0 = P_0 - sum_{i<k} y_i W_i (the
-// next cycle's residual and first direction); the stop flags of stop_out become g.stop.
+hipError_t ss_begin(const cpx<T>* b, cpx<T>* P0, cpx<T>* x, size_t n, int ncol, const GcrDev& g, hipStream_t st);
 template <typename T>
-hipError_t gcr_gram_last(cpx<T>* P, const cpx<T>* W, size_t stride_v, int k, cpx<T>* x, size_t n, int ncol,
-                         double tol2, const int* stop_in, int* stop_out, const GcrDev& g, const RedWork& rw,
-                         hipStream_t st);
+hipError_t ss_finish(const SsVecs<T>& P, int k, cpx<T>* x, size_t n, int ncol, double c, double tol2, bool first,
+                     const GcrDev& g, const RedWork& rw, hipStream_t st);
 // next restart cycle on the recursive residual: P0 = r, and the stop flags of the
 // cycle's last step (stop_src) become g.stop
 template <typename T>

@@ -59,9 +59,6 @@ template <typename T> inline const cpx<T>* C(const void* p) { return reinterpret
 template <typename T> constexpr int prec_of() { return std::is_same<T, float>::value ? P_F32 : P_F64; }
 constexpr int kCgChunk = 16;
 const int kSkipStride = (int)(sizeof(CgScal) / sizeof(int));
-// longest smoother restart cycle that takes the Gram-form GCR step
-constexpr int kGramSteps = 6;
-static_assert(kGramSteps <= kGramMax, "the Gram step kernels cover the cycle");
 inline const int* cg_skip(const CgScal* s) { return s ? &s[0].done : nullptr; }
 }  // namespace
 
@@ -175,16 +172,17 @@ int Hierarchy::run_graph(const GraphKey& key, hipStream_t st, F&& enqueue) {
 // ------------------------------------------------------------ level operators
 template <typename T>
 hipError_t Hierarchy::apply_dw(int l, const cpx<T>* in, cpx<T>* out, double mass, bool dag, int ncol,
-                               hipStream_t st, const int* skip) {
+                               hipStream_t st, const int* skip, const Epi<T>& epi) {
     const Level& L = levels[l];
     const int stride = skip ? kSkipStride : 1;
     if (L.fine) {
         const cpx<T>* U;
         if constexpr (std::is_same<T, float>::value) U = L.U32; else U = L.U64;
-        return fine_dw<T>(U, in, out, nullptr, L.Lx, L.Ly, L.Ls, ncol, mass, M5, dag, skip, stride, st);
+        return fine_dw<T>(U, in, out, epi.b, L.Lx, L.Ly, L.Ls, ncol, mass, M5, dag, skip, stride, st, epi.alpha,
+                          epi.beta);
     }
     CoarseGeom g{L.Lx, L.Ly, L.Ls, L.n};
-    return coarse_apply<T>(L.links, L.link_prec, in, out, g, ncol, mass, M5, dag, false, 0.0, skip, stride, st);
+    return coarse_apply<T>(L.links, L.link_prec, in, out, g, ncol, mass, M5, dag, false, 0.0, skip, stride, st, epi);
 }
 
 // Polynomial correction of the PV preconditioning (remark after eq. NormalExp,
@@ -206,13 +204,14 @@ hipError_t Hierarchy::pv_poly(const cpx<T>* w, cpx<T>* y, cpx<T>* z, int ncol, h
 // A = D_PV^dag D_DW (on the fine level with the PV polynomial: D_PV^dag p(X) D_DW)
 template <typename T>
 hipError_t Hierarchy::apply_A(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp, int ncol, hipStream_t st,
-                              const int* skip) {
+                              const int* skip, const Epi<T>& epi) {
     if (l == 0 && prm.pv_poly_order == 0) {
         if (!capturing_) cnt_.fine_applies += a_cost(0);
         const Level& L = levels[0];
         const cpx<T>* U;
         if constexpr (std::is_same<T, float>::value) U = L.U32; else U = L.U64;
-        return fine_a<T>(U, in, out, tmp, L.Lx, L.Ly, L.Ls, ncol, m, M5, skip, skip ? kSkipStride : 1, st);
+        return fine_a<T>(U, in, out, tmp, L.Lx, L.Ly, L.Ls, ncol, m, M5, skip, skip ? kSkipStride : 1, st,
+                         epi);
     }
     if constexpr (std::is_same<T, double>::value) {
         const Level& L = levels[l];
@@ -228,7 +227,7 @@ hipError_t Hierarchy::apply_A(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp,
                                                                skip, stride, st);
             if (e != hipSuccess) return e;
             return coarse_apply_mfma_io<float, double>(L.links, L.link_prec, t, out, g, ncol, 1.0, M5, true, skip,
-                                                       stride, st);
+                                                       stride, st, epi);
         }
     }
     hipError_t e = apply_dw<T>(l, in, tmp, m, false, ncol, st, skip);
@@ -238,9 +237,9 @@ hipError_t Hierarchy::apply_A(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp,
         cpx<T>* y = C<T>(work_[0].py);
         e = pv_poly<T>(tmp, y, C<T>(work_[0].pz), ncol, st, skip);
         if (e != hipSuccess) return e;
-        return apply_dw<T>(l, y, out, 1.0, true, ncol, st, skip);
+        return apply_dw<T>(l, y, out, 1.0, true, ncol, st, skip, epi);
     }
-    return apply_dw<T>(l, tmp, out, 1.0, true, ncol, st, skip);
+    return apply_dw<T>(l, tmp, out, 1.0, true, ncol, st, skip, epi);
 }
 
 // A^dag = D_DW^dag D_PV (with the PV polynomial: D_DW^dag p(X) D_PV; p(X) is Hermitian)
@@ -443,11 +442,37 @@ Task Hierarchy::cgnr(int l, const cpx<T>* b, cpx<T>* x, int ncol, hipStream_t st
     co_return DWF_OK;
 }
 
+// Shift c of the s-step directions on level l (P_{i+1} = A P_i / c - P_i).  D_W(M5) + 1 is
+// (3 + M5) minus hops of norm at most 2, the fifth-dimension hop has norm max(1, |m|), and
+// the coarse kernels are their Galerkin projections, so |A| <= B^2 with B the sum; A's
+// spectrum lies in the right half-plane.  Directions shifted to about a third of the
+// bound stay well apart while low modes do not drown in the shift: the residual's drift over
+// 20 steps in cycles of 5 in FP32 measured 3.8e-7 |r0| (1.4e-6 on a source of low modes) against
+// 2.2e-7 (1.3e-6) for directions that minimise at every step, 3.5e-6 (unshifted), and 2.1e-7 (3.5e-6)
+// at half the bound.  A power of two, so that the division by c is exact.
+double Hierarchy::ss_shift(int l) const {
+    const double B = std::fabs(3.0 + M5) + 2.0 + std::max(1.0, std::fabs(m));
+    double top = B * B;
+    if (l == 0 && prm.pv_poly_order > 0) {   // A_p = D_PV^dag p(X) D_DW: the largest |x p(x)| on [0, B^2]
+        top = 0.0;
+        for (int i = 1; i <= 1024; ++i) {
+            const double x = B * B * i / 1024.0;
+            double p = 0.0;
+            for (int k = prm.pv_poly_order; k >= 0; --k) p = p * x + prm.pv_poly[k];
+            top = std::max(top, std::fabs(x * p));
+        }
+    }
+    const double c = 0.36 * top;
+    return std::isfinite(c) && c > 1e-30 && c < 1e30 ? std::exp2(std::round(std::log2(c))) : 1.0;
+}
+
 // ------------------------------------------------------------ restarted GCR (coarsest level)
-// Unpreconditioned GCR(kmax) on A with every decision on the device (the
-// stop flags are reset by gcr_dev_init at the start of every solve): each
-// cycle runs kmax fused iterations whose kernels turn into no-ops for
-// converged columns, then updates x and restarts from the recursive residual
+// Unpreconditioned GCR(kmax) on A with every decision on the device: cycles of at most
+// kSsMax iterations take the s-step form (ss_finish: the directions first, then the
+// cycle's minimal residual in three launches, with the stop decision after every step);
+// longer ones run kmax fused iterations that orthogonalise, whose accuracy does not depend on
+// the directions' condition, and whose kernels turn into no-ops for converged columns.  Either
+// way a cycle updates x and continues from the recursive residual
 // (in FP64 over the few hundred iterations of a coarsest solve to a loose
 // tolerance it stays within rounding of the true one; recomputing it cost two
 // coarse stencils per cycle).  The stop decision is the recursive one in either
@@ -468,56 +493,64 @@ Task Hierarchy::gcr_plain(int l, const cpx<T>* b, cpx<T>* x, int ncol, double to
     cpx<T>* t = C<T>(w.tmp);
     GcrDev& g = w.gcr;
     const double tol2 = tol * tol;
-    CO_HIPCHK(vzero<T>(x, nt, st));
-    CO_HIPCHK((vconvert<T, T>(b, r, nt, st)));
-    CO_HIPCHK((vconvert<T, T>(b, P, nt, st)));   // the first search direction (later cycles: by the residual pass)
-    CO_HIPCHK(norm2<T>(b, n, ncol, g.rr, rw_, st));
-    CO_HIPCHK(gcr_dev_init(ncol, g, st));
+    const bool ss = kmax <= kSsMax;
+    const double c_ss = ss_shift(l);
+    SsVecs<T> V{};
+    if (ss) {
+        // P_0 .. P_{kmax-1}, and the last direction in W_0 (the s-step form keeps no W)
+        for (int k = 0; k < kmax; ++k) V.p[k] = P + (size_t)k * nt;
+        V.p[kmax] = W;
+        CO_HIPCHK(ss_begin<T>(b, P, x, n, ncol, g, st));
+    } else {
+        CO_HIPCHK(vzero<T>(x, nt, st));
+        CO_HIPCHK((vconvert<T, T>(b, r, nt, st)));
+        CO_HIPCHK((vconvert<T, T>(b, P, nt, st)));   // the first search direction (later cycles: by the residual pass)
+        CO_HIPCHK(norm2<T>(b, n, ncol, g.rr, rw_, st));
+        CO_HIPCHK(gcr_dev_init(ncol, g, st));
+    }
     if constexpr (std::is_same<T, double>::value) {
         if (def_nev_ > 0 && l == (int)levels.size() - 1) {
             // deflated start x0 = V Lambda^{-1} V^dag A^dag b (V: lowest eigenvectors of
             // A^dag A, the right singular vectors of A): the minimiser of |b - A x| over
             // span(V); the tolerance stays relative to |b|.  W_0 is scratch here (the
-            // first iteration writes it).
+            // first cycle writes it).
             cpx<T>* z = W;
+            if (ss) CO_HIPCHK(norm2<T>(b, n, ncol, g.bb, rw_, st));
             CO_HIPCHK(apply_Adag<T>(l, b, z, t, ncol, st));
             if (int e = deflate_guess(l, z, x, ncol, st)) co_return e;
             CO_HIPCHK(apply_A<T>(l, x, z, t, ncol, st));
-            CO_HIPCHK(vsub<T>(b, z, r, nt, st));
-            CO_HIPCHK((vconvert<T, T>(r, P, nt, st)));
-            CO_HIPCHK(norm2<T>(r, n, ncol, g.rr, rw_, st));
+            CO_HIPCHK(vsub<T>(b, z, ss ? P : r, nt, st));
+            if (!ss) {
+                CO_HIPCHK((vconvert<T, T>(r, P, nt, st)));
+                CO_HIPCHK(norm2<T>(r, n, ncol, g.rr, rw_, st));
+            }
         }
     }
-    // one restart cycle: kmax fused iterations (inner products, then one pass that orthogonalises
-    // the new direction and updates the residual; the stop flags alternate between two buffers so
-    // that no kernel writes the flags it reads), the solution update, and the restart.  Cycles
-    // of at most kGramSteps take the Gram form instead (the smoother's), with the residual in P_0.
-    const bool gram = kmax <= kGramSteps;
+    // one restart cycle.  s-step form: kmax applications of A, then ss_finish (which leaves the
+    // next cycle's residual in P_0).  Orthogonalising form: kmax fused iterations (inner
+    // products, then one pass that orthogonalises the new direction and updates the residual;
+    // the stop flags alternate between two buffers so that no kernel writes the flags it reads),
+    // the solution update, and the restart.
     auto cycle = [&]() -> int {
         for (int k = 0; k < kmax; ++k) {
+            if (ss) {
+                HIPCHK(apply_A<T>(l, V.p[k], V.p[k + 1], t, ncol, st, nullptr, Epi<T>{V.p[k], 1.0 / c_ss, -1.0}));
+                continue;
+            }
             cpx<T>* Pk = P + (size_t)k * nt;
             cpx<T>* Wk = W + (size_t)k * nt;
             const int* s_in = (k % 2 == 0) ? g.stop : g.stop2;
             int* s_out = (k % 2 == 0) ? g.stop2 : g.stop;
             HIPCHK(apply_A<T>(l, Pk, Wk, t, ncol, st));
-            if (gram && k + 1 < kmax) {
-                // the next direction: the minimal residual so far, from P_0 (the cycle's residual)
-                HIPCHK(gcr_gram_step<T>(W, nt, k, P, P + (size_t)(k + 1) * nt, n, ncol, tol2, s_in, s_out, g, rw_,
-                                        st));
-            } else if (gram) {
-                // and the solution update, P_0 = the next cycle's residual
-                HIPCHK(gcr_gram_last<T>(P, W, nt, kmax, x, n, ncol, tol2, s_in, s_out, g, rw_, st));
-            } else {
-                // the updated residual is the next search direction
-                HIPCHK(gcr_fused_step<T>(W, nt, k, Wk, r, k + 1 < kmax ? P + (size_t)(k + 1) * nt : nullptr, n,
-                                         ncol, tol2, s_in, s_out, g, rw_, st));
-            }
+            // the updated residual is the next search direction
+            HIPCHK(gcr_fused_step<T>(W, nt, k, Wk, r, k + 1 < kmax ? P + (size_t)(k + 1) * nt : nullptr, n,
+                                     ncol, tol2, s_in, s_out, g, rw_, st));
         }
         // solution update, and the next cycle continues from the recursive residual (its
         // norm and the stop flags are those of the last fused step)
-        if (!gram)
-            HIPCHK(gcr_solve_xupdate_restart<T>(P, nt, kmax, x, n, ncol, r, (kmax % 2 == 0) ? g.stop : g.stop2, g,
-                                                st));
+        if (ss) HIPCHK(ss_finish<T>(V, kmax, x, n, ncol, c_ss, tol2, false, g, rw_, st));
+        else HIPCHK(gcr_solve_xupdate_restart<T>(P, nt, kmax, x, n, ncol, r, (kmax % 2 == 0) ? g.stop : g.stop2, g,
+                                                 st));
         // the cycle ends by publishing the stop flags to the host (part of the graph)
         unsigned v = 0;
         HIPCHK(publish(st, {{h_int_, g.stop, sizeof(int) * ncol}}, &v));
@@ -561,30 +594,34 @@ int Hierarchy::smooth(int l, const cpx<T>* r, cpx<T>* z, int ncol, hipStream_t s
     cpx<T>* rs = C<T>(w.rs);
     cpx<T>* t = C<T>(w.tmp);
     cpx<T>* Az = C<T>(w.tmp2);
-    // the steps are the fused GCR iteration of the coarsest solve (inner products in
-    // one pass, orthogonalisation and residual update in a second) with a stopping
-    // threshold that is never met, so that all ns steps are taken.  With a restart
-    // length ks < ns the steps run in cycles of ks (the orthogonalisation cost of a
-    // step grows with its index in the cycle); each cycle adds its correction to z and
-    // the next starts from the recursive residual.
+    // the steps are those of the coarsest solve with a stopping threshold that is never met, so
+    // that all ns steps are taken.  With a restart length ks < ns the steps run in cycles of ks
+    // (the orthogonalisation cost of a step grows with its index in the cycle); each cycle
+    // adds its correction to z and the next starts from the recursive residual.  Cycles of at
+    // most kSsMax steps take the s-step form, the residual in P_0; longer ones the
+    // orthogonalising form, whose accuracy does not depend on the directions' condition.
     const int ks = w.kscycle;
     GcrDev& g = w.gsm;
-    // Short cycles take the Gram form (the directions' inner products and the cycle's starting
-    // residual give each step's minimal residual; no orthogonalised direction and no running
-    // residual is stored: two vector passes fewer per step, and the starting residual is the
-    // first direction P_0 itself); long ones keep the orthogonalising form, whose accuracy does
-    // not depend on the Gram matrix's condition (the square of the directions').
-    const bool gram = ks <= kGramSteps;
+    const bool ss = ks <= kSsMax;
+    const double c_ss = ss_shift(l);
+    SsVecs<T> V{};
+    if (ss)
+        for (int j = 0; j <= ks; ++j) V.p[j] = Ps + (size_t)j * nt;
     auto body = [&]() -> int {
-        HIPCHK(apply_A<T>(l, z, Az, t, ncol, st));
-        if (gram) {
-            HIPCHK(vsub<T>(r, Az, Ps, nt, st));
-            HIPCHK(norm2<T>(Ps, n, ncol, g.rr, rw_, st));
-        } else {
-            HIPCHK(vsub<T>(r, Az, rs, nt, st));
-            HIPCHK(vconvert<T, T>(rs, Ps, nt, st));
-            HIPCHK(norm2<T>(rs, n, ncol, g.rr, rw_, st));
+        if (ss) {
+            HIPCHK(apply_A<T>(l, z, Ps, t, ncol, st, nullptr, Epi<T>{r, -1.0, 1.0}));   // P_0 = r - A z
+            for (int c0 = 0; c0 < ns; c0 += ks) {
+                const int kc = std::min(ks, ns - c0);
+                for (int j = 0; j < kc; ++j)
+                    HIPCHK(apply_A<T>(l, V.p[j], V.p[j + 1], t, ncol, st, nullptr, Epi<T>{V.p[j], 1.0 / c_ss, -1.0}));
+                HIPCHK(ss_finish<T>(V, kc, z, n, ncol, c_ss, -1.0, c0 == 0, g, rw_, st));
+            }
+            return DWF_OK;
         }
+        HIPCHK(apply_A<T>(l, z, Az, t, ncol, st));
+        HIPCHK(vsub<T>(r, Az, rs, nt, st));
+        HIPCHK(vconvert<T, T>(rs, Ps, nt, st));
+        HIPCHK(norm2<T>(rs, n, ncol, g.rr, rw_, st));
         HIPCHK(gcr_dev_init(ncol, g, st));
         for (int c0 = 0; c0 < ns; c0 += ks) {
             const int kc = std::min(ks, ns - c0);
@@ -594,20 +631,10 @@ int Hierarchy::smooth(int l, const cpx<T>* r, cpx<T>* z, int ncol, hipStream_t s
                 const int* s_in = (j % 2 == 0) ? g.stop : g.stop2;
                 int* s_out = (j % 2 == 0) ? g.stop2 : g.stop;
                 HIPCHK(apply_A<T>(l, Pj, Wj, t, ncol, st));
-                if (gram && j + 1 < kc) {
-                    // the next direction r_{j+1} = P_0 - sum y_i W_i
-                    HIPCHK(gcr_gram_step<T>(Ws, nt, j, Ps, Ps + (size_t)(j + 1) * nt, n, ncol, -1.0, s_in, s_out, g,
-                                            rw_, st));
-                } else if (gram) {
-                    // z += this cycle's correction, P_0 = the next cycle's starting residual
-                    HIPCHK(gcr_gram_last<T>(Ps, Ws, nt, kc, z, n, ncol, -1.0, s_in, s_out, g, rw_, st));
-                } else {
-                    HIPCHK(gcr_fused_step<T>(Ws, nt, j, Wj, rs, (j + 1 < kc) ? Ps + (size_t)(j + 1) * nt : nullptr,
-                                             n, ncol, -1.0, s_in, s_out, g, rw_, st));
-                }
+                HIPCHK(gcr_fused_step<T>(Ws, nt, j, Wj, rs, (j + 1 < kc) ? Ps + (size_t)(j + 1) * nt : nullptr, n, ncol,
+                                         -1.0, s_in, s_out, g, rw_, st));
             }
             const int* s_last = (kc % 2 == 0) ? g.stop : g.stop2;
-            if (gram) continue;   // (the last Gram step did the solution update)
             if (c0 + kc < ns) {
                 // z += this cycle's correction, P_0 = the residual, the last step's flags to g.stop
                 HIPCHK(gcr_solve_xupdate_restart<T>(Ps, nt, kc, z, n, ncol, rs, s_last, g, st));

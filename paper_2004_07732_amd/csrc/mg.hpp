@@ -300,14 +300,17 @@ private:
 
     // operators on level l in precision T
     template <typename T> hipError_t apply_dw(int l, const cpx<T>* in, cpx<T>* out, double mass, bool dag,
-                                              int ncol, hipStream_t st, const int* skip = nullptr);
+                                              int ncol, hipStream_t st, const int* skip = nullptr,
+                                              const Epi<T>& epi = {});
     // stencil applications of one A (or A^dag) on level l
     int a_cost(int l) const { return (l == 0 && prm.pv_poly_order > 0) ? 2 * prm.pv_poly_order + 2 : 2; }
     // y = p(X) w on the fine level, X = D_PV D_PV^dag, p from prm.pv_poly (z: scratch)
     template <typename T> hipError_t pv_poly(const cpx<T>* w, cpx<T>* y, cpx<T>* z, int ncol, hipStream_t st,
                                              const int* skip = nullptr);
     template <typename T> hipError_t apply_A(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp, int ncol,
-                                             hipStream_t st, const int* skip = nullptr);
+                                             hipStream_t st, const int* skip = nullptr, const Epi<T>& epi = {});
+    // shift of the s-step Krylov directions on level l
+    double ss_shift(int l) const;
     template <typename T> hipError_t apply_Adag(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp, int ncol,
                                                 hipStream_t st, const int* skip = nullptr);
     template <typename T> hipError_t apply_wilson(int l, const cpx<T>* in, cpx<T>* out, double mass,
