@@ -810,10 +810,12 @@ __global__ void __launch_bounds__(kBlock, 2) k_ss_dots(SsVecs<T> P, size_t nw, R
 // One workgroup per column: wave w adds the partials of blocks w, w + 16, ... (lane = sum), then
 // wave 0 factors G by Cholesky with lane i holding row i.  The residual norm after step k is
 // |r0|^2 - sum_{i<=k} |u_i|^2 (u = L^-1 b), so a tolerance met inside the cycle ends it at that
-// step: the coefficients are those of its leading block.  A pivot within rounding of zero
+// step: the coefficients are those of its leading block.  Below kSsTrust of the cycle's start that
+// difference is rounding; the next cycle's |P_0|^2 then decides.  A pivot within rounding of zero
 // against its direction's own norm drops that direction.
 constexpr int kSsFinWaves = 16;
 constexpr double kSsPivot = 1e-13;
+constexpr double kSsTrust = 1e-12;
 template <int K>
 __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb, GcrDev g, double tol2, double inv_c,
                                                             int first) {
@@ -854,7 +856,7 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
     const double bb = bb0 < 0.0 ? rr0 : bb0;
     int flag = flag0;
     if (flag == 0 && !sane) flag = 2;
-    if (flag == 0 && rr0 == 0.0) flag = 1;
+    if (flag == 0 && (rr0 == 0.0 || (bb0 >= 0.0 && rr0 <= tol2 * bb))) flag = 1;
     if (flag != 0) {   // the column takes no update
         if (lane == 0) {
             coef[kGcrTot - 1] = 0.0;
@@ -907,7 +909,7 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
             rr -= u[k].re * u[k].re + u[k].im * u[k].im;
             kend = k + 1;
             if (!finite(rr)) flag = 2;
-            else if (rr <= tol2 * bb) flag = 1;
+            else if (rr <= tol2 * bb && rr > kSsTrust * rr0) flag = 1;
         }
     }
     if (lane != 0) return;
