@@ -689,6 +689,8 @@ k_gcr_fused_update(const cpx<T>* W, size_t wstride, cpx<T>* w, cpx<T>* r, cpx<T>
 // 256^2 x 16 FP32, 5 steps: 73 vector passes and 25 launches a cycle before (with the
 // stencils), 42 passes and 13 launches now.
 namespace {
+// 512 threads: half as many partials to add as 256 would leave for the same waves in flight
+constexpr int kSsThreads = 512;
 constexpr int ss_nq(int k) { return (k + 1) * (k + 1); }   // real sums of a (k+1)^2 Hermitian H
 // complex entries of one 16-byte word, and their sum over a word
 template <typename T> struct Word;
@@ -710,32 +712,31 @@ constexpr int ss_off(int k, int a, int b) { return (k + 1) + 2 * (a * (2 * k + 1
 // Sum v[0..NP) over the 64 lanes by halving: lanes that differ in one bit exchange half of their
 // values each, so NP sums take NP - 1 exchanges instead of 6 NP.  The total of value i ends in
 // v[0] of the lanes whose bits 0.. hold i (log2 NP of them, most significant bit of i first).
-template <int NP>
+template <int NP, int BIT = 1>
 __device__ __forceinline__ void reduce_scatter(double* v, int lane) {
-    int bit = 1;
+    if constexpr (NP > 1) {
+        const bool up = lane & BIT;
 #pragma unroll
-    for (int h = NP / 2; h >= 1; h >>= 1, bit <<= 1) {
-        const bool up = lane & bit;
-#pragma unroll
-        for (int i = 0; i < h; ++i) {
-            const double keep = up ? v[i + h] : v[i], give = up ? v[i] : v[i + h];
-            v[i] = keep + __shfl_xor(give, bit, 64);
+        for (int i = 0; i < NP / 2; ++i) {
+            const double keep = up ? v[i + NP / 2] : v[i], give = up ? v[i] : v[i + NP / 2];
+            v[i] = keep + __shfl_xor(give, BIT, 64);
         }
+        reduce_scatter<NP / 2, BIT * 2>(v, lane);
+    } else if constexpr (BIT < 64) {
+        v[0] += __shfl_xor(v[0], BIT, 64);
+        reduce_scatter<1, BIT * 2>(v, lane);
     }
-    for (; bit < 64; bit <<= 1) v[0] += __shfl_xor(v[0], bit, 64);
 }
 // the value whose total lane `lane` holds after reduce_scatter<NP>
-template <int NP>
+template <int NP, int BIT = 1>
 __device__ __forceinline__ int scatter_index(int lane) {
-    int i = 0, bit = 1;
-#pragma unroll
-    for (int h = NP / 2; h >= 1; h >>= 1, bit <<= 1) i |= (lane & bit) ? h : 0;
-    return i;
+    if constexpr (NP > 1) return ((lane & BIT) ? NP / 2 : 0) + scatter_index<NP / 2, BIT * 2>(lane);
+    else return 0;
 }
 }  // namespace
 
 template <typename T, int K>
-__global__ void __launch_bounds__(kBlock, 2) k_ss_dots(SsVecs<T> P, size_t nw, RedWork rw) {
+__global__ void __launch_bounds__(kSsThreads) k_ss_dots(SsVecs<T> P, size_t nw, RedWork rw) {
     using W = Word<T>;
     typedef typename W::type word;
     constexpr int NQ = ss_nq(K);
@@ -743,7 +744,7 @@ __global__ void __launch_bounds__(kBlock, 2) k_ss_dots(SsVecs<T> P, size_t nw, R
     constexpr int N1 = NQ <= 4 ? 4 : (NQ <= 16 ? 16 : (NQ <= 36 ? 32 : 64));
     constexpr int N2 = NQ <= N1 ? 0 : (NQ - N1 <= 4 ? 4 : 32);
     static_assert(NQ <= N1 + N2, "two groups hold every sum");
-    __shared__ double sh[kWaves][N1 + N2];
+    __shared__ double sh[kSsThreads / 64][N1 + N2];
     const int col = blockIdx.y;
     const size_t o = (size_t)col * nw;
     const word* p[K + 1];
@@ -760,20 +761,23 @@ __global__ void __launch_bounds__(kBlock, 2) k_ss_dots(SsVecs<T> P, size_t nw, R
             for (int a = 0; a <= K; ++a) z[a] = W::at(w[a], e);
 #pragma unroll
             for (int a = 0; a <= K; ++a) {
-                v[a] += z[a].re * z[a].re + z[a].im * z[a].im;
+                v[a] = fma(z[a].re, z[a].re, v[a]);
+                v[a] = fma(z[a].im, z[a].im, v[a]);
 #pragma unroll
                 for (int b = a + 1; b <= K; ++b) {
                     const int q = ss_off(K, a, b);
-                    v[q] += z[a].re * z[b].re + z[a].im * z[b].im;
-                    v[q + 1] += z[a].re * z[b].im - z[a].im * z[b].re;
+                    v[q] = fma(z[a].re, z[b].re, v[q]);
+                    v[q + 1] = fma(z[a].re, z[b].im, v[q + 1]);
+                    v[q] = fma(z[a].im, z[b].im, v[q]);
+                    v[q + 1] = fma(-z[a].im, z[b].re, v[q + 1]);
                 }
             }
         }
     };
     // U words of every vector are loaded together (bounded by the registers beside the sums)
     constexpr int U = K <= 3 ? 4 : (K <= 5 || (K == 6 && W::E == 1) ? 2 : 1);
-    const size_t stride = (size_t)gridDim.x * kBlock;
-    size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    const size_t stride = (size_t)gridDim.x * kSsThreads;
+    size_t e = (size_t)blockIdx.x * kSsThreads + threadIdx.x;
     for (; e + (U - 1) * stride < nw; e += U * stride) {
         word w[U][K + 1];
 #pragma unroll
@@ -799,10 +803,10 @@ __global__ void __launch_bounds__(kBlock, 2) k_ss_dots(SsVecs<T> P, size_t nw, R
     __syncthreads();
     // partials block by block, the sums of one block side by side
     double* part = rw.partial + (size_t)col * rw.max_q * rw.nblk + (size_t)blockIdx.x * NQ;
-    for (int q = threadIdx.x; q < NQ; q += kBlock) {
+    for (int q = threadIdx.x; q < NQ; q += kSsThreads) {
         double t = 0.0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) t += sh[w][q];
+        for (int w = 0; w < kSsThreads / 64; ++w) t += sh[w][q];
         part[q] = t;
     }
 }
@@ -894,7 +898,7 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
         if (flag == 0) {   // (uniform)
             const double d = bcast(G[k].re, k), d0 = bcast(dg, k);
             const bool ok = d > kSsPivot * d0 && finite(d);
-            inv[k] = ok ? 1.0 / sqrt(d) : 0.0;
+            inv[k] = ok ? rsqrt(d) : 0.0;
             u[k] = {bcast(bi.re, k) * inv[k], bcast(bi.im, k) * inv[k]};
             const cpx<double> lk = {G[k].re * inv[k], G[k].im * inv[k]};   // L_ik of this lane's row
             if (lane < K) sL[i][k] = lk;
@@ -970,11 +974,15 @@ __global__ void __launch_bounds__(kBlock) k_ss_update(SsVecs<T> P, cpx<T>* x, si
             for (int k = 0; k <= K; ++k) {
                 const cpx<double> z = W::at(w[k], c);
                 if (k < K) {
-                    xa.re += y[k].re * z.re - y[k].im * z.im;
-                    xa.im += y[k].re * z.im + y[k].im * z.re;
+                    xa.re = fma(y[k].re, z.re, xa.re);
+                    xa.im = fma(y[k].re, z.im, xa.im);
+                    xa.re = fma(-y[k].im, z.im, xa.re);
+                    xa.im = fma(y[k].im, z.re, xa.im);
                 }
-                ra.re += d[k].re * z.re - d[k].im * z.im;
-                ra.im += d[k].re * z.im + d[k].im * z.re;
+                ra.re = fma(d[k].re, z.re, ra.re);
+                ra.im = fma(d[k].re, z.im, ra.im);
+                ra.re = fma(-d[k].im, z.im, ra.re);
+                ra.im = fma(d[k].im, z.re, ra.im);
             }
             W::put(xv, c, xa);
             W::put(r, c, ra);
@@ -1178,14 +1186,14 @@ hipError_t ss_finish(const SsVecs<T>& P, int k, cpx<T>* x, size_t n, int ncol, d
                      const GcrDev& g, const RedWork& rw, hipStream_t st) {
     if (k < 1 || k > kSsMax || 4 * k + 3 > kGcrTot || n % Word<T>::E) return hipErrorInvalidValue;
     const size_t nw = n / Word<T>::E;
-    // blocks per column: two words per thread at least, two workgroups per CU over all columns
+    // blocks per column: two words per thread at least, one workgroup per CU over all columns
     // (a block's sums cost as much as streaming several words, and one workgroup adds them all)
-    long long nb = (long long)((nw + 2 * kBlock - 1) / (2 * kBlock));
-    nb = std::min<long long>(nb, std::max(kSsBlocks / ncol, 64));
+    long long nb = (long long)((nw + 2 * kSsThreads - 1) / (2 * kSsThreads));
+    nb = std::min<long long>(nb, std::max(kSsBlocks / ncol, 32));
     nb = std::max<long long>(std::min<long long>(nb, (long long)rw.max_q * rw.nblk / ss_nq(k)), 1);
     auto launch = [&](auto kc) {
         constexpr int K = decltype(kc)::value + 1;
-        hipLaunchKernelGGL((k_ss_dots<T, K>), dim3((unsigned)nb, ncol), dim3(kBlock), 0, st, P, nw, rw);
+        hipLaunchKernelGGL((k_ss_dots<T, K>), dim3((unsigned)nb, ncol), dim3(kSsThreads), 0, st, P, nw, rw);
         hipLaunchKernelGGL(k_ss_fin<K>, dim3(ncol), dim3(64 * kSsFinWaves), 0, st, rw, (int)nb, g, tol2, 1.0 / c,
                            first ? 1 : 0);
         hipLaunchKernelGGL((k_ss_update<T, K>), ew_grid(nw, ncol), dim3(kBlock), 0, st, P, x, nw, g);

@@ -210,7 +210,7 @@ hipError_t gcr_fused_step(const cpx<T>* W, size_t wstride, int j, cpx<T>* w, cpx
 // steps it took.  A stopped column takes no update.  `first` starts the column state afresh
 // (|b|^2 = |P_0|^2); otherwise ss_begin (P_0 = b, x = 0) or the previous cycle left it.
 constexpr int kSsMax = 8;
-constexpr int kSsBlocks = 512;
+constexpr int kSsBlocks = 256;
 template <typename T> struct SsVecs { cpx<T>* p[kSsMax + 1]; };
 template <typename T>
 hipError_t ss_begin(const cpx<T>* b, cpx<T>* P0, cpx<T>* x, size_t n, int ncol, const GcrDev& g, hipStream_t st);

@@ -75,11 +75,11 @@ def test_narrow_links(link, Lsc, ncol):
     mg, o = pair(16, 24, 12, (4, 4), Lsc, ncol, lp, 970)
 
     def rnd(a):
+        if link == "f16":   # (rounded once, from FP64)
+            return np.asarray(a).astype(np.float16).astype(np.float64)
         f = np.ascontiguousarray(a, dtype=np.float32)
         if link == "f32":
             return f.astype(np.float64)
-        if link == "f16":
-            return f.astype(np.float16).astype(np.float64)
         u = f.view(np.uint32).astype(np.uint64)
         u = ((u + 0x7FFF + ((u >> 16) & 1)) >> 16) << 16
         return u.astype(np.uint32).view(np.float32).astype(np.float64)
