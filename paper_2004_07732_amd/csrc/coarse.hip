@@ -209,7 +209,7 @@ coarse_block_kernel(const L* __restrict__ links, const cpx<T>* __restrict__ in, 
     __shared__ __attribute__((aligned(16))) cpx<A> sm[5][OUT];           // staged vectors, then the wave's part
     const int lane = threadIdx.x & 63;
     const int d = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int site = (int)xcd_block(blockIdx.x, gridDim.x);
+    const int site = (int)xcd_block_dir<DAG>(blockIdx.x, gridDim.x);
     const int x = site % Lx, y = site / Lx;
     int nb = site;
     if (d == 1) nb = y * Lx + ((x + 1 == Lx) ? 0 : x + 1);

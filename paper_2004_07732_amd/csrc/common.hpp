@@ -101,6 +101,19 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned nb) {
     return x * q + (x < r ? x : r) + k;
 }
 
+// The same ranges, each XCD's walked from its end.  The adjoint stencils walk this way: an A or
+// A^dagger alternates the two directions, so a launch begins with the links and vectors that the
+// previous launch read and wrote last, which are still in the XCD's 4 MB L2 (a forward walk finds
+// none of a larger range: least recently used is replaced first).
+__device__ __forceinline__ unsigned xcd_block_rev(unsigned b, unsigned nb) {
+    const unsigned x = b % kXcds, k = b / kXcds, q = nb / kXcds, r = nb % kXcds;
+    return x * q + (x < r ? x : r) + (q + (x < r ? 1 : 0) - 1 - k);
+}
+template <bool REV>
+__device__ __forceinline__ unsigned xcd_block_dir(unsigned b, unsigned nb) {
+    return REV ? xcd_block_rev(b, nb) : xcd_block(b, nb);
+}
+
 inline unsigned grid_for(long long n, int block = kBlock) {
     long long g = (n + block - 1) / block;
     return (unsigned)(g < 1 ? 1 : g);
