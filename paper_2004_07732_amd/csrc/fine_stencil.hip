@@ -845,6 +845,175 @@ bool fine_a_chosen(int prec_bytes, int Lx, int Ly, int Ls, int ncol, int* shape,
     return true;
 }
 
+// ------------------------------------------------------------ null-vector relaxation, one CG iteration
+// CG on B v = 0, B = D_W D_W^dag, for a block of 2-d vectors, three launches an iteration:
+//   1: t = D_W^dag p, partial sums of |t|^2
+//   2: alpha = zz / |t|^2;  r -= alpha D_W t, partial sums of |r|^2   (D_W t is never stored)
+//   3: beta = |r|^2 / zz;  x += alpha p, p = r + beta p
+// HBM / Infinity Cache bound: 10 vector passes (read 6, written 4) where separate stencils,
+// norms, finalisers and updates took 15 in eight launches (256^2, 16 vectors: 108 us an
+// iteration before, see the figure at wilson_cg).  Every workgroup adds the partial sums itself,
+// in the same order, so no finaliser stands between the launches; the column's state is read
+// from one buffer and written to the other by the column's first workgroup.  Two columns a thread
+// share the links.
+__device__ __forceinline__ double wave_add(double x) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+    return x;
+}
+// sum of nb partials by one workgroup of kBlock threads (the same value in every thread)
+__device__ __forceinline__ double block_total(const double* part, int nb, double* sh) {
+    double s = 0.0;
+    for (int b = threadIdx.x; b < nb; b += kBlock) s += part[b];
+    s = wave_add(s);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    s = sh[0] + sh[1] + sh[2] + sh[3];
+    __syncthreads();
+    return s;
+}
+__device__ __forceinline__ bool is_finite(double x) { return !(isnan(x) || isinf(x)); }
+
+template <int STEP, int CPT>
+__global__ void __launch_bounds__(kBlock)
+wilson_cg_kernel(const cpx<double>* __restrict__ U, const spinor<double>* __restrict__ in, spinor<double>* __restrict__ out,
+                 int Lx, int Ly, int ncol, int nb, double diag, const CgScal* __restrict__ sin, CgScal* __restrict__ sout,
+                 const double* __restrict__ pin, double* __restrict__ pout, size_t pstride) {
+    constexpr bool DAG = STEP == 1;
+    __shared__ double sh[4], red[CPT][4];
+    const int V = Lx * Ly;
+    const int ngrp = (ncol + CPT - 1) / CPT;
+    const unsigned lb = xcd_block(blockIdx.x, gridDim.x);   // column groups of one site block side by side
+    const int c0 = (int)(lb % (unsigned)ngrp) * CPT, sb = (int)(lb / (unsigned)ngrp);
+    bool live[CPT];
+    double alpha[CPT];
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+        const int c = min(c0 + j, ncol - 1);
+        CgScal s = sin[c];
+        live[j] = c0 + j < ncol && s.done == 0;
+        alpha[j] = 0.0;
+        if (STEP == 2 && c0 + j < ncol) {   // (the same for the whole workgroup)
+            if (live[j]) {
+                const double ww = block_total(pin + (size_t)c * pstride, nb, sh);
+                if (!(ww > 0.0) || !is_finite(ww)) {
+                    s.done = is_finite(ww) ? 2 : 4;   // breakdown / non-finite
+                    s.alpha = 0.0;
+                    live[j] = false;
+                } else {
+                    s.alpha = s.zz / ww;
+                }
+                alpha[j] = s.alpha;
+            }
+            if (sb == 0 && threadIdx.x == 0) sout[c] = s;
+        }
+    }
+    double acc[CPT];
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) acc[j] = 0.0;
+    for (int tile = sb; tile * kBlock < V; tile += nb) {
+        const int site = tile * kBlock + (int)threadIdx.x;
+        if (site >= V) continue;
+        const int x = site % Lx, y = site / Lx;
+        const int xp = (x + 1 == Lx) ? 0 : x + 1, xm = (x == 0) ? Lx - 1 : x - 1;
+        const int yp = (y + 1 == Ly) ? 0 : y + 1, ym = (y == 0) ? Ly - 1 : y - 1;
+        const int sxp = y * Lx + xp, sxm = y * Lx + xm, syp = yp * Lx + x, sym = ym * Lx + x;
+        const cpx<double> hu0 = 0.5 * U[site], hu0m = 0.5 * U[sxm];
+        const cpx<double> hu1 = 0.5 * U[V + site], hu1m = 0.5 * U[V + sym];
+#pragma unroll
+        for (int j = 0; j < CPT; ++j) {
+            if (!live[j]) continue;
+            const spinor<double>* src = in + (size_t)(c0 + j) * V;
+            const spinor<double> cur = src[site], fx = src[sxp], bx = src[sxm], fy = src[syp], by = src[sym];
+            spinor<double>* dst = out + (size_t)(c0 + j) * V + site;
+            spinor<double> o;
+            if (STEP == 2) o = *dst;
+            cpx<double> a0 = {0.0, 0.0}, a1 = {0.0, 0.0};
+            wilson_hops<double, DAG>(fx, bx, fy, by, hu0, hu0m, hu1, hu1m, a0, a1);
+            spinor<double> w;
+            w.c0 = diag * cur.c0 - a0;
+            w.c1 = diag * cur.c1 - a1;
+            if (STEP == 2) {
+                w.c0 = {o.c0.re - alpha[j] * w.c0.re, o.c0.im - alpha[j] * w.c0.im};
+                w.c1 = {o.c1.re - alpha[j] * w.c1.re, o.c1.im - alpha[j] * w.c1.im};
+            }
+            *dst = w;
+            acc[j] += w.c0.re * w.c0.re + w.c0.im * w.c0.im + w.c1.re * w.c1.re + w.c1.im * w.c1.im;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+        const double s = wave_add(acc[j]);
+        if ((threadIdx.x & 63) == 0) red[j][threadIdx.x >> 6] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x < CPT && c0 + (int)threadIdx.x < ncol)
+        pout[(size_t)(c0 + threadIdx.x) * pstride + sb] =
+            red[threadIdx.x][0] + red[threadIdx.x][1] + red[threadIdx.x][2] + red[threadIdx.x][3];
+}
+
+// step 3; the stop rule is that of cg_beta
+__global__ void __launch_bounds__(kBlock)
+wilson_cg_update(spinor<double>* __restrict__ x, spinor<double>* __restrict__ p, const spinor<double>* __restrict__ r,
+                 int V, int nb, int maxit, const CgScal* __restrict__ sin, CgScal* __restrict__ sout,
+                 const double* __restrict__ pin, size_t pstride) {
+    __shared__ double sh[4];
+    const int col = blockIdx.y;
+    CgScal s = sin[col];
+    const bool live = s.done == 0;
+    if (live) {
+        const double znew = block_total(pin + (size_t)col * pstride, nb, sh);
+        s.iters += 1;
+        if (!is_finite(znew)) {
+            s.done = 4;
+        } else {
+            s.beta = znew / s.zz;
+            s.zz = znew;
+            if (znew <= s.tol2 * s.zz0) s.done = 1;
+            else if (s.iters >= maxit) s.done = 3;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) sout[col] = s;
+    if (!live) return;
+    const double al = s.alpha, be = s.beta;
+    const bool more = s.done == 0;
+    const size_t o = (size_t)col * V;
+    for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < (size_t)V; i += (size_t)gridDim.x * kBlock) {
+        const spinor<double> pi = p[o + i], ri = r[o + i];
+        spinor<double> xi = x[o + i];
+        xi.c0 = {xi.c0.re + al * pi.c0.re, xi.c0.im + al * pi.c0.im};
+        xi.c1 = {xi.c1.re + al * pi.c1.re, xi.c1.im + al * pi.c1.im};
+        x[o + i] = xi;
+        if (more) {
+            spinor<double> pn;
+            pn.c0 = {ri.c0.re + be * pi.c0.re, ri.c0.im + be * pi.c0.im};
+            pn.c1 = {ri.c1.re + be * pi.c1.re, ri.c1.im + be * pi.c1.im};
+            p[o + i] = pn;
+        }
+    }
+}
+
+hipError_t wilson_cg(const cpx<double>* U, cpx<double>* x, cpx<double>* r, cpx<double>* p, cpx<double>* t, int Lx, int Ly,
+                     int ncol, double M, int maxit, CgScal* s, CgScal* s2, const RedWork& rw, hipStream_t st) {
+    const int V = Lx * Ly;
+    // (a workgroup adds nb partials: larger lattices give a workgroup several site tiles)
+    const int nb = std::min((V + kBlock - 1) / kBlock, 1024);
+    if (rw.max_q < 2 || nb > rw.nblk || ncol > rw.max_cols) return hipErrorInvalidValue;
+    const size_t pstride = (size_t)rw.max_q * rw.nblk;
+    double* pa = rw.partial;
+    double* pb = rw.partial + rw.nblk;
+    auto S = [](cpx<double>* v) { return reinterpret_cast<spinor<double>*>(v); };
+    const long long blocks = (long long)nb * ((ncol + 1) / 2);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((wilson_cg_kernel<1, 2>), dim3((unsigned)blocks), dim3(kBlock), 0, st, U, S(p), S(t), Lx, Ly, ncol,
+                       nb, 2.0 + M, s, s, (const double*)nullptr, pa, pstride);
+    hipLaunchKernelGGL((wilson_cg_kernel<2, 2>), dim3((unsigned)blocks), dim3(kBlock), 0, st, U, S(t), S(r), Lx, Ly, ncol,
+                       nb, 2.0 + M, s, s2, pa, pb, pstride);
+    hipLaunchKernelGGL(wilson_cg_update, dim3((unsigned)std::min(nb, 256), ncol), dim3(kBlock), 0, st, S(x), S(p), S(r), V,
+                       nb, maxit, s2, s, pb, pstride);
+    return hipGetLastError();
+}
+
 template <typename R>
 hipError_t wilson2d(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, int Lx, int Ly, int ncol,
                     double M, bool dagger, hipStream_t st) {

@@ -145,14 +145,102 @@ hipError_t block_orthonormalize(cpx<double>* V, int Lx, int Ly, int nc, int nvec
     const size_t shm = (size_t)bx * by * nc * nvec * sizeof(cpx<double>);
     if (shm > 64 * 1024 || nvec > 64) return hipErrorInvalidValue;
     dim3 grid((Lx / bx) * (Ly / by), 2);
-    hipLaunchKernelGGL(k_block_orth, grid, dim3(kBlock), shm, st, V, Lx, Ly, nc, nvec, bx, by, bad);
+    // one wavefront for small aggregates: the sums are serial per thread and the barriers between
+    // them were most of the time (16 entries x 16 columns, 4096 aggregates: 306 us with 256 threads)
+    const int threads = bx * by * nc <= 64 ? 64 : kBlock;
+    hipLaunchKernelGGL(k_block_orth, grid, dim3(threads), shm, st, V, Lx, Ly, nc, nvec, bx, by, bad);
     return hipGetLastError();
 }
 
 // ------------------------------------------------------------ Galerkin, level 0
 // Output column layout: links[((X*5 + d)*n + b)*n + a] = block_d[a][b], n = 2 nvec.
-__global__ void k_galerkin_fine(const cpx<double>* U, const cpx<double>* V, cpx<double>* links,
-                                int Lx, int Ly, int nvec, int bx, int by) {
+// One workgroup per coarse site: the aggregate's V with a one-site margin and its links are
+// staged in LDS once; a thread owns column b and four rows a of all five blocks, so that every
+// V(x+h) it reads serves four products.  Bound by the 5 n^2 FP64 entries a site that it writes
+// (256^2, 16 vectors: 335 MB); a thread per entry that read V through the caches took 560 us.
+__global__ void __launch_bounds__(kBlock)
+k_galerkin_fine(const cpx<double>* __restrict__ U, const cpx<double>* __restrict__ V, cpx<double>* __restrict__ links,
+                int Lx, int Ly, int nvec, int bx, int by) {
+    extern __shared__ unsigned char smem_raw[];
+    const int n = 2 * nvec, q4 = n / 4, W = bx + 2;
+    cpx<double>* sv = reinterpret_cast<cpx<double>*>(smem_raw);   // [(by + 2)(bx + 2)][n], chirality-major
+    cpx<double>* su = sv + (size_t)W * (by + 2) * n;              // [by bx][4] links of the hops +x, -x, +y, -y
+    const int cX = Lx / bx, cs = blockIdx.x;
+    const int X = cs % cX, Y = cs / cX;
+    const int V2 = Lx * Ly;
+    auto site_at = [&](int px, int py) {
+        int x = X * bx + px, y = Y * by + py;
+        x = x < 0 ? Lx - 1 : (x == Lx ? 0 : x);
+        y = y < 0 ? Ly - 1 : (y == Ly ? 0 : y);
+        return y * Lx + x;
+    };
+    for (int t = threadIdx.x; t < W * (by + 2) * n; t += kBlock) {
+        const int k = t % n, l = t / n;
+        const int px = l % W - 1, py = l / W - 1;
+        if ((px < 0 || px == bx) && (py < 0 || py == by)) continue;   // (corners are not read)
+        sv[t] = V[(size_t)site_at(px, py) * n + k];
+    }
+    for (int t = threadIdx.x; t < 4 * bx * by; t += kBlock) {
+        const int h = t & 3, l = t >> 2, px = l % bx, py = l / bx;
+        const int site = site_at(px, py);
+        su[t] = h == 0 ? U[site] : (h == 1 ? conj(U[site_at(px - 1, py)])
+                                           : (h == 2 ? U[V2 + site] : conj(U[V2 + site_at(px, py - 1)])));
+    }
+    __syncthreads();
+    for (int t = threadIdx.x; t < n * q4; t += kBlock) {
+        const int a0 = t % q4, b = t / q4;
+        const int cb = b / nvec;
+        cpx<double> acc[5][4];
+#pragma unroll
+        for (int d = 0; d < 5; ++d)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[d][j] = {0.0, 0.0};
+        for (int l = 0; l < bx * by; ++l) {
+            const int lx = l % bx, ly = l / bx;
+            const cpx<double>* own = sv + (size_t)((ly + 1) * W + lx + 1) * n;
+            cpx<double> va[4];   // rows a0 + j n/4: j = 0, 1 chirality +, j = 2, 3 chirality -
+#pragma unroll
+            for (int j = 0; j < 4; ++j) va[j] = own[a0 + j * q4];
+            {
+                const cpx<double> vb = own[b];   // site-diagonal term d * 1 of D_W(0)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if ((j >> 1) == cb) {
+                        const cpx<double> p = cjmul(va[j], vb);
+                        acc[0][j].re += 2.0 * p.re;
+                        acc[0][j].im += 2.0 * p.im;
+                    }
+            }
+#pragma unroll
+            for (int h = 1; h <= 4; ++h) {
+                const int o = h == 1 ? 1 : (h == 2 ? -1 : (h == 3 ? W : -W));
+                const cpx<double> hv = cmul(su[l * 4 + h - 1], own[(long long)o * n + b]);
+                const cpx<double> h0 = cb == 0 ? hv : cmul(hop_spin(h, 0, 1), hv);
+                const cpx<double> h1 = cb == 1 ? hv : cmul(hop_spin(h, 1, 0), hv);
+                const bool leaves = hop_leaves(lx, ly, bx, by, h);   // the same for the whole workgroup
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const cpx<double> p = cjmul(va[j], (j >> 1) ? h1 : h0);
+                    if (leaves) {
+                        acc[h][j].re -= 0.5 * p.re;
+                        acc[h][j].im -= 0.5 * p.im;
+                    } else {
+                        acc[0][j].re -= 0.5 * p.re;
+                        acc[0][j].im -= 0.5 * p.im;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < 5; ++d)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) links[(((size_t)cs * 5 + d) * n + b) * n + a0 + j * q4] = acc[d][j];
+    }
+}
+
+// the same with a thread per entry, for aggregates whose vectors do not fit 64 KB of LDS
+__global__ void k_galerkin_fine_large(const cpx<double>* U, const cpx<double>* V, cpx<double>* links,
+                                      int Lx, int Ly, int nvec, int bx, int by) {
     const int n = 2 * nvec;
     const int cX = Lx / bx, cY = Ly / by;
     const long long total = (long long)cX * cY * 5 * n * n;
@@ -204,8 +292,15 @@ __global__ void k_galerkin_fine(const cpx<double>* U, const cpx<double>* V, cpx<
 hipError_t galerkin_fine(const cpx<double>* U, const cpx<double>* V, cpx<double>* links,
                          int Lx, int Ly, int nvec, int bx, int by, hipStream_t st) {
     const int n = 2 * nvec;
+    const size_t shm = ((size_t)(bx + 2) * (by + 2) * n + (size_t)4 * bx * by) * sizeof(cpx<double>);
+    if (n % 4 == 0 && shm <= 64 * 1024) {
+        hipLaunchKernelGGL(k_galerkin_fine, dim3((Lx / bx) * (Ly / by)), dim3(kBlock), shm, st, U, V, links, Lx, Ly, nvec,
+                           bx, by);
+        return hipGetLastError();
+    }
     const long long total = (long long)(Lx / bx) * (Ly / by) * 5 * n * n;
-    hipLaunchKernelGGL(k_galerkin_fine, dim3(grid_for(total)), dim3(kBlock), 0, st, U, V, links, Lx, Ly, nvec, bx, by);
+    hipLaunchKernelGGL(k_galerkin_fine_large, dim3(grid_for(total)), dim3(kBlock), 0, st, U, V, links, Lx, Ly, nvec, bx,
+                       by);
     return hipGetLastError();
 }
 
