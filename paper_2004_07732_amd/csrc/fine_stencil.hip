@@ -845,26 +845,41 @@ bool fine_a_chosen(int prec_bytes, int Lx, int Ly, int Ls, int ncol, int* shape,
     return true;
 }
 
-// ------------------------------------------------------------ null-vector relaxation, one CG iteration
-// CG on B v = 0, B = D_W D_W^dag, for a block of 2-d vectors, three launches an iteration:
-//   1: t = D_W^dag p, partial sums of |t|^2
+// ------------------------------------------------------------ null-vector relaxation
+// CG on B v = 0, B = D_W D_W^dag, for a block of 2-d vectors, two launches an iteration:
+//   1: beta = |r|^2 / zz;  x += alpha p, p' = r + beta p, t = D_W^dag p', partial sums of |t|^2
 //   2: alpha = zz / |t|^2;  r -= alpha D_W t, partial sums of |r|^2   (D_W t is never stored)
-//   3: beta = |r|^2 / zz;  x += alpha p, p = r + beta p
-// HBM / Infinity Cache bound: 10 vector passes (read 6, written 4) where separate stencils,
-// norms, finalisers and updates took 15 in eight launches (256^2, 16 vectors: 108 us an
-// iteration before, see the figure at wilson_cg).  Every workgroup adds the partial sums itself,
-// in the same order, so no finaliser stands between the launches; the column's state is read
-// from one buffer and written to the other by the column's first workgroup.  Two columns a thread
-// share the links.
+// (the first iteration of a group starts with p as it is, and the group ends with a launch for
+// the last x and p).  HBM / Infinity Cache bound: 9 vector passes (5 read, 4 written) an iteration
+// where separate stencils, norms, finalisers and updates took 15 in eight launches.  Every workgroup
+// adds the partial sums itself, in the same order, behind its own loads, so no finaliser stands
+// between the launches; the column's state is read from one buffer and written to the other by
+// the column's first workgroup, and p' goes to a second buffer since neighbours still read p.
 __device__ __forceinline__ double wave_add(double x) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
     return x;
 }
-// sum of nb partials by one workgroup of kBlock threads (the same value in every thread)
-__device__ __forceinline__ double block_total(const double* part, int nb, double* sh) {
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nb; b += kBlock) s += part[b];
+// this thread's share of nb <= kCgBlocks partials (loads that wait for nothing), and their total
+// over the workgroup (the same in every thread)
+constexpr int kCgBlocks = 1024;
+struct PartialShare { double v[kCgBlocks / kBlock]; };
+__device__ __forceinline__ PartialShare partial_share(const double* part, int nb) {
+    PartialShare s;
+#pragma unroll
+    for (int k = 0; k < kCgBlocks / kBlock; ++k) {
+        const int b = (int)threadIdx.x + k * kBlock;
+        s.v[k] = b < nb ? part[b] : 0.0;
+    }
+    return s;
+}
+__device__ __forceinline__ double share_sum(const PartialShare& s) {
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < kCgBlocks / kBlock; ++k) t += s.v[k];
+    return t;
+}
+__device__ __forceinline__ double block_total(double s, double* sh) {
     s = wave_add(s);
     if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
     __syncthreads();
@@ -873,86 +888,121 @@ __device__ __forceinline__ double block_total(const double* part, int nb, double
     return s;
 }
 __device__ __forceinline__ bool is_finite(double x) { return !(isnan(x) || isinf(x)); }
+// the state after |r|^2 is known: the stop rule of cg_beta
+__device__ __forceinline__ void cg_state_beta(double& zz, double& beta, int& done, int& iters, double zz0, double tol2,
+                                              double znew, int maxit) {
+    iters += 1;
+    if (!is_finite(znew)) {
+        done = 4;
+    } else {
+        beta = znew / zz;
+        zz = znew;
+        if (znew <= tol2 * zz0) done = 1;
+        else if (iters >= maxit) done = 3;
+    }
+}
+__device__ __forceinline__ spinor<double> axpy_spinor(double a, const spinor<double>& x, const spinor<double>& y) {
+    spinor<double> r;
+    r.c0 = {y.c0.re + a * x.c0.re, y.c0.im + a * x.c0.im};
+    r.c1 = {y.c1.re + a * x.c1.re, y.c1.im + a * x.c1.im};
+    return r;
+}
 
-template <int STEP, int CPT>
+// STEP 0: t = D_W^dag p;  1: the fused first half;  2: the second half (in = t, out = r)
+template <int STEP>
 __global__ void __launch_bounds__(kBlock)
 wilson_cg_kernel(const cpx<double>* __restrict__ U, const spinor<double>* __restrict__ in, spinor<double>* __restrict__ out,
-                 int Lx, int Ly, int ncol, int nb, double diag, const CgScal* __restrict__ sin, CgScal* __restrict__ sout,
-                 const double* __restrict__ pin, double* __restrict__ pout, size_t pstride) {
-    constexpr bool DAG = STEP == 1;
-    __shared__ double sh[4], red[CPT][4];
+                 const spinor<double>* __restrict__ r, spinor<double>* __restrict__ pn, spinor<double>* __restrict__ xv,
+                 int Lx, int Ly, int ncol, int nb, double diag, int maxit, const CgScal* __restrict__ sin,
+                 CgScal* __restrict__ sout, const double* __restrict__ pin, double* __restrict__ pout, size_t pstride) {
+    constexpr bool DAG = STEP != 2;
+    __shared__ double sh[4];
     const int V = Lx * Ly;
-    const int ngrp = (ncol + CPT - 1) / CPT;
-    const unsigned lb = xcd_block(blockIdx.x, gridDim.x);   // column groups of one site block side by side
-    const int c0 = (int)(lb % (unsigned)ngrp) * CPT, sb = (int)(lb / (unsigned)ngrp);
-    bool live[CPT];
-    double alpha[CPT];
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) {
-        const int c = min(c0 + j, ncol - 1);
-        CgScal s = sin[c];
-        live[j] = c0 + j < ncol && s.done == 0;
-        alpha[j] = 0.0;
-        if (STEP == 2 && c0 + j < ncol) {   // (the same for the whole workgroup)
-            if (live[j]) {
-                const double ww = block_total(pin + (size_t)c * pstride, nb, sh);
-                if (!(ww > 0.0) || !is_finite(ww)) {
-                    s.done = is_finite(ww) ? 2 : 4;   // breakdown / non-finite
-                    s.alpha = 0.0;
-                    live[j] = false;
-                } else {
-                    s.alpha = s.zz / ww;
-                }
-                alpha[j] = s.alpha;
-            }
-            if (sb == 0 && threadIdx.x == 0) sout[c] = s;
-        }
-    }
-    double acc[CPT];
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) acc[j] = 0.0;
-    for (int tile = sb; tile * kBlock < V; tile += nb) {
-        const int site = tile * kBlock + (int)threadIdx.x;
-        if (site >= V) continue;
+    const unsigned lb = xcd_block(blockIdx.x, gridDim.x);   // the columns of one site block side by side (its links)
+    const int col = (int)(lb % (unsigned)ncol), sb = (int)(lb / (unsigned)ncol);
+    // the state, the partials and the first tile's fields are loaded together: a stopped column
+    // reads them in vain, but a live one waits for one round trip instead of three (vector loads:
+    // an offset the compiler cannot see is zero)
+    int zoff;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(zoff));
+    double zz = sin[col + zoff].zz, zz0 = sin[col + zoff].zz0, alpha = sin[col + zoff].alpha,
+           beta = sin[col + zoff].beta, tol2 = sin[col + zoff].tol2;
+    int done = sin[col + zoff].done, iters = sin[col + zoff].iters;
+    PartialShare share{};
+    if (STEP != 0) share = partial_share(pin + (size_t)col * pstride, nb);
+    const size_t o = (size_t)col * V;
+    const spinor<double>* src = in + o;
+    double acc = 0.0;
+    bool first = true, more = true;   // (the same for the whole workgroup)
+    for (int tile = sb; tile * kBlock < V; tile += nb) {   // (the same count for the whole workgroup)
+        const int site0 = tile * kBlock + (int)threadIdx.x;
+        const bool on = site0 < V;
+        const int site = on ? site0 : 0;
         const int x = site % Lx, y = site / Lx;
         const int xp = (x + 1 == Lx) ? 0 : x + 1, xm = (x == 0) ? Lx - 1 : x - 1;
         const int yp = (y + 1 == Ly) ? 0 : y + 1, ym = (y == 0) ? Ly - 1 : y - 1;
-        const int sxp = y * Lx + xp, sxm = y * Lx + xm, syp = yp * Lx + x, sym = ym * Lx + x;
-        const cpx<double> hu0 = 0.5 * U[site], hu0m = 0.5 * U[sxm];
-        const cpx<double> hu1 = 0.5 * U[V + site], hu1m = 0.5 * U[V + sym];
+        const int nbr[5] = {site, y * Lx + xp, y * Lx + xm, yp * Lx + x, ym * Lx + x};
+        spinor<double> f[5], g[5], xo = {}, ro = {};
 #pragma unroll
-        for (int j = 0; j < CPT; ++j) {
-            if (!live[j]) continue;
-            const spinor<double>* src = in + (size_t)(c0 + j) * V;
-            const spinor<double> cur = src[site], fx = src[sxp], bx = src[sxm], fy = src[syp], by = src[sym];
-            spinor<double>* dst = out + (size_t)(c0 + j) * V + site;
-            spinor<double> o;
-            if (STEP == 2) o = *dst;
-            cpx<double> a0 = {0.0, 0.0}, a1 = {0.0, 0.0};
-            wilson_hops<double, DAG>(fx, bx, fy, by, hu0, hu0m, hu1, hu1m, a0, a1);
-            spinor<double> w;
-            w.c0 = diag * cur.c0 - a0;
-            w.c1 = diag * cur.c1 - a1;
-            if (STEP == 2) {
-                w.c0 = {o.c0.re - alpha[j] * w.c0.re, o.c0.im - alpha[j] * w.c0.im};
-                w.c1 = {o.c1.re - alpha[j] * w.c1.re, o.c1.im - alpha[j] * w.c1.im};
+        for (int e = 0; e < 5; ++e) f[e] = src[nbr[e]];
+        if (STEP == 1) {
+#pragma unroll
+            for (int e = 0; e < 5; ++e) g[e] = r[o + nbr[e]];
+            xo = xv[o + site];
+        }
+        if (STEP == 2) ro = out[o + site];
+        const cpx<double> hu0 = 0.5 * U[site], hu0m = 0.5 * U[nbr[2]];
+        const cpx<double> hu1 = 0.5 * U[V + site], hu1m = 0.5 * U[V + nbr[4]];
+        if (first) {
+            __builtin_amdgcn_sched_barrier(0);   // (the loads stay above)
+            first = false;
+            const bool live = done == 0;
+            if (STEP != 0) {
+                const double tot = block_total(share_sum(share), sh);
+                if (live) {
+                    if (STEP == 1) {
+                        cg_state_beta(zz, beta, done, iters, zz0, tol2, tot, maxit);
+                    } else if (!(tot > 0.0) || !is_finite(tot)) {
+                        done = is_finite(tot) ? 2 : 4;   // breakdown / non-finite
+                        alpha = 0.0;
+                    } else {
+                        alpha = zz / tot;
+                    }
+                }
+                if (sb == 0 && threadIdx.x == 0) {
+                    CgScal w;
+                    w.zz = zz; w.zz0 = zz0; w.alpha = alpha; w.beta = beta; w.tol2 = tol2; w.done = done; w.iters = iters;
+                    sout[col] = w;
+                }
             }
-            *dst = w;
-            acc[j] += w.c0.re * w.c0.re + w.c0.im * w.c0.im + w.c1.re * w.c1.re + w.c1.im * w.c1.im;
+            if (!live) return;
+            more = done == 0;
+        }
+        if (STEP == 1) {
+            if (on) xv[o + site] = axpy_spinor(alpha, f[0], xo);
+            if (!more) continue;
+#pragma unroll
+            for (int e = 0; e < 5; ++e) f[e] = axpy_spinor(beta, f[e], g[e]);
+            if (on) pn[o + site] = f[0];
+        }
+        if (STEP == 2 && !more) return;   // (no product: r stays)
+        cpx<double> a0 = {0.0, 0.0}, a1 = {0.0, 0.0};
+        wilson_hops<double, DAG>(f[1], f[2], f[3], f[4], hu0, hu0m, hu1, hu1m, a0, a1);
+        spinor<double> w;
+        w.c0 = diag * f[0].c0 - a0;
+        w.c1 = diag * f[0].c1 - a1;
+        if (STEP == 2) w = axpy_spinor(-alpha, w, ro);
+        if (on) {
+            out[o + site] = w;
+            acc += w.c0.re * w.c0.re + w.c0.im * w.c0.im + w.c1.re * w.c1.re + w.c1.im * w.c1.im;
         }
     }
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) {
-        const double s = wave_add(acc[j]);
-        if ((threadIdx.x & 63) == 0) red[j][threadIdx.x >> 6] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x < CPT && c0 + (int)threadIdx.x < ncol)
-        pout[(size_t)(c0 + threadIdx.x) * pstride + sb] =
-            red[threadIdx.x][0] + red[threadIdx.x][1] + red[threadIdx.x][2] + red[threadIdx.x][3];
+    if (!more) return;
+    const double tot = block_total(acc, sh);
+    if (threadIdx.x == 0) pout[(size_t)col * pstride + sb] = tot;
 }
 
-// step 3; the stop rule is that of cg_beta
+// the end of a group: x += alpha p, p = r + beta p
 __global__ void __launch_bounds__(kBlock)
 wilson_cg_update(spinor<double>* __restrict__ x, spinor<double>* __restrict__ p, const spinor<double>* __restrict__ r,
                  int V, int nb, int maxit, const CgScal* __restrict__ sin, CgScal* __restrict__ sout,
@@ -961,56 +1011,47 @@ wilson_cg_update(spinor<double>* __restrict__ x, spinor<double>* __restrict__ p,
     const int col = blockIdx.y;
     CgScal s = sin[col];
     const bool live = s.done == 0;
-    if (live) {
-        const double znew = block_total(pin + (size_t)col * pstride, nb, sh);
-        s.iters += 1;
-        if (!is_finite(znew)) {
-            s.done = 4;
-        } else {
-            s.beta = znew / s.zz;
-            s.zz = znew;
-            if (znew <= s.tol2 * s.zz0) s.done = 1;
-            else if (s.iters >= maxit) s.done = 3;
-        }
-    }
+    if (live)
+        cg_state_beta(s.zz, s.beta, s.done, s.iters, s.zz0, s.tol2,
+                      block_total(share_sum(partial_share(pin + (size_t)col * pstride, nb)), sh), maxit);
     if (blockIdx.x == 0 && threadIdx.x == 0) sout[col] = s;
     if (!live) return;
-    const double al = s.alpha, be = s.beta;
-    const bool more = s.done == 0;
     const size_t o = (size_t)col * V;
     for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < (size_t)V; i += (size_t)gridDim.x * kBlock) {
-        const spinor<double> pi = p[o + i], ri = r[o + i];
-        spinor<double> xi = x[o + i];
-        xi.c0 = {xi.c0.re + al * pi.c0.re, xi.c0.im + al * pi.c0.im};
-        xi.c1 = {xi.c1.re + al * pi.c1.re, xi.c1.im + al * pi.c1.im};
-        x[o + i] = xi;
-        if (more) {
-            spinor<double> pn;
-            pn.c0 = {ri.c0.re + be * pi.c0.re, ri.c0.im + be * pi.c0.im};
-            pn.c1 = {ri.c1.re + be * pi.c1.re, ri.c1.im + be * pi.c1.im};
-            p[o + i] = pn;
-        }
+        const spinor<double> pi = p[o + i];
+        x[o + i] = axpy_spinor(s.alpha, pi, x[o + i]);
+        if (s.done == 0) p[o + i] = axpy_spinor(s.beta, pi, r[o + i]);
     }
 }
 
-hipError_t wilson_cg(const cpx<double>* U, cpx<double>* x, cpx<double>* r, cpx<double>* p, cpx<double>* t, int Lx, int Ly,
-                     int ncol, double M, int maxit, CgScal* s, CgScal* s2, const RedWork& rw, hipStream_t st) {
+hipError_t wilson_cg(const cpx<double>* U, cpx<double>* x, cpx<double>* r, cpx<double>** p, cpx<double>** q, cpx<double>* t,
+                     int Lx, int Ly, int ncol, double M, int iters, int maxit, CgScal* s, CgScal* s2, const RedWork& rw,
+                     hipStream_t st) {
     const int V = Lx * Ly;
     // (a workgroup adds nb partials: larger lattices give a workgroup several site tiles)
-    const int nb = std::min((V + kBlock - 1) / kBlock, 1024);
-    if (rw.max_q < 2 || nb > rw.nblk || ncol > rw.max_cols) return hipErrorInvalidValue;
+    const int nb = std::min((V + kBlock - 1) / kBlock, kCgBlocks);
+    const long long blocks = (long long)nb * ncol;
+    if (rw.max_q < 2 || nb > rw.nblk || ncol > rw.max_cols || blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t pstride = (size_t)rw.max_q * rw.nblk;
     double* pa = rw.partial;
     double* pb = rw.partial + rw.nblk;
     auto S = [](cpx<double>* v) { return reinterpret_cast<spinor<double>*>(v); };
-    const long long blocks = (long long)nb * ((ncol + 1) / 2);
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((wilson_cg_kernel<1, 2>), dim3((unsigned)blocks), dim3(kBlock), 0, st, U, S(p), S(t), Lx, Ly, ncol,
-                       nb, 2.0 + M, s, s, (const double*)nullptr, pa, pstride);
-    hipLaunchKernelGGL((wilson_cg_kernel<2, 2>), dim3((unsigned)blocks), dim3(kBlock), 0, st, U, S(t), S(r), Lx, Ly, ncol,
-                       nb, 2.0 + M, s, s2, pa, pb, pstride);
-    hipLaunchKernelGGL(wilson_cg_update, dim3((unsigned)std::min(nb, 256), ncol), dim3(kBlock), 0, st, S(x), S(p), S(r), V,
-                       nb, maxit, s2, s, pb, pstride);
+    const double diag = 2.0 + M;
+    const dim3 grid((unsigned)blocks), block(kBlock);
+    for (int i = 0; i < iters; ++i) {
+        if (i == 0) {
+            hipLaunchKernelGGL((wilson_cg_kernel<0>), grid, block, 0, st, U, S(*p), S(t), S(r), S(*q), S(x), Lx, Ly, ncol, nb,
+                               diag, maxit, s, s, pb, pa, pstride);
+        } else {   // p' into q
+            hipLaunchKernelGGL((wilson_cg_kernel<1>), grid, block, 0, st, U, S(*p), S(t), S(r), S(*q), S(x), Lx, Ly, ncol, nb,
+                               diag, maxit, s2, s, pb, pa, pstride);
+            std::swap(*p, *q);
+        }
+        hipLaunchKernelGGL((wilson_cg_kernel<2>), grid, block, 0, st, U, S(t), S(r), S(r), S(*q), S(x), Lx, Ly, ncol, nb, diag,
+                           maxit, s, s2, pa, pb, pstride);
+    }
+    hipLaunchKernelGGL(wilson_cg_update, dim3((unsigned)std::min(nb, 256), ncol), block, 0, st, S(x), S(*p), S(r), V, nb,
+                       maxit, s2, s, pb, pstride);
     return hipGetLastError();
 }
 

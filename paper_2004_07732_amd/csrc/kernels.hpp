@@ -72,11 +72,13 @@ template <typename R>
 hipError_t wilson2d(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, int Lx, int Ly, int ncol,
                     double M, bool dagger, hipStream_t st);
 
-// one iteration of the null-vector relaxation on the fine level, CG on B x = 0 with
-// B = D_W(M) D_W(M)^dag for ncol 2-d vectors (r, p as CG keeps them, t scratch); the state is read
-// from and returned in s (s2: a second buffer of ncol states; columns that are done are left)
-hipError_t wilson_cg(const cpx<double>* U, cpx<double>* x, cpx<double>* r, cpx<double>* p, cpx<double>* t, int Lx, int Ly,
-                     int ncol, double M, int maxit, CgScal* s, CgScal* s2, const RedWork& rw, hipStream_t st);
+// `iters` iterations of the null-vector relaxation on the fine level, CG on B x = 0 with
+// B = D_W(M) D_W(M)^dag for ncol 2-d vectors: r and *p as CG keeps them (*p and *q, a second
+// buffer, change places on the way), t scratch.  The state is read from and returned in s (s2: a
+// second buffer of ncol states); columns that are done are left.
+hipError_t wilson_cg(const cpx<double>* U, cpx<double>* x, cpx<double>* r, cpx<double>** p, cpx<double>** q, cpx<double>* t,
+                     int Lx, int Ly, int ncol, double M, int iters, int maxit, CgScal* s, CgScal* s2, const RedWork& rw,
+                     hipStream_t st);
 
 // ------------------------------------------------------------ coarse operator
 // Coarse links in "column" layout: per coarse site, five n x n blocks

@@ -784,13 +784,12 @@ int Hierarchy::null_vectors(int l, const cpx<double>* start, cpx<double>* v, hip
     const int maxit = prm.setup_iters;
     for (int it0 = 0; it0 < maxit; it0 += kCgChunk) {
         const int nchunk = std::min(kCgChunk, maxit - it0);
-        for (int c = 0; c < nchunk; ++c) {
-            if (L.fine) {
-                // (the second state buffer lies in the partial sums' unused last quantity)
-                CgScal* s2 = reinterpret_cast<CgScal*>(rw_.partial + (size_t)(rw_.max_q - 1) * rw_.nblk);
-                HIPCHK(wilson_cg(L.U64, v, r, p, t, L.Lx, L.Ly, nv, ms, maxit, s, s2, rw_, st));
-                continue;
-            }
+        if (L.fine) {
+            // (the second state buffer lies in the partial sums' unused last quantity)
+            CgScal* s2 = reinterpret_cast<CgScal*>(rw_.partial + (size_t)(rw_.max_q - 1) * rw_.nblk);
+            HIPCHK(wilson_cg(L.U64, v, r, &p, &q, t, L.Lx, L.Ly, nv, ms, nchunk, maxit, s, s2, rw_, st));
+        }
+        for (int c = 0; c < nchunk && !L.fine; ++c) {
             HIPCHK(apply_wilson<double>(l, p, t, ms, true, nv, st));
             HIPCHK(cg_alpha<double>(t, n, nv, s, rw_, st));
             HIPCHK(apply_wilson<double>(l, t, q, ms, false, nv, st));
