@@ -32,6 +32,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include <type_traits>
@@ -334,6 +335,15 @@ static hipError_t launch_fine(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, co
                               int Ls, int ncol, double m, double M5, bool dagger, const int* skip, int skip_stride,
                               int cfg, hipStream_t st, double alpha = -1.0, double beta = 1.0);
 
+// key of the timed choices: precision, lattice, columns and adjoint flag (the operators are called
+// on small lattices too, where building a text key per call shows; DWF_TUNE_CACHE holds text)
+struct TuneKey {
+    int prec, Lx, Ly, Ls, ncol, dag;
+    bool operator<(const TuneKey& o) const {
+        return std::tie(prec, Lx, Ly, Ls, ncol, dag) < std::tie(o.prec, o.Lx, o.Ly, o.Ls, o.ncol, o.dag);
+    }
+};
+
 // Launch configuration of the fine stencil (kernel shape and chunk length),
 // chosen by timing the candidates once per lattice shape, column count,
 // precision and adjoint flag (DWF_AUTOTUNE=0 disables it); the choices persist
@@ -342,22 +352,21 @@ template <typename R>
 static int tuned_cfg(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, int Lx, int Ly, int Ls, int ncol,
                      double m, double M5, bool dagger, hipStream_t st, bool may_time = true) {
     static std::mutex mu;
-    static std::map<std::string, int> cache;
+    static std::map<TuneKey, int> cache;
     static bool loaded = false;
     const int heuristic = pick_cfg(Lx, Ly, Ls, ncol);
     const char* en = std::getenv("DWF_AUTOTUNE");
     if (en && en[0] == '0') return heuristic;
-    char keyb[128];
-    std::snprintf(keyb, sizeof keyb, "fine_dw2/%zu/%d/%d/%d/%d/%d", sizeof(R), Lx, Ly, Ls, ncol, dagger ? 1 : 0);
-    const std::string key(keyb);
+    const TuneKey key{(int)sizeof(R), Lx, Ly, Ls, ncol, dagger ? 1 : 0};
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        auto it = cache.find(key);
+        if (it != cache.end()) return it->second;
+    }
     // inside a graph capture, or for a caller that must not synchronise: use a
     // choice already made, never time
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (!may_time || hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-        std::lock_guard<std::mutex> lk(mu);
-        auto it = cache.find(key);
-        return it != cache.end() ? it->second : heuristic;
-    }
+    if (!may_time || hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return heuristic;
     // the timing runs synchronise: keep them apart from captures on other threads
     std::lock_guard<std::recursive_mutex> rlk(runtime_mutex());
     std::lock_guard<std::mutex> lk(mu);
@@ -368,7 +377,11 @@ static int tuned_cfg(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, int Lx, int
             std::ifstream f(path);
             std::string k;
             int v;
-            while (f >> k >> v) cache[k] = v;
+            while (f >> k >> v) {
+                TuneKey t{};
+                if (std::sscanf(k.c_str(), "fine_dw2/%d/%d/%d/%d/%d/%d", &t.prec, &t.Lx, &t.Ly, &t.Ls, &t.ncol, &t.dag) == 6)
+                    cache[t] = v;
+            }
         }
     }
     auto it = cache.find(key);
@@ -411,7 +424,8 @@ static int tuned_cfg(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, int Lx, int
     cache[key] = best;
     if (path) {
         std::ofstream f(path, std::ios::app);
-        f << key << " " << best << "\n";
+        f << "fine_dw2/" << key.prec << "/" << Lx << "/" << Ly << "/" << Ls << "/" << ncol << "/" << key.dag << " " << best
+          << "\n";
     }
     return best;
 }

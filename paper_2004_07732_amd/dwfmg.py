@@ -254,9 +254,12 @@ class SolveStats:
     escalations: int = 0
 
 
-def _stream(stream=None) -> ctypes.c_void_p:
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+def _stream(stream=None) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    # the current device's current stream as a plain integer (building a Stream object for it
+    # costs as much as the rest of a small call's checks)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
@@ -293,17 +296,38 @@ def _fine_dims(U: torch.Tensor, psi: torch.Tensor):
     return Lx, Ly, psi.shape[1], psi.shape[0]
 
 
-# ----------------------------------------------------------------------------- operators
-def dwf_apply(U, psi, m_f, M5, dagger=False, out=None, stream=None):
-    """out = D_DW(m_f) psi (or its adjoint); U [2,Ly,Lx], psi [nrhs,Ls,Ly,Lx,2] (or without nrhs)."""
+def _fine_args(U, psi, out):
+    """Checked arguments of the fine operators: (out, Lx, Ly, Ls, nrhs, precision flag).  Well-formed
+    calls take the first branch, which reads each attribute once (the small operators are bound by
+    this); anything else goes through the named checks, which raise."""
+    if isinstance(U, torch.Tensor) and isinstance(psi, torch.Tensor):
+        dt = psi.dtype
+        us, ps = U.shape, psi.shape
+        if (U.is_cuda and psi.is_cuda and U.dtype == dt and (dt == torch.complex64 or dt == torch.complex128)
+                and U.is_contiguous() and psi.is_contiguous() and len(us) == 3 and len(ps) in (4, 5)
+                and us[0] == 2 and us[1] == ps[-3] and us[2] == ps[-2] and ps[-1] == 2):
+            if out is None:
+                out = torch.empty_like(psi)
+            else:
+                _need(out, "out", dt, ps)
+            return (out, us[2], us[1], ps[-4], ps[0] if len(ps) == 5 else 1,
+                    DWF_PREC_F32 if dt == torch.complex64 else 0)
     _need(U, "U", psi.dtype)
     _need(psi, "psi")
     Lx, Ly, Ls, nrhs = _fine_dims(U, psi)
     out = torch.empty_like(psi) if out is None else out
     _need(out, "out", psi.dtype, psi.shape)
-    flags = _prec(psi) | (DWF_DAGGER if dagger else 0)
-    _check(lib().dwf_apply(_ptr(U), _ptr(psi), _ptr(out), Lx, Ly, Ls, nrhs, float(m_f), float(M5), flags,
-                           _stream(stream)), "dwf_apply")
+    return out, Lx, Ly, Ls, nrhs, _prec(psi)
+
+
+# ----------------------------------------------------------------------------- operators
+def dwf_apply(U, psi, m_f, M5, dagger=False, out=None, stream=None):
+    """out = D_DW(m_f) psi (or its adjoint); U [2,Ly,Lx], psi [nrhs,Ls,Ly,Lx,2] (or without nrhs)."""
+    out, Lx, Ly, Ls, nrhs, flags = _fine_args(U, psi, out)
+    code = (_lib or lib()).dwf_apply(U.data_ptr(), psi.data_ptr(), out.data_ptr(), Lx, Ly, Ls, nrhs, float(m_f), float(M5),
+                                     flags | DWF_DAGGER if dagger else flags, _stream(stream))
+    if code != DWF_OK:
+        _check(code, "dwf_apply")
     return out
 
 
@@ -352,13 +376,11 @@ def dwf_fine_a_chosen(Lx, Ly, Ls, nrhs, f32=True):
 def dwf_pv_apply(U, psi, m_f, M5, mode=DWF_PVDAG_DW, out=None, stream=None):
     """Pauli-Villars forms: DWF_PV, DWF_PV_DAG, DWF_PVDAG_DW (A), DWF_PVDAG_DW_DAG (A^dagger),
     DWF_PVINV_DW (D_PV^-1 D_DW by an inner CGNR solve to 1e-12, complex128 only)."""
-    _need(U, "U", psi.dtype)
-    _need(psi, "psi")
-    Lx, Ly, Ls, nrhs = _fine_dims(U, psi)
-    out = torch.empty_like(psi) if out is None else out
-    _need(out, "out", psi.dtype, psi.shape)
-    _check(lib().dwf_pv_apply(_ptr(U), _ptr(psi), _ptr(out), Lx, Ly, Ls, nrhs, float(m_f), float(M5), int(mode),
-                              _prec(psi), _stream(stream)), "dwf_pv_apply")
+    out, Lx, Ly, Ls, nrhs, flags = _fine_args(U, psi, out)
+    code = (_lib or lib()).dwf_pv_apply(U.data_ptr(), psi.data_ptr(), out.data_ptr(), Lx, Ly, Ls, nrhs, float(m_f), float(M5),
+                                        int(mode), flags, _stream(stream))
+    if code != DWF_OK:
+        _check(code, "dwf_pv_apply")
     return out
 
 
