@@ -118,18 +118,18 @@ int dwf_fine_config(int shape, int chunk);
  * (each with its dwf_fine_config choice) through an intermediate field; the fused
  * shapes apply both in one launch over LDS tiles of the given size, evaluating the
  * intermediate on every tile and its one-site ring and never storing it (the
- * lattice must divide into the tiles; FP64 fields only with DWF_FINE_A_16x8, whose
- * LDS fits).  Both forms evaluate every site with the same arithmetic, to rounding
+ * lattice must divide into the tiles; a pinned FP64 shape is DWF_FINE_A_16x8).  Both forms evaluate every site with the same arithmetic, to rounding
  * (FMA contraction may differ between the kernels).  By default (DWF_FINE_A_AUTO)
  * the library times the candidates once per lattice shape, column count and
- * precision and keeps the fused launch only when it is more than 3% faster.
+ * precision, starting from a rule on the sizes (the fused launch wherever a tile divides
+ * the lattice) and keeping it unless another is more than 3% faster.
  * dwf_fine_a_config pins a choice for later calls (chunk = output slices per
  * workgroup, 1..4095, capped at Ls; ignored for DWF_FINE_A_TWO and
  * DWF_FINE_A_AUTO); a pinned fused shape that does not fit a lattice falls back to
  * the automatic choice there.  Returns DWF_EINVAL for an unknown shape or a chunk
  * out of range.  dwf_fine_a_chosen reports the automatic choice made for a shape
- * (prec: 0 FP64, DWF_PREC_F32 FP32): DWF_OK with *shape and *chunk, or
- * DWF_EINVAL if none was made yet. */
+ * (prec: 0 FP64, DWF_PREC_F32 FP32): DWF_OK with *shape and *chunk (shape 4: tiles of
+ * 32 x 16, which only the automatic choice takes), or DWF_EINVAL if none was made yet. */
 #define DWF_FINE_A_AUTO   -1
 #define DWF_FINE_A_TWO     0   /* two stencil launches through an intermediate field  */
 #define DWF_FINE_A_16x16   1   /* one fused launch, LDS tiles of 16 x 16 sites        */
@@ -139,9 +139,10 @@ int dwf_fine_a_config(int shape, int chunk);
 int dwf_fine_a_chosen(int prec, int Lx, int Ly, int Ls, int nrhs, int* shape, int* chunk);
 
 /* Pauli-Villars forms (Sec. 2.2, eq. NormalExp): see the DWF_PV* modes.  The
- * product modes use a library-owned intermediate field (allocated on first use
- * and kept until dwf_release_scratch; a call on one stream waits, on the
- * device, for the previous call's use of it on another).  Same layout rules as
+ * product modes are one launch where a tile of 32 x 16, 32 x 8, 16 x 16 or 16 x 8 sites
+ * divides the lattice and Ls >= 2; elsewhere they use a library-owned intermediate field
+ * (allocated on first use and kept until dwf_release_scratch; a call on one stream waits,
+ * on the device, for the previous call's use of it on another).  Same layout rules as
  * dwf_apply.
  * DWF_PVINV_DW (FP64 only; DWF_EUNSUPPORTED with DWF_PREC_F32) applies D_DW(m)
  * and then solves D_PV out = D_DW psi for each right-hand side by CGNR to a

@@ -87,11 +87,13 @@ int pv_apply_t(const void* U, const void* psi, void* out, int Lx, int Ly, int Ls
         case DWF_PV_DAG: return hip_status(fine_dw<R>(u, in, o, nullptr, Lx, Ly, Ls, nrhs, 1.0, M5, true, nullptr, 1, st));
         case DWF_PVDAG_DW:
         case DWF_PVDAG_DW_DAG: {
+            const double m1 = (mode == DWF_PVDAG_DW) ? m : 1.0, m2 = (mode == DWF_PVDAG_DW) ? 1.0 : m;
+            if (fine_product_fits<R>(Lx, Ly, Ls, nrhs))
+                return hip_status(fine_product<R>(u, in, o, Lx, Ly, Ls, nrhs, m1, m2, M5, st));
             std::lock_guard<std::mutex> lk(g_scratch_mu);
             const size_t bytes = sizeof(cpx<R>) * 2 * (size_t)Lx * Ly * Ls * nrhs;
             auto t = reinterpret_cast<cpx<R>*>(acquire(g_fields, bytes, st));
             if (!t) return DWF_EHIP;
-            const double m1 = (mode == DWF_PVDAG_DW) ? m : 1.0, m2 = (mode == DWF_PVDAG_DW) ? 1.0 : m;
             if (fine_dw<R>(u, in, t, nullptr, Lx, Ly, Ls, nrhs, m1, M5, false, nullptr, 1, st) != hipSuccess)
                 return release(g_fields, st, DWF_EHIP);
             return release(g_fields, st,
@@ -129,6 +131,9 @@ int pv_poly_apply_t(const void* U, const void* psi, void* out, int Lx, int Ly, i
     auto in = reinterpret_cast<const cpx<R>*>(psi);
     auto o = reinterpret_cast<cpx<R>*>(out);
     const size_t n = (size_t)2 * Lx * Ly * Ls * nrhs;
+    // p = 1: the product itself, as dwf_pv_apply applies it
+    if (order == 0 && c[0] == 1.0 && fine_product_fits<R>(Lx, Ly, Ls, nrhs))
+        return hip_status(fine_product<R>(u, in, o, Lx, Ly, Ls, nrhs, dag ? 1.0 : m, dag ? m : 1.0, M5, st));
     std::lock_guard<std::mutex> lk(g_scratch_mu);
     auto t = reinterpret_cast<cpx<R>*>(acquire(g_fields, sizeof(cpx<R>) * 3 * n, st));
     if (!t) return DWF_EHIP;

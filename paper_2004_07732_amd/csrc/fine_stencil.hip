@@ -539,29 +539,31 @@ static hipError_t launch_fine(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, co
 // One launch for both stencils of the fine A (eq. NormalExp): the intermediate
 // t = D_DW(m) psi never goes to memory.  A workgroup owns a TX x TY tile of one column
 // and a chunk [s0, s1) of output slices and walks k = s0-1 .. s1:
-//  - t_k is evaluated on the tile and its one-site ring (each ring site again, from the
-//    LDS box of psi_k with a two-site margin and the boxes of psi_{k-1}, psi_{k+1}) into an
-//    LDS tile, so that D_PV^dag finds all four neighbours of every tile site;
+//  - t_k is evaluated on the tile and its one-site ring into an LDS tile, so that D_PV^dag finds
+//    all four neighbours of every tile site; psi_{k-1}, psi_k, psi_{k+1} of a thread's own site
+//    and of its ring site stay in its registers, and only the spatial neighbours come from an
+//    LDS box of psi_k with a two-site margin;
 //  - out_{k-1} = D_PV^dag t follows from the tile of t_{k-1} and, at the thread's own site,
 //    t_{k-2} (lower chirality, from below) and t_k (upper chirality, from above);
-//  - psi_{k+2}'s box is loaded while t_k is evaluated and written to LDS after it.
-// Four psi boxes and two t tiles rotate, so one barrier per slice suffices: the psi box
-// written at step k was last read at step k-1, the t tile written at step k was last read
-// at step k-1, both before step k-1's barrier.  Every site evaluates the same expressions
-// as the two separate stencil kernels (dw_site), in the same order.
-// Requires Lx % TX == 0 and Ly % TY == 0.
+//  - psi_{k+1} goes to the other box and psi_{k+2} is loaded meanwhile (own site by every thread,
+//    ring sites by the first NRING, the margin's arms and corners by others).
+// Two psi boxes and two t tiles alternate, so one barrier per slice suffices: the box and the
+// tile written at step k were last read at step k-1, before step k-1's barrier.  Every
+// site evaluates the same expressions as the two separate stencil kernels (dw_site), in the same
+// order.  Requires Lx % TX == 0 and Ly % TY == 0.
 template <typename R, int TX, int TY, bool AXPBY, bool NTS>
 __global__ void __launch_bounds__(TX * TY)
 fine_a_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in, spinor<R>* __restrict__ out,
               const spinor<R>* __restrict__ b, const int* __restrict__ skip, int skip_stride, int Lx, int Ly, int Ls,
               int nchunk, int cs, int ntile, R diag, R mdw, R mpv, R alpha, R beta) {
     constexpr int NTH = TX * TY;
-    constexpr int BX = TX + 4, BY = TY + 4;                            // psi box: two-site margin
-    constexpr int EX = TX + 2, EY = TY + 2;                            // t tile: one-site margin
-    constexpr int NBOX = (TX + 2) * (TY + 2) + 2 * TX + 2 * TY;        // psi sites read per slice
-    constexpr int NRING = 2 * TX + 2 * TY;                             // ring sites of t
-    static_assert(NBOX <= 2 * NTH && NRING <= NTH, "two box sites and one ring site per thread at most");
-    __shared__ __attribute__((aligned(16))) spinor<R> pb[4][BY][BX];
+    constexpr int BX = TX + 4, BY = TY + 4;             // psi box: two-site margin
+    constexpr int EX = TX + 2, EY = TY + 2;             // t tile: one-site margin
+    constexpr int NRING = 2 * TX + 2 * TY;              // ring sites of t
+    constexpr int NARM = 2 * TX + 2 * TY + 4;           // the rest of the box: arms at distance two, ring corners
+    constexpr int ARM0 = (NRING + 63) / 64 * 64;        // first thread that loads them
+    static_assert(ARM0 + NARM <= NTH, "one ring site or one margin site per thread");
+    __shared__ __attribute__((aligned(16))) spinor<R> pb[2][BY][BX];
     __shared__ __attribute__((aligned(16))) spinor<R> tb[2][EY][EX];
     typedef typename vec4_of<R>::type vec4;
     const unsigned lb = xcd_block(blockIdx.x, gridDim.x);
@@ -590,91 +592,74 @@ fine_a_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in, sp
     const int site = y * Lx + x;
     cpx<R> hu0, hu0m, hu1, hu1m;
     links(x, y, hu0, hu0m, hu1, hu1m);
-    // this thread's ring site of t (threads tid < NRING): row below, row above, left
-    // column, right column, in tile-local coordinates
-    const bool has_ring = tid < NRING;
-    int rpx = 0, rpy = 0;
-    {
-        const int r = has_ring ? tid : 0;
-        if (r < TX) { rpx = r; rpy = -1; }
-        else if (r < 2 * TX) { rpx = r - TX; rpy = TY; }
-        else if (r < 2 * TX + TY) { rpx = -1; rpy = r - 2 * TX; }
-        else { rpx = TX; rpy = r - 2 * TX - TY; }
+    // this thread's ring site of t (row below, row above, left column, right column) or margin
+    // site (left, right, below, above arm, corners), in tile-local coordinates
+    const bool ring = tid < NRING, arm = tid >= ARM0 && tid < ARM0 + NARM;
+    int px = 0, py = 0;
+    if (ring) {
+        const int r = tid;
+        if (r < TX) { px = r; py = -1; }
+        else if (r < 2 * TX) { px = r - TX; py = TY; }
+        else if (r < 2 * TX + TY) { px = -1; py = r - 2 * TX; }
+        else { px = TX; py = r - 2 * TX - TY; }
+    } else if (arm) {
+        const int r = tid - ARM0;
+        if (r < TY) { px = -2; py = r; }
+        else if (r < 2 * TY) { px = TX + 1; py = r - TY; }
+        else if (r < 2 * TY + TX) { px = r - 2 * TY; py = -2; }
+        else if (r < 2 * TY + 2 * TX) { px = r - 2 * TY - TX; py = TY + 1; }
+        else { px = (r & 1) ? TX : -1; py = (r & 2) ? TY : -1; }
     }
+    static_assert((2 * TX + 2 * TY) % 4 == 0, "the corners' low bits count from zero");
+    const bool extra = ring || arm;
+    const int xsite = wy(y0 + py) * Lx + wx(x0 + px);   // (threads with neither: a tile site, not used)
     cpx<R> ru0 = {}, ru0m = {}, ru1 = {}, ru1m = {};
-    if (has_ring) links(wx(x0 + rpx), wy(y0 + rpy), ru0, ru0m, ru1, ru1m);
-    // this thread's (at most two) psi box sites: the (TX+2) x (TY+2) box, then the four
-    // arms of the two-site margin (left, right, below, above)
-    int gs[2] = {-1, -1}, ls[2] = {0, 0};
-#pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const int i = tid + e * NTH;
-        if (i < NBOX) {
-            int px, py;
-            if (i < (TX + 2) * (TY + 2)) { px = i % (TX + 2) - 1; py = i / (TX + 2) - 1; }
-            else {
-                const int j = i - (TX + 2) * (TY + 2);
-                if (j < TY) { px = -2; py = j; }
-                else if (j < 2 * TY) { px = TX + 1; py = j - TY; }
-                else if (j < 2 * TY + TX) { px = j - 2 * TY; py = -2; }
-                else { px = j - 2 * TY - TX; py = TY + 1; }
-            }
-            gs[e] = wy(y0 + py) * Lx + wx(x0 + px);
-            ls[e] = (py + 2) * BX + (px + 2);
-        }
-    }
+    if (ring) links(wx(x0 + px), wy(y0 + py), ru0, ru0m, ru1, ru1m);
     const size_t colbase = (size_t)col * Ls * V;
     const spinor<R>* src = in + colbase;
     const int s0 = chunk * cs;
     const int s1 = min(s0 + cs, Ls);
     auto slice = [&](int k) { k %= Ls; return k < 0 ? k + Ls : k; };   // walk index -> slice
-    auto buf = [&](int k) -> spinor<R>(*)[BX] { return pb[(k + 8) & 3]; };   // k >= -2
-    auto load_box = [&](int k, vec4 (&a)[2]) {
-        const spinor<R>* sl = src + (size_t)slice(k) * V;
+    auto at = [&](int k, int st) { return load4(src + (size_t)slice(k) * V + st); };
+    // psi_{k-1}, psi_k, psi_{k+1} of the own and of the ring site; of a margin site only psi_{k+1}
+    vec4 own[3], ext[3] = {};
 #pragma unroll
-        for (int e = 0; e < 2; ++e)
-            if (gs[e] >= 0) a[e] = load4(sl + gs[e]);
-    };
-    auto put_box = [&](int k, const vec4 (&a)[2]) {
-        spinor<R>* b = &buf(k)[0][0];
+    for (int e = 0; e < 3; ++e) own[e] = at(s0 - 2 + e, site);
+    if (extra) {
 #pragma unroll
-        for (int e = 0; e < 2; ++e)
-            if (gs[e] >= 0) *reinterpret_cast<vec4*>(b + ls[e]) = a[e];
+        for (int e = 0; e < 3; ++e) ext[e] = at(s0 - 2 + e, xsite);
+    }
+    auto put = [&](int k, const vec4& o, const vec4& r) {
+        spinor<R>(*bf)[BX] = pb[k & 1];
+        *reinterpret_cast<vec4*>(&bf[ly + 2][lx + 2]) = o;
+        if (extra) *reinterpret_cast<vec4*>(&bf[py + 2][px + 2]) = r;
     };
-    // t_k at tile-local (px, py): D_DW(m) from the psi boxes (corner blocks -m at the wrap)
-    auto t_at = [&](int k, int px, int py, cpx<R> h0, cpx<R> h0m, cpx<R> h1, cpx<R> h1m) {
-        const spinor<R>(*c)[BX] = buf(k);
-        const spinor<R>(*pv)[BX] = buf(k - 1);
-        const spinor<R>(*nx)[BX] = buf(k + 1);
-        const int bx = px + 2, by = py + 2;
-        spinor<R> prv = pv[by][bx], nxt = nx[by][bx];
+    put(s0 - 1, own[1], ext[1]);
+    __syncthreads();
+    // t_k at tile-local (tx, ty) from the box of psi_k (corner blocks -m at the wrap)
+    auto t_at = [&](int k, int tx, int ty, const vec4 (&p)[3], cpx<R> h0, cpx<R> h0m, cpx<R> h1, cpx<R> h1m) {
+        const spinor<R>(*c)[BX] = pb[k & 1];
+        spinor<R> prv = unpack4<R>(p[0]), nxt = unpack4<R>(p[2]);
         const int sk = slice(k);
         if (sk == 0) { prv.c0 = mdw * prv.c0; prv.c1 = mdw * prv.c1; }
         if (sk == Ls - 1) { nxt.c0 = mdw * nxt.c0; nxt.c1 = mdw * nxt.c1; }
-        return dw_site<R, false>(c[by][bx + 1], c[by][bx - 1], c[by + 1][bx], c[by - 1][bx], c[by][bx], prv, nxt,
+        const int bx = tx + 2, by = ty + 2;
+        return dw_site<R, false>(c[by][bx + 1], c[by][bx - 1], c[by + 1][bx], c[by - 1][bx], unpack4<R>(p[1]), prv, nxt,
                                  h0, h0m, h1, h1m, diag);
     };
-    {   // the boxes of psi_{s0-2}, psi_{s0-1}, psi_{s0}
-        vec4 a[3][2] = {};
-        load_box(s0 - 2, a[0]);
-        load_box(s0 - 1, a[1]);
-        load_box(s0, a[2]);
-        put_box(s0 - 2, a[0]);
-        put_box(s0 - 1, a[1]);
-        put_box(s0, a[2]);
-    }
-    __syncthreads();
     spinor<R> tp = {}, tc = {}, tn = {};   // t at the own site, walk k-2, k-1, k
     for (int k = s0 - 1; k <= s1; ++k) {   // (the same bounds for the whole workgroup)
-        vec4 a[2] = {};
-        const bool pre = k + 2 <= s1 + 1;
-        if (pre) load_box(k + 2, a);
-        vec4 bv = {};
+        vec4 no = {}, nx = {}, bv = {};
+        if (k < s1) {
+            put(k + 1, own[2], ext[2]);
+            no = at(k + 2, site);
+            if (extra) nx = at(k + 2, xsite);
+        }
         if (AXPBY && k - 1 >= s0) bv = load4(b + colbase + (size_t)(k - 1) * V + site);
-        tn = t_at(k, lx, ly, hu0, hu0m, hu1, hu1m);
+        tn = t_at(k, lx, ly, own, hu0, hu0m, hu1, hu1m);
         spinor<R>(*tw)[EX] = tb[k & 1];
         tw[ly + 1][lx + 1] = tn;
-        if (has_ring && k >= s0 && k < s1) tw[rpy + 1][rpx + 1] = t_at(k, rpx, rpy, ru0, ru0m, ru1, ru1m);
+        if (ring && k >= s0 && k < s1) tw[py + 1][px + 1] = t_at(k, px, py, ext, ru0, ru0m, ru1, ru1m);
         if (k - 1 >= s0) {   // out_{k-1} = D_PV^dag t (corner blocks -1 at the wrap)
             const int so = k - 1;
             const spinor<R>(*q)[EX] = tb[so & 1];
@@ -686,29 +671,61 @@ fine_a_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in, sp
             if (AXPBY) res = axpby(alpha, res, beta, unpack4<R>(bv));
             store_out<NTS>(out + colbase + (size_t)so * V + site, res);
         }
-        if (pre) put_box(k + 2, a);
         tp = tc;
         tc = tn;
+        own[0] = own[1]; own[1] = own[2]; own[2] = no;
+        ext[0] = ext[1]; ext[1] = ext[2]; ext[2] = nx;
         __syncthreads();
     }
 }
 
+// Measured (graph of 20 applications, us; two launches before): FP32 256^2 x 16: 12.5 (15.0), x 4 rhs
+// 26.8 (50.0), x 16 rhs 111 (191); 512^2 x 32 x 4 rhs 234 (377), 4.6 TB/s of 1.08 GB; 64^2 x 16 x
+// 2 rhs 5.7 (6.5); FP64 256^2 x 16 x 4 rhs 70 (127), 128^2 x 16 10.8 (11.5).  Holding the slices in
+// registers instead of four LDS boxes took it from 138 to 83 registers and 50 to 23 KB of LDS (FP32),
+// 146 to 111 us at 256^2 x 16 x 16 rhs.
+
 // Launch configuration of the fine A: 0 = the two stencil launches (each with its own
 // configuration), else fused tile shape * kCfgStride + slice chunk
 struct ATileShape { int tx, ty; };
-static constexpr ATileShape kATiles[] = {{16, 16}, {32, 8}, {16, 8}};
+static constexpr ATileShape kATiles[] = {{16, 16}, {32, 8}, {16, 8}, {32, 16}};
 static constexpr int kNumATiles = (int)(sizeof(kATiles) / sizeof(kATiles[0]));
 
-// the fused kernel's LDS (four psi boxes, two t tiles) must fit one workgroup's 64 KB
+// the fused kernel's LDS (two psi boxes, two t tiles) must fit one workgroup's 64 KB
 template <typename R>
 static constexpr bool a_tile_lds_ok(int tx, int ty) {
-    return (4 * (tx + 4) * (ty + 4) + 2 * (tx + 2) * (ty + 2)) * (int)sizeof(spinor<R>) <= 64 * 1024;
+    return (2 * (tx + 4) * (ty + 4) + 2 * (tx + 2) * (ty + 2)) * (int)sizeof(spinor<R>) <= 64 * 1024;
 }
 template <typename R>
 static bool a_tile_fits(int shape, int Lx, int Ly) {
     if (shape < 1 || shape > kNumATiles) return false;
     const ATileShape t = kATiles[shape - 1];
     return Lx % t.tx == 0 && Ly % t.ty == 0 && a_tile_lds_ok<R>(t.tx, t.ty);
+}
+
+// The fused configuration for a shape, or 0 where no tile divides the lattice (two launches).
+// The largest tile has the least ring and margin and measured fastest at every shape (FP64: the
+// largest that LDS holds).  Chunks as long as 4096 wavefronts allow, since each chunk evaluates two
+// slices of t and reads four of psi beyond its own (256^2 x 16 FP32, one column: 12.5 us in chunks
+// of 4, 12.9 of 8; four columns: 26.8 us in one chunk, 31.0 in chunks of 8), and at least 2
+// (128^2 x 16: 6.5 us in chunks of 2, 8.0 of 4).
+template <typename R>
+static int a_rule(int Lx, int Ly, int Ls, int ncol) {
+    if (Ls < 2) return 0;
+    for (int shape : {4, 2, 1, 3}) {
+        if (!a_tile_fits<R>(shape, Lx, Ly)) continue;
+        const ATileShape t = kATiles[shape - 1];
+        const long long waves = (long long)(Lx / t.tx) * (Ly / t.ty) * ncol * (t.tx * t.ty / 64);
+        const long long want = std::min<long long>((4096 + waves - 1) / waves, Ls);
+        const int cs = (int)std::max<long long>(2, (Ls + want - 1) / want);
+        return shape * kCfgStride + std::min(std::min(cs, Ls), kCfgStride - 1);
+    }
+    return 0;
+}
+// fused shapes that a caller may pin (FP64: the one whose LDS fitted a first form of the kernel)
+template <typename R>
+static bool a_pin_fits(int shape, int Lx, int Ly) {
+    return shape <= 3 && (sizeof(R) == 4 || shape == 3) && a_tile_fits<R>(shape, Lx, Ly);
 }
 
 template <typename R, int TX, int TY>
@@ -739,25 +756,26 @@ static hipError_t launch_a_tile(const cpx<R>* U, const spinor<R>* si, spinor<R>*
 
 template <typename R>
 static hipError_t launch_a(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* tmp, int Lx, int Ly, int Ls,
-                           int ncol, double m, double M5, const int* skip, int skip_stride, int cfg, hipStream_t st,
-                           bool may_time, const Epi<R>& epi = {}) {
+                           int ncol, double m1, double m2, double M5, const int* skip, int skip_stride, int cfg,
+                           hipStream_t st, bool may_time, const Epi<R>& epi = {}) {
     const int shape = cfg / kCfgStride, cs = cfg % kCfgStride;
     if (shape == 0) {
-        hipError_t e = fine_dw_impl<R>(U, in, tmp, nullptr, Lx, Ly, Ls, ncol, m, M5, false, skip, skip_stride, st,
+        hipError_t e = fine_dw_impl<R>(U, in, tmp, nullptr, Lx, Ly, Ls, ncol, m1, M5, false, skip, skip_stride, st,
                                        may_time);
         if (e != hipSuccess) return e;
-        return fine_dw_impl<R>(U, tmp, out, epi.b, Lx, Ly, Ls, ncol, 1.0, M5, true, skip, skip_stride, st, may_time,
+        return fine_dw_impl<R>(U, tmp, out, epi.b, Lx, Ly, Ls, ncol, m2, M5, true, skip, skip_stride, st, may_time,
                                epi.alpha, epi.beta);
     }
     if (cs < 1 || !a_tile_fits<R>(shape, Lx, Ly)) return hipErrorInvalidValue;
-    const R diag = R(2.0 + M5 + 1.0), mdw = R(-m), mpv = R(-1.0);
+    const R diag = R(2.0 + M5 + 1.0), mdw = R(-m1), mpv = R(-m2);
     auto* si = reinterpret_cast<const spinor<R>*>(in);
     auto* so = reinterpret_cast<spinor<R>*>(out);
-    static_assert(kNumATiles == 3, "one case per fused tile shape");
+    static_assert(kNumATiles == 4, "one case per fused tile shape");
     switch (shape) {
         case 1: return launch_a_tile<R, kATiles[0].tx, kATiles[0].ty>(U, si, so, Lx, Ly, Ls, ncol, diag, mdw, mpv, skip, skip_stride, cs, st, epi);
         case 2: return launch_a_tile<R, kATiles[1].tx, kATiles[1].ty>(U, si, so, Lx, Ly, Ls, ncol, diag, mdw, mpv, skip, skip_stride, cs, st, epi);
         case 3: return launch_a_tile<R, kATiles[2].tx, kATiles[2].ty>(U, si, so, Lx, Ly, Ls, ncol, diag, mdw, mpv, skip, skip_stride, cs, st, epi);
+        case 4: return launch_a_tile<R, kATiles[3].tx, kATiles[3].ty>(U, si, so, Lx, Ly, Ls, ncol, diag, mdw, mpv, skip, skip_stride, cs, st, epi);
         default: return hipErrorInvalidValue;
     }
 }
@@ -767,14 +785,14 @@ static std::atomic<int> g_a_pin{-1};
 
 bool set_fine_a_config(int shape, int chunk) {
     if (shape == -1) { g_a_pin.store(-1); return true; }
-    if (shape < 0 || shape > kNumATiles || (shape > 0 && (chunk < 1 || chunk >= kCfgStride))) return false;
+    if (shape < 0 || shape > 3 || (shape > 0 && (chunk < 1 || chunk >= kCfgStride))) return false;
     g_a_pin.store(shape * kCfgStride + (shape > 0 ? chunk : 0));
     return true;
 }
 
 // the fine A's configuration, timed once per lattice shape, column count and precision
-// (two launches or one fused launch per tile shape and chunk); the two launches stay
-// unless a fused configuration is faster by more than 3%
+// (two launches or one fused launch per tile shape and chunk); the rule's configuration stays
+// unless another is faster by more than 3%, and is what a capture takes before the timing
 static std::mutex g_a_mu;
 static std::map<std::string, int> g_a_cache;
 
@@ -783,7 +801,7 @@ static int tuned_a_cfg(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* t
                        int ncol, double m, double M5, hipStream_t st, bool may_time) {
     std::mutex& mu = g_a_mu;
     std::map<std::string, int>& cache = g_a_cache;
-    const int heuristic = 0;
+    const int heuristic = a_rule<R>(Lx, Ly, Ls, ncol);
     const char* en = std::getenv("DWF_AUTOTUNE");
     if (en && en[0] == '0') return heuristic;
     char keyb[128];
@@ -807,6 +825,7 @@ static int tuned_a_cfg(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* t
             if (c >= 1 && c <= Ls && std::find(chunks.begin(), chunks.end(), c) == chunks.end()) chunks.push_back(c);
         for (int c : chunks) cand.push_back(shape * kCfgStride + c);
     }
+    if (std::find(cand.begin(), cand.end(), heuristic) == cand.end()) cand.push_back(heuristic);
     int best = heuristic;
     if (cand.size() > 1) {
         hipEvent_t e0, e1;
@@ -814,12 +833,12 @@ static int tuned_a_cfg(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* t
         if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return heuristic; }
         float best_t = 1e30f, heur_t = 1e30f;
         for (int c : cand) {
-            if (launch_a<R>(U, in, out, tmp, Lx, Ly, Ls, ncol, m, M5, nullptr, 1, c, st, true) != hipSuccess) continue;
+            if (launch_a<R>(U, in, out, tmp, Lx, Ly, Ls, ncol, m, 1.0, M5, nullptr, 1, c, st, true) != hipSuccess) continue;
             float tc = 1e30f;
             for (int trial = 0; trial < 3; ++trial) {
                 (void)hipEventRecord(e0, st);
                 for (int r = 0; r < 10; ++r)
-                    (void)launch_a<R>(U, in, out, tmp, Lx, Ly, Ls, ncol, m, M5, nullptr, 1, c, st, true);
+                    (void)launch_a<R>(U, in, out, tmp, Lx, Ly, Ls, ncol, m, 1.0, M5, nullptr, 1, c, st, true);
                 (void)hipEventRecord(e1, st);
                 (void)hipEventSynchronize(e1);
                 float t = 0.f;
@@ -841,11 +860,22 @@ hipError_t fine_a(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* tmp, i
                   double m, double M5, const int* skip, int skip_stride, hipStream_t st, const Epi<R>& epi) {
     const int pin = g_a_pin.load(std::memory_order_relaxed);
     int cfg;
-    if (pin >= 0 && (pin / kCfgStride == 0 || (a_tile_fits<R>(pin / kCfgStride, Lx, Ly) && Ls >= 2)))
+    if (pin >= 0 && (pin / kCfgStride == 0 || (a_pin_fits<R>(pin / kCfgStride, Lx, Ly) && Ls >= 2)))
         cfg = pin / kCfgStride == 0 ? 0 : (pin / kCfgStride) * kCfgStride + std::min(pin % kCfgStride, Ls);
     else
         cfg = tuned_a_cfg<R>(U, in, out, tmp, Lx, Ly, Ls, ncol, m, M5, st, true);
-    return launch_a<R>(U, in, out, tmp, Lx, Ly, Ls, ncol, m, M5, skip, skip_stride, cfg, st, true, epi);
+    return launch_a<R>(U, in, out, tmp, Lx, Ly, Ls, ncol, m, 1.0, M5, skip, skip_stride, cfg, st, true, epi);
+}
+
+template <typename R>
+bool fine_product_fits(int Lx, int Ly, int Ls, int ncol) { return a_rule<R>(Lx, Ly, Ls, ncol) != 0; }
+
+template <typename R>
+hipError_t fine_product(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, int Lx, int Ly, int Ls, int ncol, double m1,
+                        double m2, double M5, hipStream_t st) {
+    const int cfg = a_rule<R>(Lx, Ly, Ls, ncol);
+    if (cfg == 0) return hipErrorInvalidValue;
+    return launch_a<R>(U, in, out, nullptr, Lx, Ly, Ls, ncol, m1, m2, M5, nullptr, 1, cfg, st, false);
 }
 
 bool fine_a_chosen(int prec_bytes, int Lx, int Ly, int Ls, int ncol, int* shape, int* chunk) {
@@ -1098,6 +1128,10 @@ template hipError_t fine_dw_untimed<float>(const cpx<float>*, const cpx<float>*,
 template hipError_t fine_dw_untimed<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, int, int, int, int, double, double, bool, hipStream_t);
 template hipError_t fine_a<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, cpx<float>*, int, int, int, int, double, double, const int*, int, hipStream_t, const Epi<float>&);
 template hipError_t fine_a<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, cpx<double>*, int, int, int, int, double, double, const int*, int, hipStream_t, const Epi<double>&);
+template bool fine_product_fits<float>(int, int, int, int);
+template bool fine_product_fits<double>(int, int, int, int);
+template hipError_t fine_product<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, int, int, int, int, double, double, double, hipStream_t);
+template hipError_t fine_product<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, int, int, int, int, double, double, double, hipStream_t);
 template hipError_t wilson2d<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, int, int, int, double, bool, hipStream_t);
 template hipError_t wilson2d<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, int, int, int, double, bool, hipStream_t);
 

@@ -63,6 +63,13 @@ bool set_fine_config(int shape, int chunk);
 template <typename R>
 hipError_t fine_a(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* tmp, int Lx, int Ly, int Ls, int ncol,
                   double m, double M5, const int* skip, int skip_stride, hipStream_t st, const Epi<R>& epi = {});
+// out = D(m2)^dag D(m1) in in one launch without an intermediate field (A: m1 = m, m2 = 1; A^dag:
+// m1 = 1, m2 = m), by a rule on the sizes, never timed; only where fine_product_fits
+template <typename R>
+bool fine_product_fits(int Lx, int Ly, int Ls, int ncol);
+template <typename R>
+hipError_t fine_product(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, int Lx, int Ly, int Ls, int ncol, double m1,
+                        double m2, double M5, hipStream_t st);
 // pin the fine A's configuration: shape -1 timed choice, 0 two launches, k >= 1 fused tile
 // shape k with the given slice chunk; false for an unknown shape or chunk
 bool set_fine_a_config(int shape, int chunk);
