@@ -399,6 +399,172 @@ hipError_t cg_update_p(cpx<T>* p, const cpx<T>* z, size_t n, int ncol, const CgS
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------ CGNR (coarsest level)
+// A finaliser per inner product cost two of ten launches an iteration, 1.7 us each on a coarsest
+// level of 256 sites where a whole iteration took 30 us; here every workgroup adds the partials
+// (L2 hits, at most a few tens of KB) and the column's first workgroup passes the state on in a
+// second buffer.  The norms' passes over the vectors are gone too: the stencils leave the partials.
+// All first loads - partials, state, fields - are issued before any is waited for, the state field by
+// field: with the state as a local struct (which the compiler put in LDS) and the partials
+// loaded behind it, x and r took 7.8 us on 256 sites x 8 slices x 16; now 2.8, p 2.6.  An iteration
+// there takes six launches, 22 us against 30 with ten.
+namespace {
+constexpr int kPartBatch = 8;   // partials per thread in flight
+struct PartLoads {
+    double v[kPartBatch];
+};
+__device__ __forceinline__ PartLoads partials_load(const double* part, int np) {
+    PartLoads l;
+#pragma unroll
+    for (int j = 0; j < kPartBatch; ++j) {
+        const int b = (int)threadIdx.x + j * kBlock;
+        l.v[j] = part[b < np ? b : 0];
+    }
+    return l;
+}
+__device__ __forceinline__ double partials_total(const PartLoads& l, const double* part, int np, double* sh) {
+    double t = 0.0;
+#pragma unroll
+    for (int j = 0; j < kPartBatch; ++j) t += (int)threadIdx.x + j * kBlock < np ? l.v[j] : 0.0;
+    for (int b = threadIdx.x + kPartBatch * kBlock; b < np; b += kBlock) t += part[b];
+    t = wave_sum(t);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = t;
+    __syncthreads();
+    t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) t += sh[w];
+    return t;
+}
+}  // namespace
+
+template <typename T>
+__global__ void __launch_bounds__(kBlock)
+k_cgnr_xr(cpx<T>* x, cpx<T>* r, const cpx<T>* p, const cpx<T>* q, size_t n, const CgScal* s, double* s2,
+          const double* part, size_t pstride, int np) {
+    __shared__ double sh[kWaves];
+    const int col = blockIdx.y;
+    const size_t o = (size_t)col * n, stride = (size_t)gridDim.x * kBlock;
+    size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    const size_t e0 = e < n ? e : 0;
+    const double* pc = part + (size_t)col * pstride;
+    const PartLoads pl = partials_load(pc, np);
+    const CgScal* sc = s + col;
+    const double zz = sc->zz, zz0 = sc->zz0, tol2 = sc->tol2, beta = sc->beta;
+    const int iters = sc->iters;
+    int done = sc->done;
+    double alpha = sc->alpha;
+    cpx<T> pi = p[o + e0], qi = q[o + e0], xi = x[o + e0], ri = r[o + e0];
+    const double ww = partials_total(pl, pc, np, sh);
+    if (done == 0) {
+        alpha = zz / ww;
+        if (!(ww > 0.0) || !finite(ww)) {
+            alpha = 0.0;
+            done = finite(ww) ? 2 : 4;   // breakdown / non-finite
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        CgScal* d = reinterpret_cast<CgScal*>(s2 + (size_t)col * pstride);
+        d->zz = zz;
+        d->zz0 = zz0;
+        d->tol2 = tol2;
+        d->alpha = alpha;
+        d->beta = beta;
+        d->done = done;
+        d->iters = iters;
+    }
+    if (done) return;
+    const T a = (T)alpha;
+    while (e < n) {
+        x[o + e] = {xi.re + a * pi.re, xi.im + a * pi.im};
+        r[o + e] = {ri.re - a * qi.re, ri.im - a * qi.im};
+        e += stride;
+        if (e < n) { pi = p[o + e]; qi = q[o + e]; xi = x[o + e]; ri = r[o + e]; }
+    }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kBlock)
+k_cgnr_p(cpx<T>* p, const cpx<T>* z, size_t n, int maxit, const double* s2, CgScal* s, const double* part, size_t pstride,
+         int np) {
+    __shared__ double sh[kWaves];
+    const int col = blockIdx.y;
+    const size_t o = (size_t)col * n, stride = (size_t)gridDim.x * kBlock;
+    size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    const size_t e0 = e < n ? e : 0;
+    const double* pc = part + (size_t)col * pstride;
+    const PartLoads pl = partials_load(pc, np);
+    const CgScal* sc = reinterpret_cast<const CgScal*>(s2 + (size_t)col * pstride);
+    const double zz0 = sc->zz0, tol2 = sc->tol2, alpha = sc->alpha;
+    double zz = sc->zz, beta = sc->beta;
+    int done = sc->done, iters = sc->iters;
+    cpx<T> pi = p[o + e0], zi = z[o + e0];
+    const double znew = partials_total(pl, pc, np, sh);
+    if (done == 0) {
+        iters += 1;
+        if (!finite(znew)) {
+            done = 4;
+        } else {
+            beta = znew / zz;
+            zz = znew;
+            if (znew <= tol2 * zz0) done = 1;
+            else if (iters >= maxit) done = 3;
+        }
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        CgScal* d = s + col;
+        d->zz = zz;
+        d->zz0 = zz0;
+        d->tol2 = tol2;
+        d->alpha = alpha;
+        d->beta = beta;
+        d->done = done;
+        d->iters = iters;
+    }
+    if (done) return;
+    const T b = (T)beta;
+    while (e < n) {
+        p[o + e] = {zi.re + b * pi.re, zi.im + b * pi.im};
+        e += stride;
+        if (e < n) { pi = p[o + e]; zi = z[o + e]; }
+    }
+}
+
+namespace {
+// workgroups of the updates: one entry per thread while the chip has room, then several (each
+// workgroup adds the partials once)
+inline dim3 cgnr_grid(size_t n, int ncol) {
+    const size_t nb = (n + kBlock - 1) / kBlock;
+    return dim3((unsigned)std::max<size_t>(1, std::min<size_t>(nb, std::max(1024 / ncol, 64))), (unsigned)ncol);
+}
+}  // namespace
+
+template <typename T>
+hipError_t cgnr_xr(cpx<T>* x, cpx<T>* r, const cpx<T>* p, const cpx<T>* q, size_t n, int ncol, const CgScal* s, double* s2,
+                   const double* part, size_t pstride, int np, hipStream_t st) {
+    hipLaunchKernelGGL(k_cgnr_xr<T>, cgnr_grid(n, ncol), dim3(kBlock), 0, st, x, r, p, q, n, s, s2, part, pstride, np);
+    return hipGetLastError();
+}
+template <typename T>
+hipError_t cgnr_p(cpx<T>* p, const cpx<T>* z, size_t n, int ncol, int maxit, const double* s2, CgScal* s, const double* part,
+                  size_t pstride, int np, hipStream_t st) {
+    hipLaunchKernelGGL(k_cgnr_p<T>, cgnr_grid(n, ncol), dim3(kBlock), 0, st, p, z, n, maxit, s2, s, part, pstride, np);
+    return hipGetLastError();
+}
+template <typename T>
+hipError_t norm2_partials(const cpx<T>* x, size_t n, int ncol, const CgScal* s, double* part, size_t pstride, int* np,
+                          hipStream_t st) {
+    // k_norm2_part with its partials at `part` (one quantity per column, pstride apart)
+    RedWork rw;
+    rw.partial = part;
+    rw.nblk = (int)pstride;
+    rw.max_q = 1;
+    rw.max_cols = ncol;
+    const unsigned nb = (unsigned)std::max<size_t>(1, std::min<size_t>((n + 2 * kBlock - 1) / (2 * kBlock), 512));
+    *np = (int)nb;
+    hipLaunchKernelGGL(k_norm2_part<T>, dim3(nb, ncol), dim3(kBlock), 0, st, x, n, rw, &s[0].done, kCgSkipStride);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------ GCR
 namespace {
 __device__ __forceinline__ cpx<double> ld2(const double* p) { return {p[0], p[1]}; }
@@ -1284,6 +1450,9 @@ hipError_t check_finite(const cpx<T>* x, size_t n, int* flag, hipStream_t st) {
     template hipError_t cg_update_xr<T>(cpx<T>*, cpx<T>*, const cpx<T>*, const cpx<T>*, size_t, int, const CgScal*, hipStream_t); \
     template hipError_t cg_beta<T>(const cpx<T>*, size_t, int, CgScal*, int, const RedWork&, hipStream_t); \
     template hipError_t cg_update_p<T>(cpx<T>*, const cpx<T>*, size_t, int, const CgScal*, hipStream_t); \
+    template hipError_t cgnr_xr<T>(cpx<T>*, cpx<T>*, const cpx<T>*, const cpx<T>*, size_t, int, const CgScal*, double*, const double*, size_t, int, hipStream_t); \
+    template hipError_t cgnr_p<T>(cpx<T>*, const cpx<T>*, size_t, int, int, const double*, CgScal*, const double*, size_t, int, hipStream_t); \
+    template hipError_t norm2_partials<T>(const cpx<T>*, size_t, int, const CgScal*, double*, size_t, int*, hipStream_t); \
     template hipError_t gcr_multidot<T>(const cpx<T>*, size_t, int, const cpx<T>*, size_t, int, const GcrDev&, const RedWork&, hipStream_t); \
     template hipError_t gcr_orth<T>(const cpx<T>*, size_t, int, cpx<T>*, const cpx<T>*, size_t, int, const GcrDev&, const RedWork&, hipStream_t); \
     template hipError_t gcr_rupdate<T>(const cpx<T>*, cpx<T>*, cpx<T>*, int, size_t, int, bool, const GcrDev&, const RedWork&, hipStream_t); \

@@ -194,7 +194,7 @@ __global__ void __launch_bounds__(320) __attribute__((amdgpu_waves_per_eu(block_
 coarse_block_kernel(const L* __restrict__ links, const cpx<T>* __restrict__ in, cpx<T>* __restrict__ out,
                     const int* __restrict__ skip, int skip_stride, int Lx, int Ly, int Ls, int nsites, int ncol,
                     int tpb, typename acc_of<L>::type cdiag, typename acc_of<L>::type mwrap,
-                    const cpx<T>* __restrict__ eb, T ealpha, T ebeta) {
+                    const cpx<T>* __restrict__ eb, T ealpha, T ebeta, double* __restrict__ norm, size_t norm_stride) {
     using A = typename acc_of<L>::type;
     constexpr int H = N / 2;
     constexpr int RI = block_rows(N);
@@ -354,6 +354,18 @@ coarse_block_kernel(const L* __restrict__ links, const cpx<T>* __restrict__ in, 
             cpx<T> w = {(T)r.re, (T)r.im};
             if (eb) w = {ealpha * w.re + ebeta * le[p].re, ealpha * w.im + ebeta * le[p].im};
             out[((size_t)c * nsites + site) * N + i] = w;
+            // (a thread reads only its own outputs' parts: their place takes |out|^2)
+            if (norm) *reinterpret_cast<double*>(&sm[0][o]) = (double)w.re * w.re + (double)w.im * w.im;
+        }
+        if (norm) {   // (uniform) one partial per (column, site)
+            __syncthreads();
+            const int c = cbase + (int)threadIdx.x;
+            if ((int)threadIdx.x < CT && live(c)) {
+                double sum = 0.0;
+#pragma unroll 8
+                for (int i = 0; i < N; ++i) sum += *reinterpret_cast<const double*>(&sm[0][threadIdx.x * N + i]);
+                norm[(size_t)(c / Ls) * norm_stride + (size_t)(c % Ls) * nsites + site] = sum;
+            }
         }
         if (t + 1 < t_hi) __syncthreads();   // the next tile stages over the parts
     }
@@ -384,7 +396,7 @@ hipError_t launch_n(const void* links, const cpx<T>* in, cpx<T>* out, const Coar
             hipLaunchKernelGGL((coarse_block_kernel<L, T, N, decltype(dagc)::value, decltype(wilc)::value,
                                                     decltype(ctc)::value>),
                                grid, block, 0, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, ncol, tpb, cd, mw,
-                               epi.b, ea, ebt);
+                               epi.b, ea, ebt, epi.norm, epi.norm_stride);
         };
         auto with_ct = [&](auto ctc) {
             if (wil) { if (dagger) go(ctc, std::true_type{}, std::true_type{}); else go(ctc, std::false_type{}, std::true_type{}); }
@@ -431,12 +443,15 @@ hipError_t launch_l(const void* links, const cpx<T>* in, cpx<T>* out, const Coar
 
 }  // namespace
 
+bool coarse_norm_supported(int n, int link_prec) { return n >= 16 && !coarse_mfma_supported(n, link_prec); }
+
 template <typename T>
 hipError_t coarse_apply(const void* links, int link_prec, const cpx<T>* in, cpx<T>* out,
                         const CoarseGeom& g, int ncol, double m, double M5, bool dagger,
                         bool wilson_mode, double wilson_mass, const int* skip, int sks, hipStream_t st,
                         const Epi<T>& epi) {
     if (g.Ls < 1 || g.Ls > kMaxCoarseLs) return hipErrorInvalidValue;
+    if (epi.norm && (wilson_mode || !coarse_norm_supported(g.n, link_prec))) return hipErrorInvalidValue;
     if (!wilson_mode && coarse_mfma_supported(g.n, link_prec))
         return coarse_apply_mfma<T>(links, link_prec, in, out, g, ncol, m, M5, dagger, skip, sks, st, epi);
     switch (link_prec) {

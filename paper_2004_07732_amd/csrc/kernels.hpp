@@ -43,6 +43,10 @@ template <typename R>
 struct Epi {
     const cpx<R>* b = nullptr;
     double alpha = 1.0, beta = 0.0;
+    // coarse operators where coarse_norm_supported: |out|^2 in partial sums, Ls nsites of them
+    // per right-hand side, right-hand side r's from norm + r norm_stride
+    double* norm = nullptr;
+    size_t norm_stride = 0;
 };
 // out = D in, or with b set beta b + alpha D in (by default the residual b - D in)
 template <typename R>
@@ -109,6 +113,9 @@ hipError_t coarse_apply(const void* links, int link_prec, const cpx<T>* in, cpx<
                         bool wilson_mode, double wilson_mass, const int* skip, int skip_stride,
                         hipStream_t st, const Epi<T>& epi = {});
 
+// whether coarse_apply can leave the partial sums of |out|^2 (Epi::norm) for such a level
+bool coarse_norm_supported(int n, int link_prec);
+
 // Matrix-core path (BF16 or FP16 links stored in MFMA fragment order per
 // site, n a multiple of 16); coarse_apply dispatches to it by itself for such levels.
 bool coarse_mfma_supported(int n, int link_prec);
@@ -165,6 +172,21 @@ hipError_t cg_update_xr(cpx<T>* x, cpx<T>* r, const cpx<T>* p, const cpx<T>* w, 
 // znew = |z|^2; unless done: done = znew <= tol2 zz0, beta = znew / zz, zz = znew, iters++
 template <typename T>
 hipError_t cg_beta(const cpx<T>* z, size_t n, int ncol, CgScal* s, int maxit, const RedWork& rw, hipStream_t st);
+// CGNR on the coarsest level: the two updates, each of which first adds np partial sums per column
+// (column c's from part + c pstride) in every workgroup, so that no finaliser launch stands
+// between.  The column state goes s -> s2 -> s (s2: one state per column, pstride doubles apart).
+//   alpha = zz / |q|^2;  x += alpha p, r -= alpha q
+template <typename T>
+hipError_t cgnr_xr(cpx<T>* x, cpx<T>* r, const cpx<T>* p, const cpx<T>* q, size_t n, int ncol, const CgScal* s, double* s2,
+                   const double* part, size_t pstride, int np, hipStream_t st);
+//   beta = |z|^2 / zz;  p = z + beta p
+template <typename T>
+hipError_t cgnr_p(cpx<T>* p, const cpx<T>* z, size_t n, int ncol, int maxit, const double* s2, CgScal* s, const double* part,
+                  size_t pstride, int np, hipStream_t st);
+// partial sums of |x_c|^2 for them (the number of partials per column in np)
+template <typename T>
+hipError_t norm2_partials(const cpx<T>* x, size_t n, int ncol, const CgScal* s, double* part, size_t pstride, int* np,
+                          hipStream_t st);
 // s.zz0 = ref[c] (a reference norm other than the starting residual), done re-evaluated
 hipError_t cg_set_ref(CgScal* s, const double* ref, int ncol, hipStream_t st);
 // p = z + beta p   (skipped when done)

@@ -245,7 +245,7 @@ hipError_t Hierarchy::apply_A(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp,
 // A^dag = D_DW^dag D_PV (with the PV polynomial: D_DW^dag p(X) D_PV; p(X) is Hermitian)
 template <typename T>
 hipError_t Hierarchy::apply_Adag(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp, int ncol, hipStream_t st,
-                                 const int* skip) {
+                                 const int* skip, const Epi<T>& epi) {
     hipError_t e = apply_dw<T>(l, in, tmp, 1.0, false, ncol, st, skip);
     if (e != hipSuccess) return e;
     if (l == 0 && !capturing_) cnt_.fine_applies += a_cost(0);
@@ -253,9 +253,9 @@ hipError_t Hierarchy::apply_Adag(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* t
         cpx<T>* y = C<T>(work_[0].py);
         e = pv_poly<T>(tmp, y, C<T>(work_[0].pz), ncol, st, skip);
         if (e != hipSuccess) return e;
-        return apply_dw<T>(l, y, out, m, true, ncol, st, skip);
+        return apply_dw<T>(l, y, out, m, true, ncol, st, skip, epi);
     }
-    return apply_dw<T>(l, tmp, out, m, true, ncol, st, skip);
+    return apply_dw<T>(l, tmp, out, m, true, ncol, st, skip, epi);
 }
 
 template <typename T>
@@ -409,15 +409,28 @@ Task Hierarchy::cgnr(int l, const cpx<T>* b, cpx<T>* x, int ncol, hipStream_t st
     const int maxit = prm.coarsest_maxit;
     int iters = 0;
     // one chunk of CGNR iterations; iterations past convergence or maxit are
-    // no-ops on the device, so chunks always have the full length
+    // no-ops on the device, so chunks always have the full length.  The norms come as partial sums
+    // from the last stencil of each operator where its kernel leaves them and they are few
+    // enough to be added by every workgroup of the updates, else from a pass of their own; the
+    // second state buffer lies in the partial sums' unused last quantity.
+    const size_t ps = (size_t)rw_.max_q * rw_.nblk;
+    double* pa = rw_.partial;
+    double* pb = rw_.partial + 4 * (size_t)rw_.nblk;
+    double* s2 = rw_.partial + (size_t)(rw_.max_q - 1) * rw_.nblk;
+    const bool fused = !L.fine && coarse_norm_supported(L.n, L.link_prec) && L.Ls * L.nsites <= 2 * rw_.nblk;
     auto chunk = [&](int len) -> int {
+        int np = L.Ls * L.nsites;
         for (int c = 0; c < len; ++c) {
-            HIPCHK(apply_A<T>(l, p, q, t, ncol, st, skip));
-            HIPCHK(cg_alpha<T>(q, n, ncol, s, rw_, st));
-            HIPCHK(cg_update_xr<T>(x, r, p, q, n, ncol, s, st));
-            HIPCHK(apply_Adag<T>(l, r, z, t, ncol, st, skip));
-            HIPCHK(cg_beta<T>(z, n, ncol, s, maxit, rw_, st));
-            HIPCHK(cg_update_p<T>(p, z, n, ncol, s, st));
+            Epi<T> e{};
+            e.norm = fused ? pa : nullptr;
+            e.norm_stride = ps;
+            HIPCHK(apply_A<T>(l, p, q, t, ncol, st, skip, e));
+            if (!fused) HIPCHK(norm2_partials<T>(q, n, ncol, s, pa, ps, &np, st));
+            HIPCHK(cgnr_xr<T>(x, r, p, q, n, ncol, s, s2, pa, ps, np, st));
+            e.norm = fused ? pb : nullptr;
+            HIPCHK(apply_Adag<T>(l, r, z, t, ncol, st, skip, e));
+            if (!fused) HIPCHK(norm2_partials<T>(z, n, ncol, s, pb, ps, &np, st));
+            HIPCHK(cgnr_p<T>(p, z, n, ncol, maxit, s2, s, pb, ps, np, st));
         }
         return DWF_OK;
     };

@@ -312,7 +312,7 @@ private:
     // shift of the s-step Krylov directions on level l
     double ss_shift(int l) const;
     template <typename T> hipError_t apply_Adag(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp, int ncol,
-                                                hipStream_t st, const int* skip = nullptr);
+                                                hipStream_t st, const int* skip = nullptr, const Epi<T>& epi = {});
     template <typename T> hipError_t apply_wilson(int l, const cpx<T>* in, cpx<T>* out, double mass,
                                                   bool dag, int ncol, hipStream_t st);
     template <typename T> hipError_t restrict_to(int l, const cpx<T>* r, void* rc_next, int ncol, hipStream_t st);

@@ -1,0 +1,51 @@
+"""CGNR on the coarsest level: the norms that the last stencil of each operator leaves as partial
+sums (16 components and more, few enough sums), and those of a pass of their own (fewer
+components, or more sums than every workgroup of the updates should add)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import dwf_oracle as O
+from paper_2004_07732_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+dwfmg = pytest.importorskip("paper_2004_07732_amd.dwfmg")
+
+
+def T(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).to("cuda")
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("L,nvec,block,Lsc", [
+    (16, 8, 4, 2),      # 32 sums
+    (24, 8, 4, 3),      # odd slices: columns of a tile span right-hand sides
+    (16, 12, 4, 4),     # 24 components
+    (64, 8, 4, 16),     # 4096 sums: the most that stay with the stencil
+    (64, 8, 4, 17),     # 4352: a pass of its own
+    (16, 4, 4, 2),      # 8 components: a pass of its own
+])
+@pytest.mark.parametrize("maxit,tol", [(1, 1e-30), (9, 1e-30), (50, 0.1)])
+def test_iterates(L, nvec, block, Lsc, maxit, tol, prec):
+    """A given number of iterations, or those to a loose tolerance, from start to end against the
+    oracle's; three columns, the middle one zero.  Bar: rounding times the condition of the few
+    Krylov steps taken (at m = 0.5, below 1e4): 1e-12 and, for 24 bits, 6e-4 on 6e-8 times 1e4."""
+    Ls = max(6, Lsc)
+    U = inputs.metropolis_u1(L, L, 6.0, 10, 930).U
+    start = inputs.gaussian_field((nvec, L, L, 2), 931)
+    q = dwfmg.P_F64 if prec == "f64" else dwfmg.P_F32
+    p = dwfmg.MGParams(nvec=[nvec], block=[(block, block)], Ls_coarse=[Lsc], link_prec=[q], vec_prec=[q], setup_iters=0,
+                       smooth_iters=0, coarsest_tol=tol, coarsest_maxit=maxit)
+    mg = dwfmg.MG(T(U), Ls, 0.5, -1.0, p, [T(start)], max_nrhs=3)
+    o = O.MG(U, Ls, 0.5, -1.0,
+             O.MGParams(levels=[O.LevelParams(nvec=nvec, block=(block, block), Ls=Lsc, setup_iters=0)], smooth_iters=0,
+                        coarsest_tol=tol, coarsest_maxit=maxit), [start])
+    r = inputs.gaussian_field((3, Ls, L, L, 2), 932)
+    r[1] = 0.0
+    r[2] *= 1e-3
+    got = mg.level_op(0, dwfmg.MG_OP_KCYCLE, T(r), 3).cpu().numpy()
+    assert not got[1].any()
+    for c in (0, 2):
+        want = o.kcycle(0, r[c])
+        assert np.linalg.norm(got[c] - want) < (1e-12 if prec == "f64" else 6e-4) * np.linalg.norm(want)
