@@ -988,7 +988,7 @@ constexpr double kSsPivot = 1e-13;
 constexpr double kSsTrust = 1e-12;
 template <int K>
 __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb, GcrDev g, double tol2, double inv_c,
-                                                            int first) {
+                                                            int first, SsPublish pub) {
     constexpr int NQ = ss_nq(K);
     constexpr int NR = (NQ + 63) / 64;
     __shared__ double sp[kSsFinWaves][NQ];
@@ -1000,14 +1000,25 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
     const int flag0 = first ? 0 : g.stop[col];
     const int it0 = first ? 0 : g.it[col];
     const double bb0 = first ? -1.0 : g.bb[col];
+    const unsigned seq = pub.word ? *pub.ctr + 1u : 0u;
+    static_assert(kSsBlocks % kSsFinWaves == 0);
+    constexpr int NB = kSsBlocks / kSsFinWaves;
+    double pv[NR][NB];   // all of a lane's partials in flight together
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        const int q = r * 64 + lane;
-        const bool on = q < NQ;
+        const int q = r * 64 + lane < NQ ? r * 64 + lane : 0;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const int b = wid + j * kSsFinWaves;
+            pv[r][j] = part[(size_t)(b < nb ? b : 0) * NQ + q];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
         double s = 0.0;
-#pragma unroll 8
-        for (int b = wid; b < nb; b += kSsFinWaves) s += part[(size_t)b * NQ + (on ? q : 0)];
-        if (on) sp[wid][q] = s;
+#pragma unroll
+        for (int j = 0; j < NB; ++j) s += wid + j * kSsFinWaves < nb ? pv[r][j] : 0.0;
+        if (r * 64 + lane < NQ) sp[wid][r * 64 + lane] = s;
     }
     __syncthreads();
     if (threadIdx.x < NQ) {
@@ -1027,12 +1038,19 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
     int flag = flag0;
     if (flag == 0 && !sane) flag = 2;
     if (flag == 0 && (rr0 == 0.0 || (bb0 >= 0.0 && rr0 <= tol2 * bb))) flag = 1;
+    auto leave = [&](int f, int it) {
+        if (pub.word)
+            __hip_atomic_store(pub.word + col,
+                               (unsigned long long)seq << 32 | (unsigned)it << 2 | (unsigned)f,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        g.stop[col] = f;
+        g.it[col] = it;
+        g.bb[col] = bb;
+    };
     if (flag != 0) {   // the column takes no update
         if (lane == 0) {
             coef[kGcrTot - 1] = 0.0;
-            g.stop[col] = flag;
-            g.it[col] = it0;
-            g.bb[col] = bb;
+            leave(flag, it0);
         }
         return;
     }
@@ -1083,6 +1101,11 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
         }
     }
     if (lane != 0) return;
+    cpx<double> Lr[K][K];   // (columns of steps not taken are never stored; their values go unused)
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int l = k + 1; l < K; ++l) Lr[l][k] = sL[l][k];
     cpx<double> y[K + 1];
     y[K] = {0.0, 0.0};
 #pragma unroll
@@ -1091,7 +1114,7 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
 #pragma unroll
         for (int l = k + 1; l < K; ++l) {
             if (l < kend) {
-                const cpx<double> t = cjmul(sL[l][k], y[l]);
+                const cpx<double> t = cjmul(Lr[l][k], y[l]);
                 acc.re -= t.re;
                 acc.im -= t.im;
             }
@@ -1111,16 +1134,15 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
         }
     }
     coef[kGcrTot - 1] = flag == 2 ? 0.0 : 1.0;
-    g.stop[col] = flag;
-    g.it[col] = it0 + kend;
-    g.bb[col] = bb;
+    leave(flag, it0 + kend);
 }
 
 template <typename T, int K>
-__global__ void __launch_bounds__(kBlock) k_ss_update(SsVecs<T> P, cpx<T>* x, size_t nw, GcrDev g) {
+__global__ void __launch_bounds__(kBlock) k_ss_update(SsVecs<T> P, cpx<T>* x, size_t nw, GcrDev g, unsigned* ctr) {
     using W = Word<T>;
     typedef typename W::type word;
     const int col = blockIdx.y;
+    if (ctr && blockIdx.x == 0 && col == 0 && threadIdx.x == 0) *ctr += 1u;   // (no other workgroup reads it)
     const double* coef = g.tot + (size_t)col * kGcrTot;
     cpx<double> y[K], d[K + 1];
 #pragma unroll
@@ -1349,8 +1371,8 @@ hipError_t ss_begin(const cpx<T>* b, cpx<T>* P0, cpx<T>* x, size_t n, int ncol, 
 }
 template <typename T>
 hipError_t ss_finish(const SsVecs<T>& P, int k, cpx<T>* x, size_t n, int ncol, double c, double tol2, bool first,
-                     const GcrDev& g, const RedWork& rw, hipStream_t st) {
-    if (k < 1 || k > kSsMax || 4 * k + 3 > kGcrTot || n % Word<T>::E) return hipErrorInvalidValue;
+                     const GcrDev& g, const RedWork& rw, hipStream_t st, const SsPublish& pub) {
+    if (k < 1 || k > kSsMax || (pub.word && !pub.ctr) || 4 * k + 3 > kGcrTot || n % Word<T>::E) return hipErrorInvalidValue;
     const size_t nw = n / Word<T>::E;
     // blocks per column: two words per thread at least, one workgroup per CU over all columns
     // (a block's sums cost as much as streaming several words, and one workgroup adds them all)
@@ -1361,8 +1383,9 @@ hipError_t ss_finish(const SsVecs<T>& P, int k, cpx<T>* x, size_t n, int ncol, d
         constexpr int K = decltype(kc)::value + 1;
         hipLaunchKernelGGL((k_ss_dots<T, K>), dim3((unsigned)nb, ncol), dim3(kSsThreads), 0, st, P, nw, rw);
         hipLaunchKernelGGL(k_ss_fin<K>, dim3(ncol), dim3(64 * kSsFinWaves), 0, st, rw, (int)nb, g, tol2, 1.0 / c,
-                           first ? 1 : 0);
-        hipLaunchKernelGGL((k_ss_update<T, K>), ew_grid(nw, ncol), dim3(kBlock), 0, st, P, x, nw, g);
+                           first ? 1 : 0, pub);
+        hipLaunchKernelGGL((k_ss_update<T, K>), ew_grid(nw, ncol), dim3(kBlock), 0, st, P, x, nw, g,
+                           pub.word ? pub.ctr : nullptr);
     };
     with_j(k - 1, launch, std::make_integer_sequence<int, kSsMax>{});
     return hipGetLastError();
@@ -1477,8 +1500,8 @@ template hipError_t gcr_solve_xupdate<float, float>(const cpx<float>*, size_t, i
 template hipError_t gcr_solve_xupdate<double, double>(const cpx<double>*, size_t, int, cpx<double>*, size_t, int, bool, const GcrDev&, hipStream_t);
 template hipError_t ss_begin<float>(const cpx<float>*, cpx<float>*, cpx<float>*, size_t, int, const GcrDev&, hipStream_t);
 template hipError_t ss_begin<double>(const cpx<double>*, cpx<double>*, cpx<double>*, size_t, int, const GcrDev&, hipStream_t);
-template hipError_t ss_finish<float>(const SsVecs<float>&, int, cpx<float>*, size_t, int, double, double, bool, const GcrDev&, const RedWork&, hipStream_t);
-template hipError_t ss_finish<double>(const SsVecs<double>&, int, cpx<double>*, size_t, int, double, double, bool, const GcrDev&, const RedWork&, hipStream_t);
+template hipError_t ss_finish<float>(const SsVecs<float>&, int, cpx<float>*, size_t, int, double, double, bool, const GcrDev&, const RedWork&, hipStream_t, const SsPublish&);
+template hipError_t ss_finish<double>(const SsVecs<double>&, int, cpx<double>*, size_t, int, double, double, bool, const GcrDev&, const RedWork&, hipStream_t, const SsPublish&);
 template hipError_t gcr_solve_xupdate_restart<float>(cpx<float>*, size_t, int, cpx<float>*, size_t, int, const cpx<float>*, const int*, const GcrDev&, hipStream_t);
 template hipError_t gcr_solve_xupdate_restart<double>(cpx<double>*, size_t, int, cpx<double>*, size_t, int, const cpx<double>*, const int*, const GcrDev&, hipStream_t);
 

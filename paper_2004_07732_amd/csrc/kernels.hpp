@@ -249,11 +249,21 @@ hipError_t gcr_fused_step(const cpx<T>* W, size_t wstride, int j, cpx<T>* w, cpx
 constexpr int kSsMax = 8;
 constexpr int kSsBlocks = 256;
 template <typename T> struct SsVecs { cpx<T>* p[kSsMax + 1]; };
+// With `word` set the finaliser also tells the host each column's state, before the update runs: one
+// 64-bit word per column in host-coherent memory (device view), the cycle's number (one more
+// than the device counter *ctr, which the update advances), g.it and g.stop in it.
+struct SsPublish {
+    unsigned long long* word = nullptr;
+    unsigned* ctr = nullptr;
+};
+constexpr int ss_word_stop(unsigned long long w) { return (int)(w & 3u); }
+constexpr int ss_word_it(unsigned long long w) { return (int)((unsigned)w >> 2); }
+constexpr unsigned ss_word_seq(unsigned long long w) { return (unsigned)(w >> 32); }
 template <typename T>
 hipError_t ss_begin(const cpx<T>* b, cpx<T>* P0, cpx<T>* x, size_t n, int ncol, const GcrDev& g, hipStream_t st);
 template <typename T>
 hipError_t ss_finish(const SsVecs<T>& P, int k, cpx<T>* x, size_t n, int ncol, double c, double tol2, bool first,
-                     const GcrDev& g, const RedWork& rw, hipStream_t st);
+                     const GcrDev& g, const RedWork& rw, hipStream_t st, const SsPublish& pub = {});
 // next restart cycle on the recursive residual: P0 = r, and the stop flags of the
 // cycle's last step (stop_src) become g.stop
 template <typename T>

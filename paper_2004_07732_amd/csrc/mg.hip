@@ -72,6 +72,7 @@ Hierarchy::~Hierarchy() {
     if (h_int_) (void)hipHostFree(h_int_);
     if (h_cg_) (void)hipHostFree(h_cg_);
     if (h_seq_) (void)hipHostFree(h_seq_);
+    if (h_col_) (void)hipHostFree(h_col_);
     if (ev_in_) (void)hipEventDestroy(ev_in_);
     if (wait_ev_) (void)hipEventDestroy(wait_ev_);
     if (st_) (void)hipStreamDestroy(st_);
@@ -85,12 +86,12 @@ std::recursive_mutex& runtime_mutex() {
 bool Hierarchy::poll() {
     if (!wait_h_) return false;
     hipError_t res = hipSuccess;
-    if (!(wait_seq_ && seq_arrived(wait_seq_))) {
+    if (!(wait_seq_ && seq_arrived(wait_seq_, wait_cols_))) {
         const hipError_t q = hipEventQuery(wait_ev_);
         if (q == hipErrorNotReady) return false;
         // the stream has finished: a published number is visible by now unless it failed
         res = q;
-        if (res == hipSuccess && wait_seq_ && !seq_arrived(wait_seq_)) res = hipErrorUnknown;
+        if (res == hipSuccess && wait_seq_ && !seq_arrived(wait_seq_, wait_cols_)) res = hipErrorUnknown;
     }
     if (wait_slot_) *wait_slot_ = res;
     std::coroutine_handle<> h = wait_h_;
@@ -124,16 +125,16 @@ hipError_t Hierarchy::publish(hipStream_t st, std::initializer_list<HostCopy> it
     return publish_to_host(a, st);
 }
 
-hipError_t Hierarchy::wait_published(unsigned v, hipStream_t st) const {
+hipError_t Hierarchy::wait_published(unsigned v, int cols, hipStream_t st) const {
     const auto t0 = std::chrono::steady_clock::now();
     for (unsigned spin = 1;; ++spin) {
-        if (seq_arrived(v)) return hipSuccess;
+        if (seq_arrived(v, cols)) return hipSuccess;
         if ((spin & 1023u) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(kSpinMs)) break;
     }
     // long GPU work (or a failure): block in the runtime instead of spinning
     const hipError_t e = hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
-    return seq_arrived(v) ? hipSuccess : hipErrorUnknown;
+    return seq_arrived(v, cols) ? hipSuccess : hipErrorUnknown;
 }
 
 void Hierarchy::clear_graphs() {
@@ -561,12 +562,17 @@ Task Hierarchy::gcr_plain(int l, const cpx<T>* b, cpx<T>* x, int ncol, double to
         }
         // solution update, and the next cycle continues from the recursive residual (its
         // norm and the stop flags are those of the last fused step)
-        if (ss) HIPCHK(ss_finish<T>(V, kmax, x, n, ncol, c_ss, tol2, false, g, rw_, st));
-        else HIPCHK(gcr_solve_xupdate_restart<T>(P, nt, kmax, x, n, ncol, r, (kmax % 2 == 0) ? g.stop : g.stop2, g,
+        if (ss) {
+            // (the finaliser itself tells the host, so that the next launches are on their way
+            // while the update runs)
+            HIPCHK(ss_finish<T>(V, kmax, x, n, ncol, c_ss, tol2, false, g, rw_, st, SsPublish{d_col_, d_pub_ctr_}));
+            return DWF_OK;
+        }
+        HIPCHK(gcr_solve_xupdate_restart<T>(P, nt, kmax, x, n, ncol, r, (kmax % 2 == 0) ? g.stop : g.stop2, g,
                                                  st));
-        // the cycle ends by publishing the stop flags to the host (part of the graph)
+        // the cycle ends by publishing the columns' state to the host (part of the graph)
         unsigned v = 0;
-        HIPCHK(publish(st, {{h_int_, g.stop, sizeof(int) * ncol}}, &v));
+        HIPCHK(publish(st, {{h_int_, g.stop, sizeof(int) * ncol}, {h_int_ + ncol, g.it, sizeof(int) * ncol}}, &v));
         return DWF_OK;
     };
     const int max_cycles = std::max(1, (maxit + kmax - 1) / kmax);
@@ -576,15 +582,19 @@ Task Hierarchy::gcr_plain(int l, const cpx<T>* b, cpx<T>* x, int ncol, double to
         } else if (int e = cycle()) {
             co_return e;
         }
-        // a replayed cycle publishes without the host's count seeing the launch
-        if (use_graphs_ && st == st_) ++pub_;
-        CO_HIPCHK(co_await wait_for(st, pub_));
+        // a replayed cycle, and the s-step finaliser, publish without the host's count seeing the launch
+        if (ss || (use_graphs_ && st == st_)) ++pub_;
+        CO_HIPCHK(co_await wait_for(st, pub_, ss ? ncol : 0));
         bool all = true;
-        for (int cc = 0; cc < ncol; ++cc)
+        for (int cc = 0; cc < ncol; ++cc) {
+            if (ss) {
+                h_int_[cc] = ss_word_stop(h_col_[cc]);
+                h_int_[ncol + cc] = ss_word_it(h_col_[cc]);
+            }
             if (h_int_[cc] == 0) all = false;
+        }
         if (all) break;
     }
-    CO_HIPCHK(co_await read_back(st, {{h_int_, g.stop, sizeof(int) * ncol}, {h_int_ + ncol, g.it, sizeof(int) * ncol}}));
     int it = 0, status = DWF_OK;
     for (int cc = 0; cc < ncol; ++cc) {
         it = std::max(it, h_int_[ncol + cc]);
@@ -812,7 +822,7 @@ int Hierarchy::null_vectors(int l, const cpx<double>* start, cpx<double>* v, hip
         }
         unsigned v = 0;
         HIPCHK(publish(st, {{h_cg_, s, sizeof(CgScal) * nv}}, &v));
-        HIPCHK(wait_published(v, st));
+        HIPCHK(wait_published(v, 0, st));
         bool all = true;
         for (int c = 0; c < nv; ++c) if (!h_cg_[c].done) all = false;
         if (all) break;
@@ -991,6 +1001,9 @@ int Hierarchy::setup(const cpx<double>* U, int Lx, int Ly, int Ls, double m_, do
         HIPCHK(hipHostMalloc((void**)&h_int_, sizeof(int) * 4 * hc, hipHostMallocCoherent));
         HIPCHK(hipHostMalloc((void**)&h_cg_, sizeof(CgScal) * hc, hipHostMallocCoherent));
         HIPCHK(hipHostMalloc((void**)&h_seq_, 64, hipHostMallocCoherent));
+        HIPCHK(hipHostMalloc((void**)&h_col_, sizeof(unsigned long long) * hc, hipHostMallocCoherent));
+        HIPCHK(hipHostGetDevicePointer((void**)&d_col_, h_col_, 0));
+        for (int c = 0; c < hc; ++c) h_col_[c] = 0;
         void* hp[4] = {h_scal_, h_int_, h_cg_, h_seq_};
         const size_t hb[4] = {sizeof(double) * 4 * hc, sizeof(int) * 4 * hc, sizeof(CgScal) * hc, 64};
         for (int i = 0; i < 4; ++i) {

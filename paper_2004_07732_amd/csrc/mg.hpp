@@ -156,6 +156,8 @@ private:
     int* h_int_ = nullptr;
     CgScal* h_cg_ = nullptr;
     unsigned* h_seq_ = nullptr;
+    unsigned long long* h_col_ = nullptr;   // one word per column from the s-step finaliser (SsPublish)
+    unsigned long long* d_col_ = nullptr;   // its device view
     struct HostView { char* host = nullptr; char* dev = nullptr; size_t bytes = 0; };
     HostView views_[4];
     unsigned pub_ = 0;            // sequence number of the last publishing launch enqueued
@@ -195,6 +197,7 @@ private:
     std::coroutine_handle<> wait_h_{};
     hipError_t* wait_slot_ = nullptr;
     unsigned wait_seq_ = 0;       // batch mode: the sequence number a suspended read waits for
+    int wait_cols_ = 0;           // and whose (see seq_arrived)
     // Scalar read-back: a one-wavefront kernel stores the device words into the host
     // mirrors and then a new sequence number (publish_to_host); the host spins on the
     // number for up to kSpinMs (a stream synchronisation after that).  About 8 us
@@ -203,20 +206,27 @@ private:
     struct HostCopy { void* host; const void* dev; size_t bytes; };
     static constexpr int kSpinMs = 20;
     hipError_t publish(hipStream_t st, std::initializer_list<HostCopy> items, unsigned* value);
-    bool seq_arrived(unsigned v) const { return __atomic_load_n(h_seq_, __ATOMIC_ACQUIRE) == v; }
-    hipError_t wait_published(unsigned v, hipStream_t st) const;
+    // number v has come: from the publishing launch, or with cols > 0 in the words of so many columns
+    bool seq_arrived(unsigned v, int cols) const {
+        if (cols == 0) return __atomic_load_n(h_seq_, __ATOMIC_ACQUIRE) == v;
+        for (int c = 0; c < cols; ++c)
+            if (ss_word_seq(__atomic_load_n(&h_col_[c], __ATOMIC_ACQUIRE)) != v) return false;
+        return true;
+    }
+    hipError_t wait_published(unsigned v, int cols, hipStream_t st) const;
     struct HostRead {
         Hierarchy* h;
         hipStream_t st;
         unsigned v;
+        int cols;
         hipError_t err;
         bool await_ready() {
             if (err != hipSuccess) return true;
             if (!h->batch_) {
-                err = h->wait_published(v, st);
+                err = h->wait_published(v, cols, st);
                 return true;
             }
-            if (h->seq_arrived(v)) return true;
+            if (h->seq_arrived(v, cols)) return true;
             err = hipEventRecord(h->wait_ev_, st);   // lets poll() tell a finished stream from a slow one
             return err != hipSuccess;
         }
@@ -224,16 +234,17 @@ private:
             h->wait_h_ = c;
             h->wait_slot_ = &err;
             h->wait_seq_ = v;
+            h->wait_cols_ = cols;
         }
         hipError_t await_resume() const { return err; }
     };
     HostRead read_back(hipStream_t st, std::initializer_list<HostCopy> items) {
         unsigned v = 0;
         const hipError_t e = publish(st, items, &v);
-        return HostRead{this, st, v, e};
+        return HostRead{this, st, v, 0, e};
     }
     // wait for a number whose publishing launch is already enqueued (inside a graph)
-    HostRead wait_for(hipStream_t st, unsigned v) { return HostRead{this, st, v, hipSuccess}; }
+    HostRead wait_for(hipStream_t st, unsigned v, int cols) { return HostRead{this, st, v, cols, hipSuccess}; }
     struct StreamWait {
         Hierarchy* h;
         hipStream_t st;
