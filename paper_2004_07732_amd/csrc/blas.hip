@@ -978,11 +978,14 @@ __global__ void __launch_bounds__(kSsThreads) k_ss_dots(SsVecs<T> P, size_t nw, 
 }
 
 // One workgroup per column: wave w adds the partials of blocks w, w + 16, ... (lane = sum), then
-// wave 0 factors G by Cholesky with lane i holding row i.  The residual norm after step k is
+// wave 0 factors G by Cholesky, an entry per lane.  The residual norm after step k is
 // |r0|^2 - sum_{i<=k} |u_i|^2 (u = L^-1 b), so a tolerance met inside the cycle ends it at that
 // step: the coefficients are those of its leading block.  Below kSsTrust of the cycle's start that
 // difference is rounding; the next cycle's |P_0|^2 then decides.  A pivot within rounding of zero
 // against its direction's own norm drops that direction.
+// The work is small and runs once, so its time is that of fetching code and of waits in turn: unrolled
+// over one row per lane it was 11 KB at 6 steps (16 KB at 8) and took 7.9 us (12.7); one entry
+// per lane in rolled loops, 4 KB, and state and partials in flight together, 7.0 (9.6).
 constexpr int kSsFinWaves = 16;
 constexpr double kSsPivot = 1e-13;
 constexpr double kSsTrust = 1e-12;
@@ -993,14 +996,9 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
     constexpr int NR = (NQ + 63) / 64;
     __shared__ double sp[kSsFinWaves][NQ];
     __shared__ double H[NQ];
-    __shared__ cpx<double> sL[K][K];
     const int col = blockIdx.x;
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const double* part = rw.partial + (size_t)col * rw.max_q * rw.nblk;
-    const int flag0 = first ? 0 : g.stop[col];
-    const int it0 = first ? 0 : g.it[col];
-    const double bb0 = first ? -1.0 : g.bb[col];
-    const unsigned seq = pub.word ? *pub.ctr + 1u : 0u;
     static_assert(kSsBlocks % kSsFinWaves == 0);
     constexpr int NB = kSsBlocks / kSsFinWaves;
     double pv[NR][NB];   // all of a lane's partials in flight together
@@ -1013,6 +1011,13 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
             pv[r][j] = part[(size_t)(b < nb ? b : 0) * NQ + q];
         }
     }
+    // (the state is loaded with the partials, whatever `first` says, by vector loads - an offset
+    // the compiler cannot see through - which it does not move behind the barriers: nothing waits in turn)
+    int z;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(z));
+    const int stop = g.stop[col + z], iters = g.it[col + z];
+    const double bbs = g.bb[col + z];
+    const unsigned ctr = (pub.ctr ? pub.ctr : reinterpret_cast<const unsigned*>(g.stop))[z];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         double s = 0.0;
@@ -1029,6 +1034,10 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
     }
     __syncthreads();
     if (wid != 0) return;
+    const int flag0 = first ? 0 : __builtin_amdgcn_readfirstlane(stop);
+    const int it0 = first ? 0 : iters;
+    const double bb0 = first ? -1.0 : bbs;
+    const unsigned seq = ctr + 1u;
     double* coef = g.tot + (size_t)col * kGcrTot;   // y_i / c (2 K), then P_0's change (2 K + 2), then the live flag
     bool sane = true;
 #pragma unroll
@@ -1054,87 +1063,74 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
         }
         return;
     }
+    // lane 8 i + l: entry (i, l) of G; a row's b, u and y in all of its lanes (rows and columns
+    // past the last repeat it; their values go nowhere)
     auto h = [&](int a, int b) -> cpx<double> {
-        if (a == b) return {H[a], 0.0};
-        const int q = a < b ? ss_off(K, a, b) : ss_off(K, b, a);
-        return {H[q], a < b ? H[q + 1] : -H[q + 1]};
+        const int lo = min(a, b), hi = max(a, b), q = a == b ? a : ss_off(K, lo, hi);
+        const double re = H[q], im = H[q + 1];
+        return {re, a == b ? 0.0 : (a < b ? im : -im)};
     };
-    const int i = lane < K ? lane : K - 1;   // (lanes past the last row repeat it)
-    cpx<double> G[K], bi = h(i + 1, 0) + h(i, 0);
-    double dg = 0.0;
-#pragma unroll
-    for (int l = 0; l < K; ++l) {
-        G[l] = h(i + 1, l + 1) + h(i + 1, l) + h(i, l + 1) + h(i, l);
-        if (l == i) dg = G[l].re;
-    }
-    // value of lane l, the same for the whole wave
-    auto bcast = [](double x, int l) {
+    auto bcast = [](double x, int l) {   // lane l's value, the same for the whole wave
         const int lo = __builtin_amdgcn_readlane(__double2loint(x), l), hi = __builtin_amdgcn_readlane(__double2hiint(x), l);
         return __hiloint2double(hi, lo);
     };
-    double rr = rr0, inv[K];
-    cpx<double> u[K];
+    auto from = [](cpx<double> z, int l) -> cpx<double> { return {__shfl(z.re, l), __shfl(z.im, l)}; };
+    const int row = lane >> 3, colm = lane & 7;
+    const int i = row < K ? row : K - 1, l = colm < K ? colm : K - 1;
+    cpx<double> G = h(i + 1, l + 1) + h(i + 1, l) + h(i, l + 1) + h(i, l);
+    cpx<double> bi = h(i + 1, 0) + h(i, 0);
+    const double dg = G.re;
+    cpx<double> L = {0.0, 0.0}, u = {0.0, 0.0};
+    double rr = rr0, inv = 0.0;
     int kend = 0;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        inv[k] = 0.0;
-        u[k] = {0.0, 0.0};
-        if (flag == 0) {   // (uniform)
-            const double d = bcast(G[k].re, k), d0 = bcast(dg, k);
-            const bool ok = d > kSsPivot * d0 && finite(d);
-            inv[k] = ok ? rsqrt(d) : 0.0;
-            u[k] = {bcast(bi.re, k) * inv[k], bcast(bi.im, k) * inv[k]};
-            const cpx<double> lk = {G[k].re * inv[k], G[k].im * inv[k]};   // L_ik of this lane's row
-            if (lane < K) sL[i][k] = lk;
-#pragma unroll
-            for (int l = k + 1; l < K; ++l) {   // G_il -= L_ik conj(L_lk)
-                const cpx<double> ll = {bcast(lk.re, l), bcast(lk.im, l)};
-                G[l].re -= lk.re * ll.re + lk.im * ll.im;
-                G[l].im -= lk.im * ll.re - lk.re * ll.im;
-            }
-            bi.re -= lk.re * u[k].re - lk.im * u[k].im;
-            bi.im -= lk.re * u[k].im + lk.im * u[k].re;
-            rr -= u[k].re * u[k].re + u[k].im * u[k].im;
-            kend = k + 1;
-            if (!finite(rr)) flag = 2;
-            else if (rr <= tol2 * bb && rr > kSsTrust * rr0) flag = 1;
+#pragma unroll 1
+    for (int k = 0; k < K && flag == 0; ++k) {   // (uniform)
+        const double d = bcast(G.re, 9 * k), d0 = bcast(dg, 9 * k);
+        const double ik = d > kSsPivot * d0 && finite(d) ? rsqrt(d) : 0.0;
+        const cpx<double> uk = {bcast(bi.re, 8 * k) * ik, bcast(bi.im, 8 * k) * ik};
+        cpx<double> lk = from(G, (i << 3) + k), ll = from(G, (l << 3) + k);   // L_ik and L_lk
+        lk = {lk.re * ik, lk.im * ik};
+        ll = {ll.re * ik, ll.im * ik};
+        if (l == k) L = lk;
+        if (i == k) { u = uk; inv = ik; }
+        G.re -= lk.re * ll.re + lk.im * ll.im;   // G_il -= L_ik conj(L_lk)
+        G.im -= lk.im * ll.re - lk.re * ll.im;
+        bi.re -= lk.re * uk.re - lk.im * uk.im;
+        bi.im -= lk.re * uk.im + lk.im * uk.re;
+        rr -= uk.re * uk.re + uk.im * uk.im;
+        kend = k + 1;
+        if (!finite(rr)) flag = 2;
+        else if (rr <= tol2 * bb && rr > kSsTrust * rr0) flag = 1;
+    }
+    cpx<double> y = {0.0, 0.0};
+    if (flag != 2) {
+#pragma unroll 1
+        for (int k = kend - 1; k >= 0; --k) {   // L^H y = u over the steps taken
+            const double ik = bcast(inv, 8 * k);
+            const cpx<double> yk = {bcast(u.re, 8 * k) * ik, bcast(u.im, 8 * k) * ik};
+            const cpx<double> t = cjmul(from(L, (k << 3) + i), yk);
+            if (i == k) y = yk;
+            u.re -= t.re;
+            u.im -= t.im;
         }
     }
-    if (lane != 0) return;
-    cpx<double> Lr[K][K];   // (columns of steps not taken are never stored; their values go unused)
-#pragma unroll
-    for (int k = 0; k < K; ++k)
-#pragma unroll
-        for (int l = k + 1; l < K; ++l) Lr[l][k] = sL[l][k];
-    cpx<double> y[K + 1];
-    y[K] = {0.0, 0.0};
-#pragma unroll
-    for (int k = K - 1; k >= 0; --k) {   // L^H y = u over the steps taken
-        cpx<double> acc = u[k];
-#pragma unroll
-        for (int l = k + 1; l < K; ++l) {
-            if (l < kend) {
-                const cpx<double> t = cjmul(Lr[l][k], y[l]);
-                acc.re -= t.re;
-                acc.im -= t.im;
-            }
-        }
-        y[k] = {acc.re * inv[k], acc.im * inv[k]};
-        if (k >= kend || flag == 2) y[k] = {0.0, 0.0};
-    }
-    double* e = coef + 2 * K;
-#pragma unroll
-    for (int k = 0; k <= K; ++k) {
-        const cpx<double> prev = k > 0 ? y[k - 1] : cpx<double>{0.0, 0.0};
-        e[2 * k] = -(y[k].re + prev.re);
-        e[2 * k + 1] = -(y[k].im + prev.im);
-        if (k < K) {
-            coef[2 * k] = y[k].re * inv_c;
-            coef[2 * k + 1] = y[k].im * inv_c;
+    const cpx<double> up = from(y, i > 0 ? (i - 1) << 3 : 0);
+    const cpx<double> prev = i > 0 ? up : cpx<double>{0.0, 0.0};
+    if (row < K && colm == 0) {
+        coef[2 * i] = y.re * inv_c;
+        coef[2 * i + 1] = y.im * inv_c;
+        double* e = coef + 2 * K;
+        e[2 * i] = -(y.re + prev.re);
+        e[2 * i + 1] = -(y.im + prev.im);
+        if (i == K - 1) {
+            e[2 * K] = -y.re;
+            e[2 * K + 1] = -y.im;
         }
     }
-    coef[kGcrTot - 1] = flag == 2 ? 0.0 : 1.0;
-    leave(flag, it0 + kend);
+    if (lane == 0) {
+        coef[kGcrTot - 1] = flag == 2 ? 0.0 : 1.0;
+        leave(flag, it0 + kend);
+    }
 }
 
 template <typename T, int K>
