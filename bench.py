@@ -249,7 +249,7 @@ def coarse_mfma_per_launch(nsites, n, Ls_c, ncol, tw=None):
     return nsites * (n // 16) * ntile * 2 * (5 * n // 16)
 
 
-GRAM_STEPS = 6   # longest smoother cycle the library runs in the Gram form
+GRAM_STEPS = 6   # longest cycle of the step-by-step Gram form in the models below (the s-step form's: sstep_model_bytes)
 
 
 def smoother_model_passes(ns, ks):
@@ -300,6 +300,31 @@ def solve_model_bytes(fine_applies, coarse_iters, k, L, Ls, coarse_a, coarse_vec
     return (fine_applies * fine_apply + coarse_iters * coarse_a
             + coarse_iters * cycle / k * coarse_vec_bytes
             + kcycles * smoother_model_passes(smooth_iters, smooth_restart) * fine_vec)
+
+
+SSTEP_STEPS = 8   # longest cycle the library runs in the s-step form
+
+
+def sstep_model_bytes(fine_applies, coarse_iters, k, L, Ls, coarse_a, coarse_vec_bytes,
+                      kcycles=0, smooth_iters=0, smooth_restart=0, fused=False):
+    """HBM bytes of one solve whose smoother and coarsest cycles all take the s-step form (at most
+    SSTEP_STEPS steps; None for longer ones), a lower bound as solve_model_bytes is: the fine
+    stencils (with the fused A half of their vector bytes, since an application reads and writes
+    one vector for its two stencils), one coarse A-hat per coarsest iteration, and per cycle of
+    k steps the shift's read of each direction (k), the inner products (k + 1) and the update
+    (k + 1 directions and x read, x and the residual written): 3 k + 5 vector passes.  The
+    smoother's first residual reads its right-hand side once."""
+    ks = smooth_restart if 0 < smooth_restart < smooth_iters else smooth_iters
+    if max(k, ks) > SSTEP_STEPS:
+        return None
+    fine_vec = Ls * L * L * 2 * 8
+    fine_apply = (1 if fused else 2) * fine_vec + 2 * L * L * 8
+    smoother, left = (1 if smooth_iters > 0 else 0), smooth_iters
+    while left > 0:
+        smoother += 3 * min(ks, left) + 5
+        left -= ks
+    return (fine_applies * fine_apply + coarse_iters * coarse_a
+            + coarse_iters * (3 * k + 5) / k * coarse_vec_bytes + kcycles * smoother * fine_vec)
 
 
 def timed(mg, b, steps, warmup, tol=1e-10):
@@ -388,6 +413,12 @@ def stencil_rows(dwfmg, inputs, torch, m, M5):
     return rows
 
 
+def fine_a_fused(dwfmg, L, Ls, ncol):
+    """Whether the solver's timed choice took the fused fine A at this shape (after a solve)."""
+    pick = dwfmg.dwf_fine_a_chosen(L, L, Ls, ncol)
+    return bool(pick) and pick[0] != dwfmg.FINE_A_TWO
+
+
 def fine_a_rows(dwfmg, inputs, torch, mg, L, Ls):
     """Level-0 A = D_PV^dag D_DW of the headline hierarchy (FP32) for 1 and 16 columns:
     HIP-event time per application (median of three runs of 100) with the two stencil
@@ -411,7 +442,7 @@ def fine_a_rows(dwfmg, inputs, torch, mg, L, Ls):
                             "two_launch_us": two, "fused_us": fused[0], "fused_tile": ["16x16", "32x8", "16x8"][fused[1] - 1],
                             "fused_chunk": fused[2], "two_launch_GB_s": nbytes / (two * 1e-6) / 1e9,
                             "fused_GB_s": nbytes / (fused[0] * 1e-6) / 1e9,
-                            "chosen": "fused" if fused[0] * 1.03 < two else "two launches"}
+                            "chosen": "fused" if fine_a_fused(dwfmg, L, Ls, ncol) else "two launches"}
         log(f"[bench] fine A {ncol} rhs: two launches {two:.1f} us, fused {fused[0]:.1f} us "
             f"({out[f'{ncol}rhs']['fused_tile']}, chunk {fused[2]})")
     return out
@@ -599,10 +630,11 @@ def main():
                    "issued_TFLOP_s": issued_tf,
                    "algorithmic_TFLOP_s": useful_tf, "peak_bf16_TFLOP_s": PEAK_BF16_TFLOPS,
                    "frac_issued": issued_tf / PEAK_BF16_TFLOPS, "frac_algorithmic": useful_tf / PEAK_BF16_TFLOPS}
-    solve_bytes = (solve_model_bytes(stats.fine_applies, stats.level_iters[0], args.coarsest_restart, L, Ls,
+    solve_bytes = (sstep_model_bytes(stats.fine_applies, stats.level_iters[0], args.coarsest_restart, L, Ls,
                                      coarse_a_bytes(coarse_bytes, nsites, n, Lsc, 1, vec_bytes),
                                      nsites * Lsc * n * vec_bytes, kcycles=stats.level_calls[0],
-                                     smooth_iters=args.smooth_iters, smooth_restart=args.smooth_restart)
+                                     smooth_iters=args.smooth_iters, smooth_restart=args.smooth_restart,
+                                     fused=fine_a_fused(dwfmg, L, Ls, 1))
                    if args.coarsest == "gcr" and len(wl["nvec"]) == 1 else None)
     solve_roofline = None
     if solve_bytes is not None:
