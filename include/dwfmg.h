@@ -140,7 +140,8 @@ int dwf_fine_a_chosen(int prec, int Lx, int Ly, int Ls, int nrhs, int* shape, in
 
 /* Pauli-Villars forms (Sec. 2.2, eq. NormalExp): see the DWF_PV* modes.  The
  * product modes are one launch where a tile of 32 x 16, 32 x 8, 16 x 16 or 16 x 8 sites
- * divides the lattice and Ls >= 2; elsewhere they use a library-owned intermediate field
+ * divides the lattice and Ls >= 2, unless two are faster (a few FP64 slices on part of the
+ * chip; not under capture); elsewhere they use a library-owned intermediate field
  * (allocated on first use and kept until dwf_release_scratch; a call on one stream waits,
  * on the device, for the previous call's use of it on another).  Same layout rules as
  * dwf_apply.

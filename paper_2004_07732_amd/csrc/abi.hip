@@ -76,6 +76,9 @@ void drop(SharedBuf& b) {
 std::mutex g_scratch_mu;
 SharedBuf g_fields, g_partials;
 
+// a capture that would have to allocate the intermediate field (g_scratch_mu held)
+bool capture_without(const SharedBuf& b, size_t bytes, hipStream_t st) { return bytes > b.bytes && capturing(st); }
+
 template <typename R>
 int pv_apply_t(const void* U, const void* psi, void* out, int Lx, int Ly, int Ls, int nrhs, double m,
                double M5, int mode, hipStream_t st) {
@@ -88,10 +91,12 @@ int pv_apply_t(const void* U, const void* psi, void* out, int Lx, int Ly, int Ls
         case DWF_PVDAG_DW:
         case DWF_PVDAG_DW_DAG: {
             const double m1 = (mode == DWF_PVDAG_DW) ? m : 1.0, m2 = (mode == DWF_PVDAG_DW) ? 1.0 : m;
-            if (fine_product_fits<R>(Lx, Ly, Ls, nrhs))
-                return hip_status(fine_product<R>(u, in, o, Lx, Ly, Ls, nrhs, m1, m2, M5, st));
-            std::lock_guard<std::mutex> lk(g_scratch_mu);
             const size_t bytes = sizeof(cpx<R>) * 2 * (size_t)Lx * Ly * Ls * nrhs;
+            const FineProduct form = fine_product_form<R>(Lx, Ly, Ls, nrhs);
+            auto one = [&] { return hip_status(fine_product<R>(u, in, o, Lx, Ly, Ls, nrhs, m1, m2, M5, st)); };
+            if (form == FineProduct::kOne) return one();
+            std::lock_guard<std::mutex> lk(g_scratch_mu);
+            if (form == FineProduct::kEither && capture_without(g_fields, bytes, st)) return one();
             auto t = reinterpret_cast<cpx<R>*>(acquire(g_fields, bytes, st));
             if (!t) return DWF_EHIP;
             if (fine_dw<R>(u, in, t, nullptr, Lx, Ly, Ls, nrhs, m1, M5, false, nullptr, 1, st) != hipSuccess)
@@ -132,8 +137,8 @@ int pv_poly_apply_t(const void* U, const void* psi, void* out, int Lx, int Ly, i
     auto o = reinterpret_cast<cpx<R>*>(out);
     const size_t n = (size_t)2 * Lx * Ly * Ls * nrhs;
     // p = 1: the product itself, as dwf_pv_apply applies it
-    if (order == 0 && c[0] == 1.0 && fine_product_fits<R>(Lx, Ly, Ls, nrhs))
-        return hip_status(fine_product<R>(u, in, o, Lx, Ly, Ls, nrhs, dag ? 1.0 : m, dag ? m : 1.0, M5, st));
+    if (order == 0 && c[0] == 1.0)
+        return pv_apply_t<R>(U, psi, out, Lx, Ly, Ls, nrhs, m, M5, dag ? DWF_PVDAG_DW_DAG : DWF_PVDAG_DW, st);
     std::lock_guard<std::mutex> lk(g_scratch_mu);
     auto t = reinterpret_cast<cpx<R>*>(acquire(g_fields, sizeof(cpx<R>) * 3 * n, st));
     if (!t) return DWF_EHIP;

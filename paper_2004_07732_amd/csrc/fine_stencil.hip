@@ -704,23 +704,49 @@ static bool a_tile_fits(int shape, int Lx, int Ly) {
 }
 
 // The fused configuration for a shape, or 0 where no tile divides the lattice (two launches).
-// The largest tile has the least ring and margin and measured fastest at every shape (FP64: the
-// largest that LDS holds).  Chunks as long as 4096 wavefronts allow, since each chunk evaluates two
-// slices of t and reads four of psi beyond its own (256^2 x 16 FP32, one column: 12.5 us in chunks
-// of 4, 12.9 of 8; four columns: 26.8 us in one chunk, 31.0 in chunks of 8), and at least 2
-// (128^2 x 16: 6.5 us in chunks of 2, 8.0 of 4).
+// Swept over 19 lattices, Ls 2 .. 32 and 1 .. 16 columns, every tile and chunk against the two
+// launches (graphs of 16 applications):
+//  - a chunk evaluates two slices of t beyond its own, so chunks are the shortest that still give
+//    no more wavefronts than run at once (FP32 4096, FP64 3072: 240^2 x 16 x 4 FP32 28.2 us in one
+//    chunk, 31.5 in two; 256^2 x 8 FP64 14.2 us in chunks of 4, 17.3 of 2), and all of one length
+//    (a few more than that run beside the others: 96 x 88 x 32 x 16 FP32 32 us in two, 41 in one);
+//  - one slice each where even that leaves the chip half empty, since the walk is then the whole
+//    time (64^2 x 4 FP32 4.6 us against 5.8 in chunks of 2; FP64 5.4 against 7.0);
+//  - FP64 chunks of at most 8 while the caches hold the field: more workgroups then help more than
+//    the two slices cost (240^2 x 10 x 2: 0.87 of the time in one chunk; 224 x 248 x 16 x 4: 61 us,
+//    67 in one), and of at most 16 where the slices come from HBM (256^2 x 16 x 16: 270 us, 309 in
+//    chunks of 8; 496 x 504 x 32: 128 us, 142 in chunks of 8 or 32);
+//  - the largest tile has the least ring and margin (FP64: the largest that LDS holds); the smallest
+//    where launch and one walk are the whole time (32^2 x 4 x 16 FP64 6.2 us against 7.2).
 template <typename R>
 static int a_rule(int Lx, int Ly, int Ls, int ncol) {
     if (Ls < 2) return 0;
-    for (int shape : {4, 2, 1, 3}) {
-        if (!a_tile_fits<R>(shape, Lx, Ly)) continue;
-        const ATileShape t = kATiles[shape - 1];
-        const long long waves = (long long)(Lx / t.tx) * (Ly / t.ty) * ncol * (t.tx * t.ty / 64);
-        const long long want = std::min<long long>((4096 + waves - 1) / waves, Ls);
-        const int cs = (int)std::max<long long>(2, (Ls + want - 1) / want);
-        return shape * kCfgStride + std::min(std::min(cs, Ls), kCfgStride - 1);
+    constexpr bool F64 = sizeof(R) == 8;
+    const long long waves = (long long)Lx * Ly / 64 * ncol, total = waves * Ls;   // per slice, in one-slice chunks
+    int shape = 0;
+    for (int s : {4, 2, 1, 3})
+        if ((s == 3 || total > 512) && a_tile_fits<R>(s, Lx, Ly)) { shape = s; break; }
+    if (shape == 0) return 0;
+    int cs = 1;
+    if (total > (F64 && shape != 3 ? 1024 : 2048)) {
+        const bool cached = (double)total * 64 * sizeof(spinor<R>) < 160e6;
+        const int cap = std::min(F64 ? (cached ? 8 : 16) : kCfgStride - 1, Ls);
+        auto fits = [&](int c) { return waves * ((Ls + c - 1) / c) <= (F64 ? 3072 : 4096) + (c < 8 ? 0 : 128); };
+        cs = F64 && Ls == 3 ? 3 : 2;
+        while (cs < cap && !fits(cs)) ++cs;
+        const int nchunk = (Ls + cs - 1) / cs;
+        cs = (Ls + nchunk - 1) / nchunk;
     }
-    return 0;
+    return shape * kCfgStride + cs;
+}
+// Where the two launches are the faster: few FP64 slices on a part of the chip, where neither form
+// is bound by memory and the fused one's two further slices of t show (80 x 88 x 3 x 8: 9.9 us in two
+// launches, 10.6 fused; 64^2 x 3 x 8: 7.1 and 8.1).  Elsewhere in the sweep the fused launch is within
+// 7% of the two launches where it is the slower, and up to 2.7 times as fast.
+template <typename R>
+static bool a_two_faster(int Lx, int Ly, int Ls, int ncol) {
+    const long long total = (long long)Lx * Ly / 64 * ncol * Ls;
+    return sizeof(R) == 8 && (Ls == 3 || Ls == 4) && total > 640 && total <= 2560;
 }
 // fused shapes that a caller may pin (FP64: the one whose LDS fitted a first form of the kernel)
 template <typename R>
@@ -801,7 +827,7 @@ static int tuned_a_cfg(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* t
                        int ncol, double m, double M5, hipStream_t st, bool may_time) {
     std::mutex& mu = g_a_mu;
     std::map<std::string, int>& cache = g_a_cache;
-    const int heuristic = a_rule<R>(Lx, Ly, Ls, ncol);
+    const int heuristic = a_two_faster<R>(Lx, Ly, Ls, ncol) ? 0 : a_rule<R>(Lx, Ly, Ls, ncol);
     const char* en = std::getenv("DWF_AUTOTUNE");
     if (en && en[0] == '0') return heuristic;
     char keyb[128];
@@ -868,7 +894,10 @@ hipError_t fine_a(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* tmp, i
 }
 
 template <typename R>
-bool fine_product_fits(int Lx, int Ly, int Ls, int ncol) { return a_rule<R>(Lx, Ly, Ls, ncol) != 0; }
+FineProduct fine_product_form(int Lx, int Ly, int Ls, int ncol) {
+    if (a_rule<R>(Lx, Ly, Ls, ncol) == 0) return FineProduct::kTwo;
+    return a_two_faster<R>(Lx, Ly, Ls, ncol) ? FineProduct::kEither : FineProduct::kOne;
+}
 
 template <typename R>
 hipError_t fine_product(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, int Lx, int Ly, int Ls, int ncol, double m1,
@@ -1128,8 +1157,8 @@ template hipError_t fine_dw_untimed<float>(const cpx<float>*, const cpx<float>*,
 template hipError_t fine_dw_untimed<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, int, int, int, int, double, double, bool, hipStream_t);
 template hipError_t fine_a<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, cpx<float>*, int, int, int, int, double, double, const int*, int, hipStream_t, const Epi<float>&);
 template hipError_t fine_a<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, cpx<double>*, int, int, int, int, double, double, const int*, int, hipStream_t, const Epi<double>&);
-template bool fine_product_fits<float>(int, int, int, int);
-template bool fine_product_fits<double>(int, int, int, int);
+template FineProduct fine_product_form<float>(int, int, int, int);
+template FineProduct fine_product_form<double>(int, int, int, int);
 template hipError_t fine_product<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, int, int, int, int, double, double, double, hipStream_t);
 template hipError_t fine_product<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, int, int, int, int, double, double, double, hipStream_t);
 template hipError_t wilson2d<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, int, int, int, double, bool, hipStream_t);

@@ -67,10 +67,13 @@ bool set_fine_config(int shape, int chunk);
 template <typename R>
 hipError_t fine_a(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* tmp, int Lx, int Ly, int Ls, int ncol,
                   double m, double M5, const int* skip, int skip_stride, hipStream_t st, const Epi<R>& epi = {});
-// out = D(m2)^dag D(m1) in in one launch without an intermediate field (A: m1 = m, m2 = 1; A^dag:
-// m1 = 1, m2 = m), by a rule on the sizes, never timed; only where fine_product_fits
+// how D(m2)^dag D(m1) is best applied by a rule on the sizes, never timed: in two launches through
+// an intermediate field (no tile divides the lattice), in one, or in two where the field is at hand
+enum class FineProduct { kTwo, kOne, kEither };
 template <typename R>
-bool fine_product_fits(int Lx, int Ly, int Ls, int ncol);
+FineProduct fine_product_form(int Lx, int Ly, int Ls, int ncol);
+// out = D(m2)^dag D(m1) in in one launch without an intermediate field (A: m1 = m, m2 = 1; A^dag:
+// m1 = 1, m2 = m); not where fine_product_form says kTwo
 template <typename R>
 hipError_t fine_product(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, int Lx, int Ly, int Ls, int ncol, double m1,
                         double m2, double M5, hipStream_t st);

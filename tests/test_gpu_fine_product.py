@@ -60,3 +60,37 @@ def test_product_allocates_nothing_under_capture():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want)
+
+
+# one slice per workgroup (16 x 8 tiles, then the largest); a whole fifth dimension of three; FP64 in two
+# launches; chunks of even length below the longest (FP64: 5 + 4 of 9), and one chunk (FP32)
+@pytest.mark.parametrize("Lx,Ly,Ls,nrhs", [(32, 32, 4, 1), (64, 64, 5, 3), (80, 88, 3, 13), (64, 64, 3, 8), (96, 64, 4, 4),
+                                           (128, 128, 9, 13)])
+@pytest.mark.parametrize("dtype", [torch.complex64, torch.complex128])
+def test_products_at_the_lines_of_the_rule(Lx, Ly, Ls, nrhs, dtype):
+    """Every choice of tile and chunk against the two stencils one after the other (the same site
+    arithmetic up to contraction: a few roundings of each site's some 60 terms) and, in the first
+    column, the oracle; then the same under capture, where an intermediate field is not used."""
+    m, M5 = 0.04, -1.1
+    U = inputs.links_from_theta(inputs.random_theta(Lx, Ly, 510))
+    x = inputs.gaussian_field((nrhs, Ls, Ly, Lx, 2), 511)
+    Ut, xt = torch.from_numpy(U).cuda().to(dtype), torch.from_numpy(x).cuda().to(dtype)
+    bar = 1e-13 if dtype == torch.complex128 else 1e-6
+    t = dwfmg.dwf_apply(Ut, xt, m, M5)
+    two = dwfmg.dwf_pv_apply(Ut, t, m, M5, mode=dwfmg.DWF_PV_DAG)
+    got = dwfmg.dwf_pv_apply(Ut, xt, m, M5)
+    assert float((got - two).norm() / two.norm()) < bar
+    Un, xn = Ut.to(torch.complex128).cpu().numpy(), xt[0].to(torch.complex128).cpu().numpy()
+    want = O.pv_dag_dw(Un, xn, m, M5)
+    assert np.linalg.norm(got[0].cpu().numpy() - want) < bar * np.linalg.norm(want)
+    out = torch.empty_like(xt)
+    dwfmg.release_scratch()
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g, stream=s):
+        dwfmg.dwf_pv_apply(Ut, xt, m, M5, out=out)
+    for _ in range(2):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert float((out - two).norm() / two.norm()) < bar
