@@ -302,7 +302,7 @@ def solve_model_bytes(fine_applies, coarse_iters, k, L, Ls, coarse_a, coarse_vec
             + kcycles * smoother_model_passes(smooth_iters, smooth_restart) * fine_vec)
 
 
-SSTEP_STEPS = 8   # longest cycle the library runs in the s-step form
+SSTEP_STEPS = 6   # longest cycle the library runs in the s-step form
 
 
 def sstep_model_bytes(fine_applies, coarse_iters, k, L, Ls, coarse_a, coarse_vec_bytes,

@@ -842,18 +842,18 @@ k_gcr_fused_update(const cpx<T>* W, size_t wstride, cpx<T>* w, cpx<T>* r, cpx<T>
     }
 }
 
-// ---- s-step GCR cycle (cycles of at most kSsMax steps: the smoother's and the coarsest
+// ---- s-step GCR cycle (short cycles, Hierarchy::ss_longest: the smoother's and the coarsest
 // solve's).  The cycle's minimal residual lies in r0 - span{A p : p in K_k(A, r0)}, whatever
 // basis spans the Krylov space, so the directions need no inner product while they are built:
-// P_0 = r0, P_{i+1} = A P_i / c - P_i (the stencil's epilogue; a shift to the middle of the
-// spectrum keeps them well apart), hence A P_i = c v_i with v_i = P_{i+1} + P_i.  One pass
+// P_0 = r0, P_{i+1} = A P_i / c - P_i (the stencil's epilogue; the shift lies inside the
+// spectrum), hence A P_i = c v_i with v_i = P_{i+1} + P_i.  One pass
 // forms H_ab = <P_a, P_b>, one workgroup per column solves G y = b, G_il = <v_i, v_l>,
 // b_i = <v_i, r0>, and one pass updates x += sum y_i P_i / c and
 // P_0 = r0 - sum y_i v_i.  HBM-bound: K + 1 vectors read for the products and K + 2 read and 2
 // written for the update, where a form that orthogonalises or minimises at every step reads
 // j + 2 and j + 2 vectors and writes one at each step j and needs three launches there.
-// 256^2 x 16 FP32, 5 steps: 73 vector passes and 25 launches a cycle before (with the
-// stencils), 42 passes and 13 launches now.
+// 256^2 x 16 FP32, 5 steps, the fused fine A in one launch of 3 passes: 30 vector passes and 8 launches
+// a cycle, against 61 and 20 for a form that minimises at every step.
 namespace {
 // 512 threads: half as many partials to add as 256 would leave for the same waves in flight
 constexpr int kSsThreads = 512;
@@ -984,8 +984,8 @@ __global__ void __launch_bounds__(kSsThreads) k_ss_dots(SsVecs<T> P, size_t nw, 
 // difference is rounding; the next cycle's |P_0|^2 then decides.  A pivot within rounding of zero
 // against its direction's own norm drops that direction.
 // The work is small and runs once, so its time is that of fetching code and of waits in turn: unrolled
-// over one row per lane it was 11 KB at 6 steps (16 KB at 8) and took 7.9 us (12.7); one entry
-// per lane in rolled loops, 4 KB, and state and partials in flight together, 7.0 (9.6).
+// over one row per lane it was 11 KB at 6 steps and took 7.9 us; one entry per lane in rolled
+// loops, 4 KB, and state and partials in flight together, 7.0.
 constexpr int kSsFinWaves = 16;
 constexpr double kSsPivot = 1e-13;
 constexpr double kSsTrust = 1e-12;

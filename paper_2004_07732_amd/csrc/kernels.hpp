@@ -249,7 +249,12 @@ hipError_t gcr_fused_step(const cpx<T>* W, size_t wstride, int j, cpx<T>* w, cpx
 // that step's correction and stops (stop 1; 2 if a value is not finite), and g.it counts the
 // steps it took.  A stopped column takes no update.  `first` starts the column state afresh
 // (|b|^2 = |P_0|^2); otherwise ss_begin (P_0 = b, x = 0) or the previous cycle left it.
-constexpr int kSsMax = 8;
+// The directions' condition grows by a factor of 10 a step and the form squares it, so the rounding of
+// a direction or of A counts several times over in the coefficients (4 times at 5 steps, 8 at 6, 30 to
+// 40 at 8): more than kSsMax steps take the orthogonalising form, and Hierarchy::ss_longest says how
+// many are as accurate as that form on a level.
+constexpr int kSsMax = 6;
+constexpr int kSsMaxF32 = 2;
 constexpr int kSsBlocks = 256;
 template <typename T> struct SsVecs { cpx<T>* p[kSsMax + 1]; };
 // With `word` set the finaliser also tells the host each column's state, before the update runs: one

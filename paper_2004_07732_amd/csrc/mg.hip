@@ -460,7 +460,7 @@ Task Hierarchy::cgnr(int l, const cpx<T>* b, cpx<T>* x, int ncol, hipStream_t st
 // (3 + M5) minus hops of norm at most 2, the fifth-dimension hop has norm max(1, |m|), and
 // the coarse kernels are their Galerkin projections, so |A| <= B^2 with B the sum; A's
 // spectrum lies in the right half-plane.  Directions shifted to about a third of the
-// bound stay well apart while low modes do not drown in the shift: the residual's drift over
+// bound lose least over sources of all kinds: the residual's drift over
 // 20 steps in cycles of 5 in FP32 measured 3.8e-7 |r0| (1.4e-6 on a source of low modes) against
 // 2.2e-7 (1.3e-6) for directions that minimise at every step, 3.5e-6 (unshifted), and 2.1e-7 (3.5e-6)
 // at half the bound.  A power of two, so that the division by c is exact.
@@ -480,9 +480,25 @@ double Hierarchy::ss_shift(int l) const {
     return std::isfinite(c) && c > 1e-30 && c < 1e30 ? std::exp2(std::round(std::log2(c))) : 1.0;
 }
 
+// The s-step form amplifies rounding where the orthogonalising one does not, so it is taken up to the
+// length at which a K-cycle is no further from the same K-cycle in FP64 (64^2 x 8 and 72 x 48 x 12, FP32
+// smoother, the residual of its result, sources of Gaussian noise, of low modes and outer residuals):
+//  - with 16-bit coarse links their rounding is all the difference (1e-3 to 1e-5 of the result):
+//    1.00 of the orthogonalising form's at every length up to 6, 1.07 in two cycles of 8;
+//  - with FP32 or FP64 links under FP32 vectors 1.00 at 2 steps, 1.04 at 3, 1.1 at 4, 1.35 at 5, 2.0 at
+//    6, 7 at 8; the same holds for FP32 links under FP64 vectors;
+//  - with everything in FP64 the factor is on 1e-16.
+int Hierarchy::ss_longest(int l) const {
+    auto narrow = [](int p) { return p == P_BF16 || p == P_F16; };
+    const int own = l > 0 ? prm.link_prec[l - 1] : P_F64;            // the level's own links
+    const int below = prm.link_prec[std::min(l, prm.nlevels - 1)];   // the next coarser level's
+    if (narrow(own) || narrow(below)) return kSsMax;
+    return levels[l].vec_prec == P_F32 || own == P_F32 ? kSsMaxF32 : kSsMax;
+}
+
 // ------------------------------------------------------------ restarted GCR (coarsest level)
 // Unpreconditioned GCR(kmax) on A with every decision on the device: cycles of at most
-// kSsMax iterations take the s-step form (ss_finish: the directions first, then the
+// ss_longest iterations take the s-step form (ss_finish: the directions first, then the
 // cycle's minimal residual in three launches, with the stop decision after every step);
 // longer ones run kmax fused iterations that orthogonalise, whose accuracy does not depend on
 // the directions' condition, and whose kernels turn into no-ops for converged columns.  Either
@@ -507,7 +523,7 @@ Task Hierarchy::gcr_plain(int l, const cpx<T>* b, cpx<T>* x, int ncol, double to
     cpx<T>* t = C<T>(w.tmp);
     GcrDev& g = w.gcr;
     const double tol2 = tol * tol;
-    const bool ss = kmax <= kSsMax;
+    const bool ss = kmax <= ss_longest(l);
     const double c_ss = ss_shift(l);
     SsVecs<T> V{};
     if (ss) {
@@ -621,11 +637,11 @@ int Hierarchy::smooth(int l, const cpx<T>* r, cpx<T>* z, int ncol, hipStream_t s
     // that all ns steps are taken.  With a restart length ks < ns the steps run in cycles of ks
     // (the orthogonalisation cost of a step grows with its index in the cycle); each cycle
     // adds its correction to z and the next starts from the recursive residual.  Cycles of at
-    // most kSsMax steps take the s-step form, the residual in P_0; longer ones the
+    // most ss_longest steps take the s-step form, the residual in P_0; longer ones the
     // orthogonalising form, whose accuracy does not depend on the directions' condition.
     const int ks = w.kscycle;
     GcrDev& g = w.gsm;
-    const bool ss = ks <= kSsMax;
+    const bool ss = ks <= ss_longest(l);
     const double c_ss = ss_shift(l);
     SsVecs<T> V{};
     if (ss)

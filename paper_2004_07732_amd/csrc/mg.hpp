@@ -320,8 +320,9 @@ private:
                                              const int* skip = nullptr);
     template <typename T> hipError_t apply_A(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp, int ncol,
                                              hipStream_t st, const int* skip = nullptr, const Epi<T>& epi = {});
-    // shift of the s-step Krylov directions on level l
+    // shift of the s-step Krylov directions on level l, and the longest cycle that takes that form
     double ss_shift(int l) const;
+    int ss_longest(int l) const;
     template <typename T> hipError_t apply_Adag(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp, int ncol,
                                                 hipStream_t st, const int* skip = nullptr, const Epi<T>& epi = {});
     template <typename T> hipError_t apply_wilson(int l, const cpx<T>* in, cpx<T>* out, double mass,

@@ -92,3 +92,78 @@ def test_exhausted_krylov_space():
     rc = o.restrict(0, r[0])
     want = o.prolong(0, np.linalg.solve(A, rc.reshape(-1)).reshape(rc.shape))
     assert np.linalg.norm(got - want) < 1e-9 * np.linalg.norm(want)
+
+
+def krylov_min_residual(A, r, steps, restart):
+    """`steps` minimal-residual steps in cycles of `restart` on an orthonormal Krylov basis, FP64."""
+    x, left = np.zeros_like(r), steps
+    while left > 0:
+        k = min(restart or steps, left)
+        left -= k
+        q = [r / np.linalg.norm(r)]
+        while True:
+            w = A(q[-1])
+            if len(q) == k:
+                break
+            for _ in range(2):
+                for v in q:
+                    w = w - np.vdot(v, w) * v
+            q.append(w / np.linalg.norm(w))
+        W = np.stack([A(v).reshape(-1) for v in q], 1)
+        y = np.linalg.lstsq(W, r.reshape(-1), rcond=None)[0]
+        x = x + sum(c * v for c, v in zip(y, q))
+        r = r - (W @ y).reshape(r.shape)
+    return x
+
+
+@pytest.mark.parametrize("link", ["f64", "f16"])
+@pytest.mark.parametrize("nrhs", [1, 3])
+@pytest.mark.parametrize("steps,restart", [(1, 0), (2, 0), (3, 0), (4, 0), (5, 0), (6, 0), (7, 0), (8, 0), (5, 2), (13, 5),
+                                           (12, 6), (14, 7), (16, 8)])
+def test_fp32_smoother_rounding(steps, restart, nrhs, link):
+    """The smoother alone (a source that vanishes on both walls restricts to zero) in FP32 against FP64:
+    the residual of its result.  Bar: an application of A rounds some 30 times per site, 3 u of its
+    size together, and the steps' errors add up at random: 3 u sqrt(steps + 1); with 16-bit coarse
+    links, whose own rounding is 2^-12, cycles of up to 6 steps may amplify that by 8."""
+    Ls, L, m = 6, 16, 0.05
+    U = inputs.metropolis_u1(L, L, 6.0, 30, 940).U
+    lp = dwfmg.P_F64 if link == "f64" else dwfmg.P_F16
+    p = dwfmg.MGParams(nvec=[4], block=[(4, 4)], Ls_coarse=[2], link_prec=[lp], vec_prec=[dwfmg.P_F64],
+                       fine_prec=dwfmg.P_F32, setup_iters=0, smooth_iters=steps, smooth_restart=restart)
+    mg = dwfmg.MG(T(U), Ls, m, -1.0, p, [T(inputs.gaussian_field((4, L, L, 2), 941))], max_nrhs=nrhs)
+    r = inputs.gaussian_field((nrhs, Ls, L, L, 2), 942).astype(np.complex64).astype(np.complex128)
+    r[:, 0] = r[:, -1] = 0.0
+    got = mg.level_op(0, dwfmg.MG_OP_KCYCLE, T(r), nrhs).cpu().numpy()
+    bar = 3 * 2.0 ** -24 * np.sqrt(steps + 1) * (8 if link == "f16" and (restart or steps) <= 6 else 1)
+    A = lambda v: O.pv_dag_dw(U, v, m, -1.0)  # noqa: E731
+    for c in range(nrhs):
+        want = krylov_min_residual(A, r[c], steps, restart)
+        assert np.linalg.norm(A(got[c] - want)) < bar * np.linalg.norm(r[c])
+
+
+@pytest.mark.parametrize("link", ["f16", "f32"])
+@pytest.mark.parametrize("restart", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_fp32_coarsest_cycles_stop_at_the_step(restart, link):
+    """test_coarsest_cycles_stop_at_the_step with FP32 vectors, against the operator as the device
+    applies it (its columns).  Bar: some tens of steps at u = 2^-24, amplified by at most 8, through
+    a correction whose condition is below 100 at m = 0.3: 1e-4."""
+    tol, m, Ls, L = 0.2, 0.3, 4, 16
+    U = inputs.metropolis_u1(L, L, 6.0, 30, 950).U
+    lp = dwfmg.P_F16 if link == "f16" else dwfmg.P_F32
+    p = dwfmg.MGParams(nvec=[4], block=[(4, 4)], Ls_coarse=[2], link_prec=[lp], vec_prec=[dwfmg.P_F32], setup_iters=0,
+                       smooth_iters=0, coarsest_solver=dwfmg.COARSEST_GCR, coarsest_restart=restart, coarsest_tol=tol)
+    start = inputs.gaussian_field((4, L, L, 2), 951)
+    mg = dwfmg.MG(T(U), Ls, m, -1.0, p, [T(start)], max_nrhs=64)
+    o = O.MG(U, Ls, m, -1.0, O.MGParams(levels=[O.LevelParams(nvec=4, block=(4, 4), Ls=2, setup_iters=0)], smooth_iters=0),
+             [start])
+    n = 2 * 4 * 4 * 8
+    eye = np.eye(n, dtype=np.complex128).reshape(n, 2, 4, 4, 8)
+    A = np.concatenate([mg.level_op(1, dwfmg.MG_OP_A, T(eye[c:c + 64]), 64).cpu().numpy().reshape(64, n)
+                        for c in range(0, n, 64)]).T
+    r = inputs.gaussian_field((3, Ls, L, L, 2), 952)
+    r[2] *= 1e-6
+    got = mg.level_op(0, dwfmg.MG_OP_KCYCLE, T(r), 3).cpu().numpy()
+    for c in range(3):
+        rc = o.restrict(0, r[c])
+        want = o.prolong(0, gcr(A, rc.reshape(-1), restart, tol).reshape(rc.shape))
+        assert np.linalg.norm(got[c] - want) < 1e-4 * np.linalg.norm(want)
