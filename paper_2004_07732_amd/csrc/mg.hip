@@ -59,7 +59,6 @@ template <typename T> inline const cpx<T>* C(const void* p) { return reinterpret
 template <typename T> constexpr int prec_of() { return std::is_same<T, float>::value ? P_F32 : P_F64; }
 constexpr int kCgChunk = 16;
 const int kSkipStride = (int)(sizeof(CgScal) / sizeof(int));
-inline const int* cg_skip(const CgScal* s) { return s ? &s[0].done : nullptr; }
 }  // namespace
 
 Hierarchy::~Hierarchy() {
@@ -173,24 +172,24 @@ int Hierarchy::run_graph(const GraphKey& key, hipStream_t st, F&& enqueue) {
 // ------------------------------------------------------------ level operators
 template <typename T>
 hipError_t Hierarchy::apply_dw(int l, const cpx<T>* in, cpx<T>* out, double mass, bool dag, int ncol,
-                               hipStream_t st, const int* skip, const Epi<T>& epi) {
+                               hipStream_t st, Skip skip, const Epi<T>& epi) {
     const Level& L = levels[l];
-    const int stride = skip ? kSkipStride : 1;
     if (L.fine) {
         const cpx<T>* U;
         if constexpr (std::is_same<T, float>::value) U = L.U32; else U = L.U64;
-        return fine_dw<T>(U, in, out, epi.b, L.Lx, L.Ly, L.Ls, ncol, mass, M5, dag, skip, stride, st, epi.alpha,
-                          epi.beta);
+        return fine_dw<T>(U, in, out, epi.b, L.Lx, L.Ly, L.Ls, ncol, mass, M5, dag, skip.flags, skip.stride, st,
+                          epi.alpha, epi.beta);
     }
     CoarseGeom g{L.Lx, L.Ly, L.Ls, L.n};
-    return coarse_apply<T>(L.links, L.link_prec, in, out, g, ncol, mass, M5, dag, false, 0.0, skip, stride, st, epi);
+    return coarse_apply<T>(L.links, L.link_prec, in, out, g, ncol, mass, M5, dag, false, 0.0, skip.flags, skip.stride, st,
+                           epi);
 }
 
 // Polynomial correction of the PV preconditioning (remark after eq. NormalExp,
 // App. A): y = p(X) w, X = D_PV D_PV^dag, by Horner's scheme (y = c_K w, then
 // y = c_k w + X y), on the fine level
 template <typename T>
-hipError_t Hierarchy::pv_poly(const cpx<T>* w, cpx<T>* y, cpx<T>* z, int ncol, hipStream_t st, const int* skip) {
+hipError_t Hierarchy::pv_poly(const cpx<T>* w, cpx<T>* y, cpx<T>* z, int ncol, hipStream_t st, Skip skip) {
     const int K = prm.pv_poly_order;
     const size_t n = levels[0].vec_elems() * ncol;
     hipError_t e = vaxpby<T>(prm.pv_poly[K], w, 0.0, y, n, st);
@@ -205,14 +204,13 @@ hipError_t Hierarchy::pv_poly(const cpx<T>* w, cpx<T>* y, cpx<T>* z, int ncol, h
 // A = D_PV^dag D_DW (on the fine level with the PV polynomial: D_PV^dag p(X) D_DW)
 template <typename T>
 hipError_t Hierarchy::apply_A(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp, int ncol, hipStream_t st,
-                              const int* skip, const Epi<T>& epi) {
+                              Skip skip, const Epi<T>& epi) {
     if (l == 0 && prm.pv_poly_order == 0) {
         if (!capturing_) cnt_.fine_applies += a_cost(0);
         const Level& L = levels[0];
         const cpx<T>* U;
         if constexpr (std::is_same<T, float>::value) U = L.U32; else U = L.U64;
-        return fine_a<T>(U, in, out, tmp, L.Lx, L.Ly, L.Ls, ncol, m, M5, skip, skip ? kSkipStride : 1, st,
-                         epi);
+        return fine_a<T>(U, in, out, tmp, L.Lx, L.Ly, L.Ls, ncol, m, M5, skip.flags, skip.stride, st, epi);
     }
     if constexpr (std::is_same<T, double>::value) {
         const Level& L = levels[l];
@@ -222,13 +220,12 @@ hipError_t Hierarchy::apply_A(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp,
             // (half its bytes); under the same launch configurations A in is the same, bit
             // for bit, as with an FP64 intermediate
             const CoarseGeom g{L.Lx, L.Ly, L.Ls, L.n};
-            const int stride = skip ? kSkipStride : 1;
             cpx<float>* t = reinterpret_cast<cpx<float>*>(tmp);
             hipError_t e = coarse_apply_mfma_io<double, float>(L.links, L.link_prec, in, t, g, ncol, m, M5, false,
-                                                               skip, stride, st);
+                                                               skip.flags, skip.stride, st);
             if (e != hipSuccess) return e;
-            return coarse_apply_mfma_io<float, double>(L.links, L.link_prec, t, out, g, ncol, 1.0, M5, true, skip,
-                                                       stride, st, epi);
+            return coarse_apply_mfma_io<float, double>(L.links, L.link_prec, t, out, g, ncol, 1.0, M5, true, skip.flags,
+                                                       skip.stride, st, epi);
         }
     }
     hipError_t e = apply_dw<T>(l, in, tmp, m, false, ncol, st, skip);
@@ -246,7 +243,7 @@ hipError_t Hierarchy::apply_A(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp,
 // A^dag = D_DW^dag D_PV (with the PV polynomial: D_DW^dag p(X) D_PV; p(X) is Hermitian)
 template <typename T>
 hipError_t Hierarchy::apply_Adag(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp, int ncol, hipStream_t st,
-                                 const int* skip, const Epi<T>& epi) {
+                                 Skip skip, const Epi<T>& epi) {
     hipError_t e = apply_dw<T>(l, in, tmp, 1.0, false, ncol, st, skip);
     if (e != hipSuccess) return e;
     if (l == 0 && !capturing_) cnt_.fine_applies += a_cost(0);
@@ -388,7 +385,7 @@ Task Hierarchy::cgnr(int l, const cpx<T>* b, cpx<T>* x, int ncol, hipStream_t st
     cpx<T>* z = C<T>(w.cz);
     cpx<T>* t = C<T>(w.tmp);
     CgScal* s = w.cg;
-    const int* skip = cg_skip(s);
+    const Skip skip{&s[0].done, kSkipStride};
     CO_HIPCHK(vzero<T>(x, nt, st));
     CO_HIPCHK(vconvert<T, T>(b, r, nt, st));
     CO_HIPCHK(apply_Adag<T>(l, r, z, t, ncol, st));
@@ -496,6 +493,11 @@ int Hierarchy::ss_longest(int l) const {
     return levels[l].vec_prec == P_F32 || own == P_F32 ? kSsMaxF32 : kSsMax;
 }
 
+Skip Hierarchy::ss_skip(int l, const GcrDev& g) const {
+    const Level& L = levels[l];
+    return !L.fine && L.link_prec == P_F16 && coarse_mfma_supported(L.n, L.link_prec) ? Skip{g.stop, 1} : Skip{};
+}
+
 // ------------------------------------------------------------ restarted GCR (coarsest level)
 // Unpreconditioned GCR(kmax) on A with every decision on the device: cycles of at most
 // ss_longest iterations take the s-step form (ss_finish: the directions first, then the
@@ -564,7 +566,7 @@ Task Hierarchy::gcr_plain(int l, const cpx<T>* b, cpx<T>* x, int ncol, double to
     auto cycle = [&]() -> int {
         for (int k = 0; k < kmax; ++k) {
             if (ss) {
-                HIPCHK(apply_A<T>(l, V.p[k], V.p[k + 1], t, ncol, st, nullptr, Epi<T>{V.p[k], 1.0 / c_ss, -1.0}));
+                HIPCHK(apply_A<T>(l, V.p[k], V.p[k + 1], t, ncol, st, ss_skip(l, g), Epi<T>{V.p[k], 1.0 / c_ss, -1.0}));
                 continue;
             }
             cpx<T>* Pk = P + (size_t)k * nt;
@@ -648,11 +650,12 @@ int Hierarchy::smooth(int l, const cpx<T>* r, cpx<T>* z, int ncol, hipStream_t s
         for (int j = 0; j <= ks; ++j) V.p[j] = Ps + (size_t)j * nt;
     auto body = [&]() -> int {
         if (ss) {
-            HIPCHK(apply_A<T>(l, z, Ps, t, ncol, st, nullptr, Epi<T>{r, -1.0, 1.0}));   // P_0 = r - A z
+            HIPCHK(apply_A<T>(l, z, Ps, t, ncol, st, Skip{}, Epi<T>{r, -1.0, 1.0}));   // P_0 = r - A z
             for (int c0 = 0; c0 < ns; c0 += ks) {
                 const int kc = std::min(ks, ns - c0);
                 for (int j = 0; j < kc; ++j)
-                    HIPCHK(apply_A<T>(l, V.p[j], V.p[j + 1], t, ncol, st, nullptr, Epi<T>{V.p[j], 1.0 / c_ss, -1.0}));
+                    HIPCHK(apply_A<T>(l, V.p[j], V.p[j + 1], t, ncol, st, c0 == 0 ? Skip{} : ss_skip(l, g),   // (the first cycle sets the flags)
+                                      Epi<T>{V.p[j], 1.0 / c_ss, -1.0}));
                 HIPCHK(ss_finish<T>(V, kc, z, n, ncol, c_ss, -1.0, c0 == 0, g, rw_, st));
             }
             return DWF_OK;

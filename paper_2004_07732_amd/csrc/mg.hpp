@@ -72,6 +72,12 @@ struct LevelWork {
     CgScal* cg = nullptr;
 };
 
+// one flag per column, `stride` ints apart: the operators leave a flagged column's output alone
+struct Skip {
+    const int* flags = nullptr;
+    int stride = 1;
+};
+
 struct SolveCounters {
     long long fine_applies = 0;
     long long level_iters[DWF_MAX_LEVELS] = {0, 0, 0};
@@ -311,20 +317,22 @@ private:
 
     // operators on level l in precision T
     template <typename T> hipError_t apply_dw(int l, const cpx<T>* in, cpx<T>* out, double mass, bool dag,
-                                              int ncol, hipStream_t st, const int* skip = nullptr,
-                                              const Epi<T>& epi = {});
+                                              int ncol, hipStream_t st, Skip skip = {}, const Epi<T>& epi = {});
     // stencil applications of one A (or A^dag) on level l
     int a_cost(int l) const { return (l == 0 && prm.pv_poly_order > 0) ? 2 * prm.pv_poly_order + 2 : 2; }
     // y = p(X) w on the fine level, X = D_PV D_PV^dag, p from prm.pv_poly (z: scratch)
     template <typename T> hipError_t pv_poly(const cpx<T>* w, cpx<T>* y, cpx<T>* z, int ncol, hipStream_t st,
-                                             const int* skip = nullptr);
+                                             Skip skip = {});
     template <typename T> hipError_t apply_A(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp, int ncol,
-                                             hipStream_t st, const int* skip = nullptr, const Epi<T>& epi = {});
+                                             hipStream_t st, Skip skip = {}, const Epi<T>& epi = {});
     // shift of the s-step Krylov directions on level l, and the longest cycle that takes that form
     double ss_shift(int l) const;
     int ss_longest(int l) const;
+    // the columns an s-step cycle leaves out: a tile of FP16 matrix-core columns shares one scale, so
+    // that a stopped column's directions would take bits from a smaller live one's
+    Skip ss_skip(int l, const GcrDev& g) const;
     template <typename T> hipError_t apply_Adag(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp, int ncol,
-                                                hipStream_t st, const int* skip = nullptr, const Epi<T>& epi = {});
+                                                hipStream_t st, Skip skip = {}, const Epi<T>& epi = {});
     template <typename T> hipError_t apply_wilson(int l, const cpx<T>* in, cpx<T>* out, double mass,
                                                   bool dag, int ncol, hipStream_t st);
     template <typename T> hipError_t restrict_to(int l, const cpx<T>* r, void* rc_next, int ncol, hipStream_t st);

@@ -167,3 +167,21 @@ def test_fp32_coarsest_cycles_stop_at_the_step(restart, link):
         rc = o.restrict(0, r[c])
         want = o.prolong(0, gcr(A, rc.reshape(-1), restart, tol).reshape(rc.shape))
         assert np.linalg.norm(got[c] - want) < 1e-4 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("restart", [1, 2, 6])
+def test_stopped_column_leaves_fp16_tile(restart):
+    """FP16 matrix-core columns of a tile share one scale (some 25 bits).  A column 3e7 times the other's
+    size leaves the small one next to nothing while both run; once it has stopped, the small one is
+    to have all its bits again, and stops too: within twice the larger count of the two solved
+    alone, where without them it takes three times as many steps or runs to the cap."""
+    U = inputs.metropolis_u1(16, 16, 6.0, 30, 960).U
+    p = dwfmg.MGParams(nvec=[8], block=[(4, 4)], Ls_coarse=[2], link_prec=[dwfmg.P_F16], vec_prec=[dwfmg.P_F64],
+                       setup_iters=0, smooth_iters=0, coarsest_solver=dwfmg.COARSEST_GCR, coarsest_restart=restart,
+                       coarsest_tol=0.03, coarsest_maxit=600, max_iters=1, max_outer=1)
+    mg = dwfmg.MG(T(U), 4, 0.05, -1.0, p, [T(inputs.gaussian_field((8, 16, 16, 2), 961))], max_nrhs=2)
+    b = inputs.gaussian_field((2, 4, 16, 16, 2), 962)
+    b[0] *= 3e7
+    its = [mg.solve(T(x), 1e-10, check=False)[1].level_iters[0] for x in (b[:1], b[1:], b)]
+    print("coarsest iterations alone, alone, together:", its, flush=True)
+    assert its[2] <= 2 * max(its[:2])
