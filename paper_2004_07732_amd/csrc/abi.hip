@@ -92,7 +92,7 @@ int pv_apply_t(const void* U, const void* psi, void* out, int Lx, int Ly, int Ls
         case DWF_PVDAG_DW_DAG: {
             const double m1 = (mode == DWF_PVDAG_DW) ? m : 1.0, m2 = (mode == DWF_PVDAG_DW) ? 1.0 : m;
             const size_t bytes = sizeof(cpx<R>) * 2 * (size_t)Lx * Ly * Ls * nrhs;
-            const FineProduct form = fine_product_form<R>(Lx, Ly, Ls, nrhs);
+            const FineProduct form = fine_product_form<R>(in, o, Lx, Ly, Ls, nrhs);
             auto one = [&] { return hip_status(fine_product<R>(u, in, o, Lx, Ly, Ls, nrhs, m1, m2, M5, st)); };
             if (form == FineProduct::kOne) return one();
             std::lock_guard<std::mutex> lk(g_scratch_mu);

@@ -29,6 +29,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <fstream>
+#include <cstdint>
 #include <map>
 #include <mutex>
 #include <string>
@@ -894,8 +895,10 @@ hipError_t fine_a(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* tmp, i
 }
 
 template <typename R>
-FineProduct fine_product_form(int Lx, int Ly, int Ls, int ncol) {
-    if (a_rule<R>(Lx, Ly, Ls, ncol) == 0) return FineProduct::kTwo;
+FineProduct fine_product_form(const cpx<R>* in, const cpx<R>* out, int Lx, int Ly, int Ls, int ncol) {
+    const uintptr_t i = reinterpret_cast<uintptr_t>(in), o = reinterpret_cast<uintptr_t>(out);
+    const size_t bytes = sizeof(spinor<R>) * (size_t)Lx * Ly * Ls * ncol;
+    if ((i < o ? o - i : i - o) < bytes || a_rule<R>(Lx, Ly, Ls, ncol) == 0) return FineProduct::kTwo;
     return a_two_faster<R>(Lx, Ly, Ls, ncol) ? FineProduct::kEither : FineProduct::kOne;
 }
 
@@ -1157,8 +1160,8 @@ template hipError_t fine_dw_untimed<float>(const cpx<float>*, const cpx<float>*,
 template hipError_t fine_dw_untimed<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, int, int, int, int, double, double, bool, hipStream_t);
 template hipError_t fine_a<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, cpx<float>*, int, int, int, int, double, double, const int*, int, hipStream_t, const Epi<float>&);
 template hipError_t fine_a<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, cpx<double>*, int, int, int, int, double, double, const int*, int, hipStream_t, const Epi<double>&);
-template FineProduct fine_product_form<float>(int, int, int, int);
-template FineProduct fine_product_form<double>(int, int, int, int);
+template FineProduct fine_product_form<float>(const cpx<float>*, const cpx<float>*, int, int, int, int);
+template FineProduct fine_product_form<double>(const cpx<double>*, const cpx<double>*, int, int, int, int);
 template hipError_t fine_product<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, int, int, int, int, double, double, double, hipStream_t);
 template hipError_t fine_product<double>(const cpx<double>*, const cpx<double>*, cpx<double>*, int, int, int, int, double, double, double, hipStream_t);
 template hipError_t wilson2d<float>(const cpx<float>*, const cpx<float>*, cpx<float>*, int, int, int, double, bool, hipStream_t);

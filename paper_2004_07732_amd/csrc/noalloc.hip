@@ -54,7 +54,7 @@ int pv_apply_noalloc_t(const void* U, const void* psi, void* out, int Lx, int Ly
     const size_t bytes = sizeof(cpx<R>) * 2 * (size_t)Lx * Ly * Ls * nrhs;
     if (bytes > kNoAllocBytes) return DWF_ESCRATCH;
     const double m1 = (mode == DWF_PVDAG_DW) ? m : 1.0, m2 = (mode == DWF_PVDAG_DW) ? 1.0 : m;
-    if (fine_product_form<R>(Lx, Ly, Ls, nrhs) == FineProduct::kOne)   // one launch, as dwf_pv_apply takes it
+    if (fine_product_form<R>(in, o, Lx, Ly, Ls, nrhs) == FineProduct::kOne)   // one launch, as dwf_pv_apply takes it
         return status_of(fine_product<R>(u, in, o, Lx, Ly, Ls, nrhs, m1, m2, M5, st));
     auto t = reinterpret_cast<cpx<R>*>(noalloc_scratch());
     if (!t) return DWF_EHIP;

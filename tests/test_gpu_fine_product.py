@@ -94,3 +94,25 @@ def test_products_at_the_lines_of_the_rule(Lx, Ly, Ls, nrhs, dtype):
         g.replay()
         torch.cuda.synchronize()
         assert float((out - two).norm() / two.norm()) < bar
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("shift", [1, -1, 3])
+def test_overlapping_output_is_not_raced(noalloc, shift):
+    """An output that overlaps the input, a slice or three further: only the one launch would read
+    what it has written.  The bits are those of the two stencils one after the other."""
+    U = torch.from_numpy(inputs.links_from_theta(inputs.random_theta(64, 64, 12))).cuda()
+    Ls, pad = 8, abs(shift)
+    x = torch.from_numpy(inputs.gaussian_field((Ls, 64, 64, 2), 13)).cuda()
+    apply = dwfmg.dwf_pv_apply_noalloc if noalloc else dwfmg.dwf_pv_apply
+    for mode in (dwfmg.DWF_PVDAG_DW, dwfmg.DWF_PVDAG_DW_DAG):
+        if mode == dwfmg.DWF_PVDAG_DW:
+            want = dwfmg.dwf_pv_apply(U, dwfmg.dwf_apply(U, x, 0.02, -1.0), 0.02, -1.0, dwfmg.DWF_PV_DAG)
+        else:
+            want = dwfmg.dwf_apply(U, dwfmg.dwf_pv_apply(U, x, 0.02, -1.0, dwfmg.DWF_PV), 0.02, -1.0, dagger=True)
+        buf = torch.zeros((Ls + pad, 64, 64, 2), dtype=x.dtype, device="cuda")
+        i0, o0 = (0, pad) if shift > 0 else (pad, 0)
+        psi, out = buf[i0:i0 + Ls], buf[o0:o0 + Ls]
+        psi.copy_(x)
+        apply(U, psi, 0.02, -1.0, mode, out=out)
+        assert torch.equal(out, want)
