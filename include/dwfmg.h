@@ -100,7 +100,8 @@ int dwf_apply(const void* U, const void* psi, void* out, int Lx, int Ly, int Ls,
  * and agree bit for bit.  By default (DWF_FINE_AUTO) the library times the
  * candidates once per lattice shape, column count, precision and adjoint flag
  * and keeps the fastest.  dwf_fine_config pins one for all later calls in the
- * process: shape DWF_FINE_ROW (any lattice) or one of the tiled shapes (used
+ * process (the products of dwf_pv_apply then take the two stencils so configured):
+ * shape DWF_FINE_ROW (any lattice) or one of the tiled shapes (used
  * only where Lx and Ly divide into its tiles; elsewhere the automatic choice
  * applies), chunk = slices walked per thread, 1 <= chunk <= 4095 (capped at
  * Ls).  shape = DWF_FINE_AUTO restores the automatic choice (chunk ignored).
@@ -141,7 +142,7 @@ int dwf_fine_a_chosen(int prec, int Lx, int Ly, int Ls, int nrhs, int* shape, in
 /* Pauli-Villars forms (Sec. 2.2, eq. NormalExp): see the DWF_PV* modes.  The
  * product modes are one launch where a tile of 32 x 16, 32 x 8, 16 x 16 or 16 x 8 sites
  * divides the lattice and Ls >= 2, unless two are faster (a few FP64 slices on part of the
- * chip; not under capture); elsewhere they use a library-owned intermediate field
+ * chip; not under capture) or dwf_fine_config pinned the stencil; elsewhere they use a library-owned intermediate field
  * (allocated on first use and kept until dwf_release_scratch; a call on one stream waits,
  * on the device, for the previous call's use of it on another).  Same layout rules as
  * dwf_apply.

@@ -899,7 +899,8 @@ FineProduct fine_product_form(const cpx<R>* in, const cpx<R>* out, int Lx, int L
     const uintptr_t i = reinterpret_cast<uintptr_t>(in), o = reinterpret_cast<uintptr_t>(out);
     const size_t bytes = sizeof(spinor<R>) * (size_t)Lx * Ly * Ls * ncol;
     if ((i < o ? o - i : i - o) < bytes || a_rule<R>(Lx, Ly, Ls, ncol) == 0) return FineProduct::kTwo;
-    return a_two_faster<R>(Lx, Ly, Ls, ncol) ? FineProduct::kEither : FineProduct::kOne;
+    const bool pinned = g_fine_pin.load(std::memory_order_relaxed) >= 0;
+    return pinned || a_two_faster<R>(Lx, Ly, Ls, ncol) ? FineProduct::kEither : FineProduct::kOne;
 }
 
 template <typename R>

@@ -70,7 +70,8 @@ hipError_t fine_a(const cpx<R>* U, const cpx<R>* in, cpx<R>* out, cpx<R>* tmp, i
 // how D(m2)^dag D(m1) is best applied by a rule on the sizes, never timed: in two launches through
 // an intermediate field (no tile divides the lattice), in one, or in two where the field is at hand
 enum class FineProduct { kTwo, kOne, kEither };
-// (the one launch reads `in` at other sites while it writes `out`: fields that overlap take two)
+// (the one launch reads `in` at other sites while it writes `out`: fields that overlap take two; so
+// does a process that pinned the stencil's configuration, where the field is at hand)
 template <typename R>
 FineProduct fine_product_form(const cpx<R>* in, const cpx<R>* out, int Lx, int Ly, int Ls, int ncol);
 // out = D(m2)^dag D(m1) in in one launch without an intermediate field (A: m1 = m, m2 = 1; A^dag:

@@ -116,3 +116,23 @@ def test_overlapping_output_is_not_raced(noalloc, shift):
         psi.copy_(x)
         apply(U, psi, 0.02, -1.0, mode, out=out)
         assert torch.equal(out, want)
+
+
+def test_pinned_stencil_reaches_the_products():
+    """dwf_fine_config governs every operator: a product under a pinned stencil takes the two
+    stencils, seen by the intermediate field that it allocates."""
+    U = torch.from_numpy(inputs.links_from_theta(inputs.random_theta(128, 128, 14))).cuda()
+    x = torch.randn((8, 16, 128, 128, 2), dtype=torch.complex128, device="cuda")   # 64 MB
+    out = torch.empty_like(x)
+    free = []
+    try:
+        for pin in (dwfmg.FINE_AUTO, dwfmg.FINE_ROW):
+            dwfmg.dwf_fine_config(pin, 4)
+            dwfmg.release_scratch()
+            dwfmg.dwf_pv_apply(U, x, 0.02, -1.0, out=out)
+            torch.cuda.synchronize()
+            free.append(torch.cuda.mem_get_info()[0])
+            dwfmg.release_scratch()
+    finally:
+        dwfmg.dwf_fine_config(dwfmg.FINE_AUTO)
+    assert free[0] - free[1] >= (48 << 20)
