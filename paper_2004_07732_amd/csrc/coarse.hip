@@ -144,10 +144,11 @@ coarse_kernel(const L* __restrict__ links, const cpx<T>* __restrict__ in, cpx<T>
 // once (one wave per site and column left one wave per SIMD at 32^2 sites: 42 us for 84 MB of
 // FP64 links at n = 32, 4 slices).  A lane holds RT rows of the block at every KG-th inner index:
 // row i = rt RI + i', column k = ks KG + kq, with the index that is contiguous in memory on the
-// consecutive lanes, 128 bytes at a time in FP64; the links stay in registers (n <= 32) for every
-// column tile.  Only the site term and the forward hops are read: the backward hop of a site is
+// consecutive lanes, 128 bytes at a time in FP64, KC inner steps ahead of their use; every column
+// tile reads them again (from L2 after the first).  Only the site term and the forward hops are read: the backward hop of a site is
 // the sigma_3-adjoint of its neighbour's forward hop (gamma_5-hermiticity and a chirality-keeping
 // prolongator), which that neighbour's own wave has just read into L2 on the same XCD.
+// A tile whose columns have all stopped costs the flags and the first links.
 // A wave stages its own neighbour's vectors in LDS, [k][column], sums over its kq lanes by
 // halving exchanges and leaves its part there; after one barrier a thread per output adds the
 // five parts in order with the site-local terms.
@@ -236,11 +237,19 @@ coarse_block_kernel(const L* __restrict__ links, const cpx<T>* __restrict__ in, 
     const int C = Ls * ncol;
     const int ntile = (C + CT - 1) / CT;
     const int t_lo = (int)blockIdx.y * tpb, t_hi = min(ntile, t_lo + tpb);
-    auto live = [&](int c) { return c < C && !(skip && skip[(size_t)(c / Ls) * skip_stride]); };
     for (int t = t_lo; t < t_hi; ++t) {
         const int cbase = t * CT;
+        // the tile's live columns, a flag per lane, loaded before the links so that waiting for it
+        // does not wait for them (the same for all five waves)
+        const bool col = lane < CT && cbase + lane < C;
+        int flag = 0;
+        if (skip) flag = skip[(size_t)((col ? cbase + lane : cbase) / Ls) * skip_stride];
 #pragma unroll
         for (int ks = 0; ks < KC; ++ks) load_step(ks);
+        __builtin_amdgcn_sched_barrier(0);
+        const unsigned alive = (unsigned)__ballot(col && flag == 0);
+        if (alive == 0) continue;
+        auto live = [&](int c) { return ((alive >> (c - cbase)) & 1u) != 0; };
         // this wave's neighbour vectors: columns past the end or stopped are zero; sigma_3 on
         // the vector for the adjoint and for the sigma_3-adjoint links
 #pragma unroll
@@ -384,8 +393,8 @@ hipError_t launch_n(const void* links, const cpx<T>* in, cpx<T>* out, const Coar
     const A mw = (A)(-m);
     const T ea = (T)epi.alpha, ebt = (T)epi.beta;
     if constexpr (N >= 16) {
-        // column tiles of 2, 4 or 8, all of a site's in one workgroup (its links are then read
-        // once) unless the sites alone would leave compute units without one
+        // column tiles of 2, 4 or 8, all of a site's in one workgroup (its later tiles then find
+        // the links in L2) unless the sites alone would leave compute units without one
         const int C = g.Ls * ncol;
         const int ct = C <= 2 ? 2 : (C <= 4 ? 4 : 8);
         const int ntile = (C + ct - 1) / ct;

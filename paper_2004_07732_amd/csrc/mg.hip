@@ -406,8 +406,8 @@ Task Hierarchy::cgnr(int l, const cpx<T>* b, cpx<T>* x, int ncol, hipStream_t st
     CO_HIPCHK(vconvert<T, T>(z, p, nt, st));
     const int maxit = prm.coarsest_maxit;
     int iters = 0;
-    // one chunk of CGNR iterations; iterations past convergence or maxit are
-    // no-ops on the device, so chunks always have the full length.  The norms come as partial sums
+    // one chunk of CGNR iterations; iterations past convergence or maxit change nothing (a launch and
+    // a look at the flags each), so chunks always have the full length.  The norms come as partial sums
     // from the last stencil of each operator where its kernel leaves them and they are few
     // enough to be added by every workgroup of the updates, else from a pass of their own; the
     // second state buffer lies in the partial sums' unused last quantity.

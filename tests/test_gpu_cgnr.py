@@ -49,3 +49,27 @@ def test_iterates(L, nvec, block, Lsc, maxit, tol, prec):
     for c in (0, 2):
         want = o.kcycle(0, r[c])
         assert np.linalg.norm(got[c] - want) < (1e-12 if prec == "f64" else 6e-4) * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("zero", [(0, 1), (2, 3), (4,), (0, 1, 2, 3, 4)])
+def test_tiles_whose_columns_have_all_stopped(zero):
+    """Five right-hand sides of four slices in column tiles of eight: a tile at either end or in the
+    middle has stopped from the start (zero sources), the others take nine iterations.  Bar: as
+    test_iterates."""
+    L, nvec, Lsc, Ls = 16, 8, 4, 6
+    U = inputs.metropolis_u1(L, L, 6.0, 10, 933).U
+    start = inputs.gaussian_field((nvec, L, L, 2), 934)
+    p = dwfmg.MGParams(nvec=[nvec], block=[(4, 4)], Ls_coarse=[Lsc], link_prec=[dwfmg.P_F64], vec_prec=[dwfmg.P_F64],
+                       setup_iters=0, smooth_iters=0, coarsest_tol=1e-30, coarsest_maxit=9)
+    mg = dwfmg.MG(T(U), Ls, 0.5, -1.0, p, [T(start)], max_nrhs=5)
+    o = O.MG(U, Ls, 0.5, -1.0, O.MGParams(levels=[O.LevelParams(nvec=nvec, block=(4, 4), Ls=Lsc, setup_iters=0)],
+                                          smooth_iters=0, coarsest_tol=1e-30, coarsest_maxit=9), [start])
+    r = inputs.gaussian_field((5, Ls, L, L, 2), 935)
+    r[list(zero)] = 0.0
+    got = mg.level_op(0, dwfmg.MG_OP_KCYCLE, T(r), 5).cpu().numpy()
+    for c in range(5):
+        if c in zero:
+            assert not got[c].any()
+        else:
+            want = o.kcycle(0, r[c])
+            assert np.linalg.norm(got[c] - want) < 1e-12 * np.linalg.norm(want)
