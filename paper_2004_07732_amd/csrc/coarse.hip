@@ -392,6 +392,15 @@ hipError_t launch_n(const void* links, const cpx<T>* in, cpx<T>* out, const Coar
     const A cd = wil ? (A)wmass : (A)(M5 + 1.0);
     const A mw = (A)(-m);
     const T ea = (T)epi.alpha, ebt = (T)epi.beta;
+    // (the 2-d operator is applied with FP64 links alone: setup and diagnostics)
+    auto with_op = [&](auto go) {
+        if constexpr (std::is_same_v<L, cpx<double>>) {
+            if (wil) return dagger ? go(std::true_type{}, std::true_type{}) : go(std::false_type{}, std::true_type{});
+        } else if (wil) {
+            return hipErrorInvalidValue;
+        }
+        return dagger ? go(std::true_type{}, std::false_type{}) : go(std::false_type{}, std::false_type{});
+    };
     if constexpr (N >= 16) {
         // column tiles of 2, 4 or 8, all of a site's in one workgroup (its later tiles then find
         // the links in L2) unless the sites alone would leave compute units without one
@@ -401,36 +410,38 @@ hipError_t launch_n(const void* links, const cpx<T>* in, cpx<T>* out, const Coar
         const int gy0 = std::min(ntile, std::max(1, 1024 / nsites));
         const int tpb = (ntile + gy0 - 1) / gy0;
         const dim3 grid(nsites, (ntile + tpb - 1) / tpb), block(320);
-        auto go = [&](auto ctc, auto dagc, auto wilc) {
-            hipLaunchKernelGGL((coarse_block_kernel<L, T, N, decltype(dagc)::value, decltype(wilc)::value,
-                                                    decltype(ctc)::value>),
-                               grid, block, 0, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, ncol, tpb, cd, mw,
-                               epi.b, ea, ebt, epi.norm, epi.norm_stride);
-        };
         auto with_ct = [&](auto ctc) {
-            if (wil) { if (dagger) go(ctc, std::true_type{}, std::true_type{}); else go(ctc, std::false_type{}, std::true_type{}); }
-            else     { if (dagger) go(ctc, std::true_type{}, std::false_type{}); else go(ctc, std::false_type{}, std::false_type{}); }
+            return with_op([&](auto dagc, auto wilc) {
+                hipLaunchKernelGGL((coarse_block_kernel<L, T, N, decltype(dagc)::value, decltype(wilc)::value,
+                                                        decltype(ctc)::value>),
+                                   grid, block, 0, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, ncol, tpb, cd, mw,
+                                   epi.b, ea, ebt, epi.norm, epi.norm_stride);
+                return hipGetLastError();
+            });
         };
-        if (ct == 2) with_ct(std::integral_constant<int, 2>{});
-        else if (ct == 4) with_ct(std::integral_constant<int, 4>{});
-        else with_ct(std::integral_constant<int, 8>{});
-        return hipGetLastError();
+        if (ct == 2) return with_ct(std::integral_constant<int, 2>{});
+        if (ct == 4) return with_ct(std::integral_constant<int, 4>{});
+        return with_ct(std::integral_constant<int, 8>{});
     } else {
         size_t per_wave_bytes = (size_t)coarse_lds_per_wave(N, g.Ls) * sizeof(cpx<A>);
         int wpb = 4;
         while (wpb > 1 && per_wave_bytes * wpb > 64 * 1024) wpb >>= 1;
         if (per_wave_bytes * wpb > 160 * 1024) return hipErrorInvalidValue;
-        dim3 grid((nsites + wpb - 1) / wpb, ncol), block(64 * wpb);
-        const size_t shm = per_wave_bytes * wpb;
-        if (wil) {
-            if (dagger) hipLaunchKernelGGL((coarse_kernel<L, T, N, true, true>), grid, block, shm, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw, epi.b, ea, ebt);
-            else        hipLaunchKernelGGL((coarse_kernel<L, T, N, false, true>), grid, block, shm, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw, epi.b, ea, ebt);
-        } else {
-            if (dagger) hipLaunchKernelGGL((coarse_kernel<L, T, N, true, false>), grid, block, shm, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw, epi.b, ea, ebt);
-            else        hipLaunchKernelGGL((coarse_kernel<L, T, N, false, false>), grid, block, shm, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw, epi.b, ea, ebt);
-        }
-        return hipGetLastError();
+        const dim3 grid((nsites + wpb - 1) / wpb, ncol), block(64 * wpb);
+        return with_op([&](auto dagc, auto wilc) {
+            hipLaunchKernelGGL((coarse_kernel<L, T, N, decltype(dagc)::value, decltype(wilc)::value>), grid, block,
+                               per_wave_bytes * wpb, st, lk, in, out, skip, sks, g.Lx, g.Ly, g.Ls, nsites, cd, mw, epi.b,
+                               ea, ebt);
+            return hipGetLastError();
+        });
     }
+}
+
+// (16-bit links of a multiple of 16 components go to the matrix cores: coarse_mfma_supported)
+template <typename L, typename T, int N, typename... Args>
+hipError_t launch_valu(const Args&... args) {
+    if constexpr (sizeof(L) == 4 && N % 16 == 0) return hipErrorInvalidValue;
+    else return launch_n<L, T, N>(args...);
 }
 
 template <typename L, typename T>
@@ -438,14 +449,14 @@ hipError_t launch_l(const void* links, const cpx<T>* in, cpx<T>* out, const Coar
                     double m, double M5, bool dagger, bool wil, double wmass, const int* skip, int sks, hipStream_t st,
                     const Epi<T>& epi) {
     switch (g.n) {
-        case 4:  return launch_n<L, T, 4>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
-        case 8:  return launch_n<L, T, 8>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
-        case 12: return launch_n<L, T, 12>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
-        case 16: return launch_n<L, T, 16>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
-        case 24: return launch_n<L, T, 24>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
-        case 32: return launch_n<L, T, 32>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
-        case 48: return launch_n<L, T, 48>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
-        case 64: return launch_n<L, T, 64>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 4:  return launch_valu<L, T, 4>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 8:  return launch_valu<L, T, 8>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 12: return launch_valu<L, T, 12>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 16: return launch_valu<L, T, 16>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 24: return launch_valu<L, T, 24>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 32: return launch_valu<L, T, 32>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 48: return launch_valu<L, T, 48>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
+        case 64: return launch_valu<L, T, 64>(links, in, out, g, ncol, m, M5, dagger, wil, wmass, skip, sks, st, epi);
         default: return hipErrorInvalidValue;
     }
 }
