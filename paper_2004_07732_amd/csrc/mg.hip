@@ -328,16 +328,19 @@ int Hierarchy::alloc_level_work(int l, int ncol) {
         if (!w.py || !w.pz) return DWF_EINVAL;
     }
     if (w.kmax > 0) {
+        // (an s-step cycle keeps no A directions: its last direction is W_0)
+        const bool ss = coarsest && w.kmax <= ss_longest(l);
         w.P = A(vb * w.kmax);
-        w.W = A(vb * w.kmax);
+        w.W = A(vb * (ss ? 1 : w.kmax));
         if (!w.P || !w.W) return DWF_EINVAL;
     }
     if (w.ksmooth > 0) {
-        w.Ps = A(vb * (w.kscycle + 1));
-        w.Ws = A(vb * w.kscycle);
-        w.rs = A(vb);
+        const bool ss = w.kscycle <= ss_longest(l);
+        w.Ps = A(vb * (w.kscycle + (ss ? 1 : 0)));
+        w.Ws = ss ? nullptr : A(vb * w.kscycle);
+        w.rs = ss ? nullptr : A(vb);
         w.zt = A(vb);
-        if (!w.Ps || !w.Ws || !w.rs || !w.zt) return DWF_EINVAL;
+        if (!w.Ps || (!ss && (!w.Ws || !w.rs)) || !w.zt) return DWF_EINVAL;
     }
     if (!coarsest) {
         const Level& N = levels[l + 1];

@@ -54,8 +54,8 @@ struct LevelWork {
     void* tmp = nullptr;
     void* tmp2 = nullptr;
     void* rhs = nullptr;
-    void* Ps = nullptr;           // [kscycle+1] smoother directions
-    void* Ws = nullptr;           // [kscycle]
+    void* Ps = nullptr;           // [kscycle] smoother directions, one more in the s-step form
+    void* Ws = nullptr;           // [kscycle], and the residual, in the orthogonalising form
     void* rs = nullptr;
     void* zt = nullptr;           // K-cycle output scratch
     void* py = nullptr;           // fine level with the PV polynomial: p(X) w and X's intermediate

@@ -204,3 +204,23 @@ def test_device_allocation_only_where_documented():
             assert inside, f"{fn}:{line}: device allocation outside the documented places"
             seen.add((fn, inside[0]))
     assert ("mg.hip", 0) in seen and ("abi.hip", 0) in seen
+
+
+def test_workspace_holds_what_the_cycles_use():
+    """Short (s-step) cycles keep their directions and one more; longer ones the directions, A times
+    each of them and a residual.  FP64, one column: in vectors of the level, to the few KB that
+    the columns' scalars take."""
+    dwfmg = pytest.importorskip("paper_2004_07732_amd.dwfmg")
+    L, Ls, Lsc, nv = 64, 8, 4, 16
+
+    def size(**kw):
+        p = dwfmg.MGParams(nvec=[nv], block=[(4, 4)], Ls_coarse=[Lsc], link_prec=[dwfmg.P_F64], vec_prec=[dwfmg.P_F64],
+                           setup_iters=0, coarsest_solver=dwfmg.COARSEST_GCR, **kw)
+        return dwfmg.workspace_bytes(L, L, Ls, p, 1)
+
+    fine, coarse = Ls * L * L * 2 * 16, Lsc * (L // 4) ** 2 * 2 * nv * 16
+    base = dict(smooth_iters=64, smooth_restart=15, coarsest_restart=6)
+    grow = lambda **kw: size(**{**base, **kw}) - size(**base)  # noqa: E731
+    assert abs(grow(smooth_restart=16) - 2 * fine) < 65536
+    assert abs(grow(coarsest_restart=7) - 7 * coarse) < 65536              # 6 + 1 vectors, then 7 + 7
+    assert abs(grow(smooth_restart=6) - (7 - 31) * fine) < 65536           # 15 + 15 + 1, then 6 + 1
