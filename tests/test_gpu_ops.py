@@ -217,3 +217,14 @@ def test_links_from_theta():
     U = dwfmg.dwf_links_from_theta(torch.from_numpy(theta).to(DEV)).cpu().numpy()
     want = inputs.links_from_theta(theta)
     assert np.max(np.abs(U - want)) < 4e-16
+
+
+# sites that do not fill a workgroup's 64, fewer and more (column, slice) fields than its four waves
+@pytest.mark.parametrize("Lx,Ly,Ls,nrhs", [(2, 2, 1, 1), (5, 3, 2, 1), (9, 7, 3, 1), (13, 10, 5, 3), (64, 1, 4, 1), (1, 65, 2, 2)])
+def test_force_on_odd_sizes(Lx, Ly, Ls, nrhs):
+    U = inputs.links_from_theta(inputs.random_theta(Lx, Ly, 19))
+    X = inputs.gaussian_field((nrhs, Ls, Ly, Lx, 2), 20)
+    Y = inputs.gaussian_field((nrhs, Ls, Ly, Lx, 2), 21)
+    F = dwfmg.dwf_force(torch.from_numpy(U).to(DEV), torch.from_numpy(X).to(DEV), torch.from_numpy(Y).to(DEV))
+    want = O.force(U, X, Y)
+    assert np.max(np.abs(F.cpu().numpy() - want)) < 1e-12 * np.max(np.abs(want))

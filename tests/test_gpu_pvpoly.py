@@ -96,3 +96,16 @@ def test_pv_poly_parameter_errors():
     with pytest.raises(dwfmg.DwfError):
         dwfmg.MG(U, Ls, 0.05, -1.0, dwfmg.MGParams(nvec=[4], block=[(4, 4)], Ls_coarse=[2], setup_iters=0,
                                                     pv_poly=[1.0, float("nan")]), [s])
+
+
+@pytest.mark.parametrize("Lx,Ly,Ls", [(20, 12, 4), (16, 8, 1)])   # no tile divides; one slice
+@pytest.mark.parametrize("dtype", [torch.complex64, torch.complex128])
+def test_pv_poly_order_zero_in_two_launches(Lx, Ly, Ls, dtype):
+    """Order zero with c = 1, and with c = 2 (the chain of stencils): the product and twice the product."""
+    m, M5 = 0.02, -1.0
+    U = T(inputs.metropolis_u1(Lx, Ly, 6.0, 10, 722).U).to(dtype)
+    psi = T(inputs.gaussian_field((2, Ls, Ly, Lx, 2), 723)).to(dtype)
+    for dag, mode in ((False, dwfmg.DWF_PVDAG_DW), (True, dwfmg.DWF_PVDAG_DW_DAG)):
+        b = dwfmg.dwf_pv_apply(U, psi, m, M5, mode=mode)
+        assert torch.equal(dwfmg.dwf_pv_poly_apply(U, psi, m, M5, [1.0], dagger=dag), b)
+        assert torch.equal(dwfmg.dwf_pv_poly_apply(U, psi, m, M5, [2.0], dagger=dag), 2.0 * b)

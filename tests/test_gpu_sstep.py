@@ -185,3 +185,21 @@ def test_stopped_column_leaves_fp16_tile(restart):
     its = [mg.solve(T(x), 1e-10, check=False)[1].level_iters[0] for x in (b[:1], b[1:], b)]
     print("coarsest iterations alone, alone, together:", its, flush=True)
     assert its[2] <= 2 * max(its[:2])
+
+
+def test_finaliser_publishes_for_every_column_count(monkeypatch):
+    """The host learns of a coarsest cycle's end from a word per column that the finaliser stores: column
+    counts in turn on one hierarchy (captured cycles replayed in between), each as on its own."""
+    monkeypatch.setenv("DWF_AUTOTUNE", "0")   # the same launch configurations on both sides
+    U = T(inputs.metropolis_u1(16, 16, 6.0, 30, 980).U)
+    start = T(inputs.gaussian_field((4, 16, 16, 2), 981))
+    p = dwfmg.MGParams(nvec=[4], block=[(4, 4)], Ls_coarse=[2], link_prec=[dwfmg.P_F64], vec_prec=[dwfmg.P_F64],
+                       setup_iters=20, smooth_iters=4, coarsest_solver=dwfmg.COARSEST_GCR, coarsest_restart=5,
+                       coarsest_tol=0.05)
+    b = T(inputs.gaussian_field((3, 4, 16, 16, 2), 982))
+    make = lambda: dwfmg.MG(U, 4, 0.05, -1.0, p, [start], max_nrhs=3)  # noqa: E731
+    want = {n: make().solve(b[:n].contiguous(), 1e-11) for n in (1, 2, 3)}
+    mg = make()
+    for n in (1, 3, 2, 3, 1):
+        x, st = mg.solve(b[:n].contiguous(), 1e-11)
+        assert torch.equal(x, want[n][0]) and st.level_iters == want[n][1].level_iters

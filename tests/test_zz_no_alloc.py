@@ -75,3 +75,24 @@ def test_noalloc_rejects_what_does_not_fit():
     out = dwfmg.dwf_pv_apply_noalloc(U, psi, 0.01, -1.0, dwfmg.DWF_PV)
     torch.cuda.synchronize()
     assert float(out.abs().max()) == 0.0
+
+
+# no tile divides either: both go through the static array, the first to well beyond the second's field
+RAGGED_CALLS = [(60, 36, 8, 3), (24, 20, 6, 1)]
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+def test_noalloc_on_a_used_array(mode, dtype):
+    m, M5 = 0.03, -1.05
+    code = getattr(dwfmg, mode)
+    bar = 1e-13 if dtype == torch.complex128 else 1e-6   # two stencils of some 30 roundings
+    for k, (Lx, Ly, Ls, nrhs) in enumerate(RAGGED_CALLS):
+        U = inputs.metropolis_u1(Lx, Ly, 6.0, 10, 520 + k).U
+        psi = inputs.gaussian_field((nrhs, Ls, Ly, Lx, 2), 530 + k)
+        Ut = torch.from_numpy(U).to(DEV).to(dtype)
+        pt = torch.from_numpy(psi).to(DEV).to(dtype)
+        got = dwfmg.dwf_pv_apply_noalloc(Ut, pt, m, M5, code)
+        assert torch.equal(got, dwfmg.dwf_pv_apply(Ut, pt, m, M5, code)), f"call {k}: differs from dwf_pv_apply"
+        ref = oracle_mode(mode, Ut.to(torch.complex128).cpu().numpy(), pt.to(torch.complex128).cpu().numpy(), m, M5)
+        assert np.linalg.norm(got.cpu().numpy() - ref) < bar * np.linalg.norm(ref)
