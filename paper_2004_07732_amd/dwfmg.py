@@ -254,12 +254,22 @@ class SolveStats:
     escalations: int = 0
 
 
+def _current_stream_reader():
+    """A function that gives the current device's current stream as a plain integer.  Building a
+    Stream object for it costs as much as the rest of a small call's checks, so torch's own raw
+    accessors are used; they are not public, and a torch without them takes the object."""
+    try:
+        raw, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+    except AttributeError:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
+
+
+_current_stream = _current_stream_reader()
+
+
 def _stream(stream=None) -> int:
-    if stream is not None:
-        return stream.cuda_stream
-    # the current device's current stream as a plain integer (building a Stream object for it
-    # costs as much as the rest of a small call's checks)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _current_stream() if stream is None else stream.cuda_stream
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:

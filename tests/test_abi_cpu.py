@@ -224,3 +224,11 @@ def test_workspace_holds_what_the_cycles_use():
     assert abs(grow(smooth_restart=16) - 2 * fine) < 65536
     assert abs(grow(coarsest_restart=7) - 7 * coarse) < 65536              # 6 + 1 vectors, then 7 + 7
     assert abs(grow(smooth_restart=6) - (7 - 31) * fine) < 65536           # 15 + 15 + 1, then 6 + 1
+
+
+def test_current_stream_without_the_raw_accessors(monkeypatch):
+    torch = pytest.importorskip("torch")
+    from paper_2004_07732_amd import dwfmg
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: type("Stream", (), {"cuda_stream": 7}))
+    assert dwfmg._current_stream_reader()() == 7
