@@ -302,20 +302,21 @@ def solve_model_bytes(fine_applies, coarse_iters, k, L, Ls, coarse_a, coarse_vec
             + kcycles * smoother_model_passes(smooth_iters, smooth_restart) * fine_vec)
 
 
-SSTEP_STEPS = 6   # longest cycle the library runs in the s-step form
+# longest cycles the library runs in the s-step form: the fine smoother's, and the coarsest level's
+SSTEP_STEPS, SSTEP_COARSE_STEPS = 8, 6
 
 
 def sstep_model_bytes(fine_applies, coarse_iters, k, L, Ls, coarse_a, coarse_vec_bytes,
                       kcycles=0, smooth_iters=0, smooth_restart=0, fused=False):
     """HBM bytes of one solve whose smoother and coarsest cycles all take the s-step form (at most
-    SSTEP_STEPS steps; None for longer ones), a lower bound as solve_model_bytes is: the fine
+    SSTEP_STEPS and SSTEP_COARSE_STEPS steps; None for longer ones), a lower bound as solve_model_bytes is: the fine
     stencils (with the fused A half of their vector bytes, since an application reads and writes
     one vector for its two stencils), one coarse A-hat per coarsest iteration, and per cycle of
     k steps the shift's read of each direction (k), the inner products (k + 1) and the update
     (k + 1 directions and x read, x and the residual written): 3 k + 5 vector passes.  The
     smoother's first residual reads its right-hand side once."""
     ks = smooth_restart if 0 < smooth_restart < smooth_iters else smooth_iters
-    if max(k, ks) > SSTEP_STEPS:
+    if k > SSTEP_COARSE_STEPS or ks > SSTEP_STEPS:
         return None
     fine_vec = Ls * L * L * 2 * 8
     fine_apply = (1 if fused else 2) * fine_vec + 2 * L * L * 8

@@ -845,8 +845,8 @@ k_gcr_fused_update(const cpx<T>* W, size_t wstride, cpx<T>* w, cpx<T>* r, cpx<T>
 // ---- s-step GCR cycle (short cycles, Hierarchy::ss_longest: the smoother's and the coarsest
 // solve's).  The cycle's minimal residual lies in r0 - span{A p : p in K_k(A, r0)}, whatever
 // basis spans the Krylov space, so the directions need no inner product while they are built:
-// P_0 = r0, P_{i+1} = A P_i / c - P_i (the stencil's epilogue; the shift lies inside the
-// spectrum), hence A P_i = c v_i with v_i = P_{i+1} + P_i.  One pass
+// P_0 = r0, P_{i+1} = A P_i / c - s_i P_i (the stencil's epilogue; the shifts lie inside the
+// spectrum), hence A P_i = c v_i with v_i = P_{i+1} + s_i P_i.  One pass
 // forms H_ab = <P_a, P_b>, one workgroup per column solves G y = b, G_il = <v_i, v_l>,
 // b_i = <v_i, r0>, and one pass updates x += sum y_i P_i / c and
 // P_0 = r0 - sum y_i v_i.  HBM-bound: K + 1 vectors read for the products and K + 2 read and 2
@@ -984,13 +984,13 @@ __global__ void __launch_bounds__(kSsThreads) k_ss_dots(SsVecs<T> P, size_t nw, 
 // difference is rounding; the next cycle's |P_0|^2 then decides.  A pivot within rounding of zero
 // against its direction's own norm drops that direction.
 // The work is small and runs once, so its time is that of fetching code and of waits in turn: unrolled
-// over one row per lane it was 11 KB at 6 steps and took 7.9 us; one entry per lane in rolled
-// loops, 4 KB, and state and partials in flight together, 7.0.
+// over one row per lane it was 11 KB at 6 steps (16 KB at 8) and took 7.9 us (12.7); one entry
+// per lane in rolled loops, 4 KB, and state and partials in flight together, 7.0 (9.6).
 constexpr int kSsFinWaves = 16;
 constexpr double kSsPivot = 1e-13;
 constexpr double kSsTrust = 1e-12;
 template <int K>
-__global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb, GcrDev g, double tol2, double inv_c,
+__global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb, GcrDev g, double tol2, SsShifts sh,
                                                             int first, SsPublish pub) {
     constexpr int NQ = ss_nq(K);
     constexpr int NR = (NQ + 63) / 64;
@@ -1077,8 +1077,14 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
     auto from = [](cpx<double> z, int l) -> cpx<double> { return {__shfl(z.re, l), __shfl(z.im, l)}; };
     const int row = lane >> 3, colm = lane & 7;
     const int i = row < K ? row : K - 1, l = colm < K ? colm : K - 1;
-    cpx<double> G = h(i + 1, l + 1) + h(i + 1, l) + h(i, l + 1) + h(i, l);
-    cpx<double> bi = h(i + 1, 0) + h(i, 0);
+    double si = sh.s[0], sl = sh.s[0];   // (selects: the arguments are not indexed by lane)
+#pragma unroll
+    for (int j = 1; j < K; ++j) {
+        si = i == j ? sh.s[j] : si;
+        sl = l == j ? sh.s[j] : sl;
+    }
+    cpx<double> G = h(i + 1, l + 1) + sl * h(i + 1, l) + si * h(i, l + 1) + si * sl * h(i, l);
+    cpx<double> bi = h(i + 1, 0) + si * h(i, 0);
     const double dg = G.re;
     cpx<double> L = {0.0, 0.0}, u = {0.0, 0.0};
     double rr = rr0, inv = 0.0;
@@ -1117,11 +1123,11 @@ __global__ void __launch_bounds__(64 * kSsFinWaves) k_ss_fin(RedWork rw, int nb,
     const cpx<double> up = from(y, i > 0 ? (i - 1) << 3 : 0);
     const cpx<double> prev = i > 0 ? up : cpx<double>{0.0, 0.0};
     if (row < K && colm == 0) {
-        coef[2 * i] = y.re * inv_c;
-        coef[2 * i + 1] = y.im * inv_c;
+        coef[2 * i] = y.re * sh.inv_c;
+        coef[2 * i + 1] = y.im * sh.inv_c;
         double* e = coef + 2 * K;
-        e[2 * i] = -(y.re + prev.re);
-        e[2 * i + 1] = -(y.im + prev.im);
+        e[2 * i] = -(si * y.re + prev.re);
+        e[2 * i + 1] = -(si * y.im + prev.im);
         if (i == K - 1) {
             e[2 * K] = -y.re;
             e[2 * K + 1] = -y.im;
@@ -1366,7 +1372,7 @@ hipError_t ss_begin(const cpx<T>* b, cpx<T>* P0, cpx<T>* x, size_t n, int ncol, 
     return hipGetLastError();
 }
 template <typename T>
-hipError_t ss_finish(const SsVecs<T>& P, int k, cpx<T>* x, size_t n, int ncol, double c, double tol2, bool first,
+hipError_t ss_finish(const SsVecs<T>& P, int k, cpx<T>* x, size_t n, int ncol, const SsShifts& sh, double tol2, bool first,
                      const GcrDev& g, const RedWork& rw, hipStream_t st, const SsPublish& pub) {
     if (k < 1 || k > kSsMax || (pub.word && !pub.ctr) || 4 * k + 3 > kGcrTot || n % Word<T>::E) return hipErrorInvalidValue;
     const size_t nw = n / Word<T>::E;
@@ -1378,7 +1384,7 @@ hipError_t ss_finish(const SsVecs<T>& P, int k, cpx<T>* x, size_t n, int ncol, d
     auto launch = [&](auto kc) {
         constexpr int K = decltype(kc)::value + 1;
         hipLaunchKernelGGL((k_ss_dots<T, K>), dim3((unsigned)nb, ncol), dim3(kSsThreads), 0, st, P, nw, rw);
-        hipLaunchKernelGGL(k_ss_fin<K>, dim3(ncol), dim3(64 * kSsFinWaves), 0, st, rw, (int)nb, g, tol2, 1.0 / c,
+        hipLaunchKernelGGL(k_ss_fin<K>, dim3(ncol), dim3(64 * kSsFinWaves), 0, st, rw, (int)nb, g, tol2, sh,
                            first ? 1 : 0, pub);
         hipLaunchKernelGGL((k_ss_update<T, K>), ew_grid(nw, ncol), dim3(kBlock), 0, st, P, x, nw, g,
                            pub.word ? pub.ctr : nullptr);
@@ -1496,8 +1502,8 @@ template hipError_t gcr_solve_xupdate<float, float>(const cpx<float>*, size_t, i
 template hipError_t gcr_solve_xupdate<double, double>(const cpx<double>*, size_t, int, cpx<double>*, size_t, int, bool, const GcrDev&, hipStream_t);
 template hipError_t ss_begin<float>(const cpx<float>*, cpx<float>*, cpx<float>*, size_t, int, const GcrDev&, hipStream_t);
 template hipError_t ss_begin<double>(const cpx<double>*, cpx<double>*, cpx<double>*, size_t, int, const GcrDev&, hipStream_t);
-template hipError_t ss_finish<float>(const SsVecs<float>&, int, cpx<float>*, size_t, int, double, double, bool, const GcrDev&, const RedWork&, hipStream_t, const SsPublish&);
-template hipError_t ss_finish<double>(const SsVecs<double>&, int, cpx<double>*, size_t, int, double, double, bool, const GcrDev&, const RedWork&, hipStream_t, const SsPublish&);
+template hipError_t ss_finish<float>(const SsVecs<float>&, int, cpx<float>*, size_t, int, const SsShifts&, double, bool, const GcrDev&, const RedWork&, hipStream_t, const SsPublish&);
+template hipError_t ss_finish<double>(const SsVecs<double>&, int, cpx<double>*, size_t, int, const SsShifts&, double, bool, const GcrDev&, const RedWork&, hipStream_t, const SsPublish&);
 template hipError_t gcr_solve_xupdate_restart<float>(cpx<float>*, size_t, int, cpx<float>*, size_t, int, const cpx<float>*, const int*, const GcrDev&, hipStream_t);
 template hipError_t gcr_solve_xupdate_restart<double>(cpx<double>*, size_t, int, cpx<double>*, size_t, int, const cpx<double>*, const int*, const GcrDev&, hipStream_t);
 

@@ -242,8 +242,8 @@ template <typename T>
 hipError_t gcr_fused_step(const cpx<T>* W, size_t wstride, int j, cpx<T>* w, cpx<T>* r, cpx<T>* copy, size_t n,
                           int ncol, double tol2, const int* stop_in, int* stop_out, const GcrDev& g,
                           const RedWork& rw, hipStream_t st);
-// s-step GCR cycle of k <= kSsMax steps: the directions P_0 = r0, P_{i+1} = A P_i / c - P_i are
-// built without an inner product (c: a shift inside the spectrum of A), then three launches take
+// s-step GCR cycle of k <= kSsMax steps: the directions P_0 = r0, P_{i+1} = A P_i / c - s_i P_i are
+// built without an inner product (shifts c s_i inside the spectrum of A), then three launches take
 // the minimal residual over r0 - span{A P_0 .. A P_{k-1}}: the products <P_a, P_b>, a finaliser
 // that solves for the coefficients once per column, and one pass x += sum y_i P_i,
 // P_0 = the new residual (the next cycle's start).  The residual norm of every step of the cycle
@@ -251,12 +251,13 @@ hipError_t gcr_fused_step(const cpx<T>* W, size_t wstride, int j, cpx<T>* w, cpx
 // that step's correction and stops (stop 1; 2 if a value is not finite), and g.it counts the
 // steps it took.  A stopped column takes no update.  `first` starts the column state afresh
 // (|b|^2 = |P_0|^2); otherwise ss_begin (P_0 = b, x = 0) or the previous cycle left it.
-// The directions' condition grows by a factor of 10 a step and the form squares it, so the rounding of
-// a direction or of A counts several times over in the coefficients (4 times at 5 steps, 8 at 6, 30 to
-// 40 at 8): more than kSsMax steps take the orthogonalising form, and Hierarchy::ss_longest says how
-// many are as accurate as that form on a level.
-constexpr int kSsMax = 6;
-constexpr int kSsMaxF32 = 2;
+// Hierarchy::ss_shifts chooses the shifts, Hierarchy::ss_longest how many steps are as accurate as the
+// orthogonalising form on a level.
+constexpr int kSsMax = 8;
+struct SsShifts {
+    double inv_c = 1.0;      // a power of two
+    double s[kSsMax] = {};   // exact in the vectors' precision
+};
 constexpr int kSsBlocks = 256;
 template <typename T> struct SsVecs { cpx<T>* p[kSsMax + 1]; };
 // With `word` set the finaliser also tells the host each column's state, before the update runs: one
@@ -272,7 +273,7 @@ constexpr unsigned ss_word_seq(unsigned long long w) { return (unsigned)(w >> 32
 template <typename T>
 hipError_t ss_begin(const cpx<T>* b, cpx<T>* P0, cpx<T>* x, size_t n, int ncol, const GcrDev& g, hipStream_t st);
 template <typename T>
-hipError_t ss_finish(const SsVecs<T>& P, int k, cpx<T>* x, size_t n, int ncol, double c, double tol2, bool first,
+hipError_t ss_finish(const SsVecs<T>& P, int k, cpx<T>* x, size_t n, int ncol, const SsShifts& sh, double tol2, bool first,
                      const GcrDev& g, const RedWork& rw, hipStream_t st, const SsPublish& pub = {});
 // next restart cycle on the recursive residual: P0 = r, and the stop flags of the
 // cycle's last step (stop_src) become g.stop

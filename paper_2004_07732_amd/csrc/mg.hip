@@ -456,44 +456,60 @@ Task Hierarchy::cgnr(int l, const cpx<T>* b, cpx<T>* x, int ncol, hipStream_t st
     co_return DWF_OK;
 }
 
-// Shift c of the s-step directions on level l (P_{i+1} = A P_i / c - P_i).  D_W(M5) + 1 is
-// (3 + M5) minus hops of norm at most 2, the fifth-dimension hop has norm max(1, |m|), and
-// the coarse kernels are their Galerkin projections, so |A| <= B^2 with B the sum; A's
-// spectrum lies in the right half-plane.  Directions shifted to about a third of the
-// bound lose least over sources of all kinds: the residual's drift over
-// 20 steps in cycles of 5 in FP32 measured 3.8e-7 |r0| (1.4e-6 on a source of low modes) against
-// 2.2e-7 (1.3e-6) for directions that minimise at every step, 3.5e-6 (unshifted), and 2.1e-7 (3.5e-6)
-// at half the bound.  A power of two, so that the division by c is exact.
-double Hierarchy::ss_shift(int l) const {
+// Shifts of the s-step directions of a cycle of k steps on level l (P_{i+1} = A P_i / c - s_i P_i).
+// D_W(M5) + 1 is (3 + M5) minus hops of norm at most 2, the fifth-dimension hop has norm
+// max(1, |m|), and the coarse kernels are their Galerkin projections, so |A| <= B^2 with B the sum;
+// A's spectrum lies in the right half-plane, near the real axis.
+// The rounding of a direction and of A counts in the coefficients as often as the directions'
+// condition allows.  With all shifts at about a third of the bound it grows tenfold a step: an FP32
+// smoother's residual (one cycle, on noise / low modes / a smoothed residual / high modes) is off from
+// FP64's by 1.2 / 1.0 / 1.3 / 2.0 times what it is with directions that minimise at every step at 4
+// steps, 1.6 / 1.0 / 2.0 / 3.1 at 5, 2.5 / 1.4 / 3.8 / 5.1 at 6, 9.2 / 4.4 / 17 / 19 at 8.  From 4 steps
+// on the shifts are therefore Leja points of [0.08, 0.8] of the bound (each the one with the
+// largest product of distances from those before it): 1.05 / 1.1 / 1.0 / 0.9 at 4 steps, 1.2 / 1.1 /
+// 1.05 / 1.3 at 5, 1.3 / 1.1 / 1.2 / 1.7 at 6, 1.6 / 1.1 / 2.0 / 2.9 at 8.  They need the spectrum's top,
+// which the bound gives on the fine level only (on coarse ones about two thirds of it, less with few
+// vectors, and shifts beyond the top cost more than they save): coarse levels and the
+// polynomial-corrected operator keep the constant.  c is a power of two, so that the division by it
+// is exact.
+SsShifts Hierarchy::ss_shifts(int l, int k) const {
+    static constexpr double kLeja[kSsMax] = {0.8, 0.08, 0.44, 0.232, 0.677, 0.138, 0.753, 0.55};
     const double B = std::fabs(3.0 + M5) + 2.0 + std::max(1.0, std::fabs(m));
     double top = B * B;
-    if (l == 0 && prm.pv_poly_order > 0) {   // A_p = D_PV^dag p(X) D_DW: the largest |x p(x)| on [0, B^2]
+    const bool poly = l == 0 && prm.pv_poly_order > 0;
+    if (poly) {   // A_p = D_PV^dag p(X) D_DW: the largest |x p(x)| on [0, B^2]
         top = 0.0;
         for (int i = 1; i <= 1024; ++i) {
             const double x = B * B * i / 1024.0;
             double p = 0.0;
-            for (int k = prm.pv_poly_order; k >= 0; --k) p = p * x + prm.pv_poly[k];
+            for (int j = prm.pv_poly_order; j >= 0; --j) p = p * x + prm.pv_poly[j];
             top = std::max(top, std::fabs(x * p));
         }
     }
-    const double c = 0.36 * top;
-    return std::isfinite(c) && c > 1e-30 && c < 1e30 ? std::exp2(std::round(std::log2(c))) : 1.0;
+    double c = 0.36 * top;
+    c = std::isfinite(c) && c > 1e-30 && c < 1e30 ? std::exp2(std::round(std::log2(c))) : 1.0;
+    SsShifts sh;
+    sh.inv_c = 1.0 / c;
+    const bool leja = l == 0 && !poly && k >= 4 && std::isfinite(top);
+    for (int i = 0; i < kSsMax; ++i) sh.s[i] = leja ? (double)(float)(kLeja[i] * top / c) : 1.0;
+    return sh;
 }
 
 // The s-step form amplifies rounding where the orthogonalising one does not, so it is taken up to the
 // length at which a K-cycle is no further from the same K-cycle in FP64 (64^2 x 8 and 72 x 48 x 12, FP32
 // smoother, the residual of its result, sources of Gaussian noise, of low modes and outer residuals):
-//  - with 16-bit coarse links their rounding is all the difference (1e-3 to 1e-5 of the result):
-//    1.00 of the orthogonalising form's at every length up to 6, 1.07 in two cycles of 8;
-//  - with FP32 or FP64 links under FP32 vectors 1.00 at 2 steps, 1.04 at 3, 1.1 at 4, 1.35 at 5, 2.0 at
-//    6, 7 at 8; the same holds for FP32 links under FP64 vectors;
-//  - with everything in FP64 the factor is on 1e-16.
+//  - with 16-bit coarse links their rounding is all the difference (1e-3 to 1e-5 of the result): 1.00
+//    of the orthogonalising form's at every length up to 6 with the constant shift and up to 8 with
+//    Leja points, also in two cycles;
+//  - with FP32 or FP64 links under FP32 vectors 0.99 at 2 steps, 1.04 at 3, 1.1 at 5, 1.2 at 6, 1.4
+//    at 8 (constant shift 1.35, 2.0, 7); the same holds for FP32 links under FP64 vectors;
+//  - with everything in FP64 such a factor is on 1e-16.
 int Hierarchy::ss_longest(int l) const {
     auto narrow = [](int p) { return p == P_BF16 || p == P_F16; };
     const int own = l > 0 ? prm.link_prec[l - 1] : P_F64;            // the level's own links
     const int below = prm.link_prec[std::min(l, prm.nlevels - 1)];   // the next coarser level's
-    if (narrow(own) || narrow(below)) return kSsMax;
-    return levels[l].vec_prec == P_F32 || own == P_F32 ? kSsMaxF32 : kSsMax;
+    if (!narrow(own) && !narrow(below) && (levels[l].vec_prec == P_F32 || own == P_F32)) return 2;
+    return l == 0 && prm.pv_poly_order == 0 ? kSsMax : 6;
 }
 
 Skip Hierarchy::ss_skip(int l, const GcrDev& g) const {
@@ -529,7 +545,7 @@ Task Hierarchy::gcr_plain(int l, const cpx<T>* b, cpx<T>* x, int ncol, double to
     GcrDev& g = w.gcr;
     const double tol2 = tol * tol;
     const bool ss = kmax <= ss_longest(l);
-    const double c_ss = ss_shift(l);
+    const SsShifts sh = ss_shifts(l, kmax);
     SsVecs<T> V{};
     if (ss) {
         // P_0 .. P_{kmax-1}, and the last direction in W_0 (the s-step form keeps no W)
@@ -569,7 +585,7 @@ Task Hierarchy::gcr_plain(int l, const cpx<T>* b, cpx<T>* x, int ncol, double to
     auto cycle = [&]() -> int {
         for (int k = 0; k < kmax; ++k) {
             if (ss) {
-                HIPCHK(apply_A<T>(l, V.p[k], V.p[k + 1], t, ncol, st, ss_skip(l, g), Epi<T>{V.p[k], 1.0 / c_ss, -1.0}));
+                HIPCHK(apply_A<T>(l, V.p[k], V.p[k + 1], t, ncol, st, ss_skip(l, g), Epi<T>{V.p[k], sh.inv_c, -sh.s[k]}));
                 continue;
             }
             cpx<T>* Pk = P + (size_t)k * nt;
@@ -586,7 +602,7 @@ Task Hierarchy::gcr_plain(int l, const cpx<T>* b, cpx<T>* x, int ncol, double to
         if (ss) {
             // (the finaliser itself tells the host, so that the next launches are on their way
             // while the update runs)
-            HIPCHK(ss_finish<T>(V, kmax, x, n, ncol, c_ss, tol2, false, g, rw_, st, SsPublish{d_col_, d_pub_ctr_}));
+            HIPCHK(ss_finish<T>(V, kmax, x, n, ncol, sh, tol2, false, g, rw_, st, SsPublish{d_col_, d_pub_ctr_}));
             return DWF_OK;
         }
         HIPCHK(gcr_solve_xupdate_restart<T>(P, nt, kmax, x, n, ncol, r, (kmax % 2 == 0) ? g.stop : g.stop2, g,
@@ -647,7 +663,6 @@ int Hierarchy::smooth(int l, const cpx<T>* r, cpx<T>* z, int ncol, hipStream_t s
     const int ks = w.kscycle;
     GcrDev& g = w.gsm;
     const bool ss = ks <= ss_longest(l);
-    const double c_ss = ss_shift(l);
     SsVecs<T> V{};
     if (ss)
         for (int j = 0; j <= ks; ++j) V.p[j] = Ps + (size_t)j * nt;
@@ -656,10 +671,11 @@ int Hierarchy::smooth(int l, const cpx<T>* r, cpx<T>* z, int ncol, hipStream_t s
             HIPCHK(apply_A<T>(l, z, Ps, t, ncol, st, Skip{}, Epi<T>{r, -1.0, 1.0}));   // P_0 = r - A z
             for (int c0 = 0; c0 < ns; c0 += ks) {
                 const int kc = std::min(ks, ns - c0);
+                const SsShifts sh = ss_shifts(l, kc);
                 for (int j = 0; j < kc; ++j)
                     HIPCHK(apply_A<T>(l, V.p[j], V.p[j + 1], t, ncol, st, c0 == 0 ? Skip{} : ss_skip(l, g),   // (the first cycle sets the flags)
-                                      Epi<T>{V.p[j], 1.0 / c_ss, -1.0}));
-                HIPCHK(ss_finish<T>(V, kc, z, n, ncol, c_ss, -1.0, c0 == 0, g, rw_, st));
+                                      Epi<T>{V.p[j], sh.inv_c, -sh.s[j]}));
+                HIPCHK(ss_finish<T>(V, kc, z, n, ncol, sh, -1.0, c0 == 0, g, rw_, st));
             }
             return DWF_OK;
         }

@@ -325,8 +325,9 @@ private:
                                              Skip skip = {});
     template <typename T> hipError_t apply_A(int l, const cpx<T>* in, cpx<T>* out, cpx<T>* tmp, int ncol,
                                              hipStream_t st, Skip skip = {}, const Epi<T>& epi = {});
-    // shift of the s-step Krylov directions on level l, and the longest cycle that takes that form
-    double ss_shift(int l) const;
+    // shifts of the s-step Krylov directions of a cycle of k steps on level l, and the longest cycle
+    // that takes that form
+    SsShifts ss_shifts(int l, int k) const;
     int ss_longest(int l) const;
     // the columns an s-step cycle leaves out: a tile of FP16 matrix-core columns shares one scale, so
     // that a stopped column's directions would take bits from a smaller live one's

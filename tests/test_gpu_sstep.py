@@ -123,8 +123,7 @@ def krylov_min_residual(A, r, steps, restart):
 def test_fp32_smoother_rounding(steps, restart, nrhs, link):
     """The smoother alone (a source that vanishes on both walls restricts to zero) in FP32 against FP64:
     the residual of its result.  Bar: an application of A rounds some 30 times per site, 3 u of its
-    size together, and the steps' errors add up at random: 3 u sqrt(steps + 1); with 16-bit coarse
-    links, whose own rounding is 2^-12, cycles of up to 6 steps may amplify that by 8."""
+    size together, and the steps' errors add up at random: 3 u sqrt(steps + 1)."""
     Ls, L, m = 6, 16, 0.05
     U = inputs.metropolis_u1(L, L, 6.0, 30, 940).U
     lp = dwfmg.P_F64 if link == "f64" else dwfmg.P_F16
@@ -134,7 +133,7 @@ def test_fp32_smoother_rounding(steps, restart, nrhs, link):
     r = inputs.gaussian_field((nrhs, Ls, L, L, 2), 942).astype(np.complex64).astype(np.complex128)
     r[:, 0] = r[:, -1] = 0.0
     got = mg.level_op(0, dwfmg.MG_OP_KCYCLE, T(r), nrhs).cpu().numpy()
-    bar = 3 * 2.0 ** -24 * np.sqrt(steps + 1) * (8 if link == "f16" and (restart or steps) <= 6 else 1)
+    bar = 3 * 2.0 ** -24 * np.sqrt(steps + 1)
     A = lambda v: O.pv_dag_dw(U, v, m, -1.0)  # noqa: E731
     for c in range(nrhs):
         want = krylov_min_residual(A, r[c], steps, restart)
