@@ -249,7 +249,10 @@ def coarse_mfma_per_launch(nsites, n, Ls_c, ncol, tw=None):
     return nsites * (n // 16) * ntile * 2 * (5 * n // 16)
 
 
-GRAM_STEPS = 6   # longest cycle of the step-by-step Gram form in the models below (the s-step form's: sstep_model_bytes)
+# The two models below are of step-by-step GCR: a Gram form up to GRAM_STEPS steps a cycle, which the
+# library no longer has (its short cycles: sstep_model_bytes), and the orthogonalising form, which its
+# longer cycles take.  No row reports them; they are kept as the yardstick the s-step passes are held to.
+GRAM_STEPS = 6
 
 
 def smoother_model_passes(ns, ks):
@@ -309,9 +312,9 @@ SSTEP_STEPS, SSTEP_COARSE_STEPS = 8, 6
 def sstep_model_bytes(fine_applies, coarse_iters, k, L, Ls, coarse_a, coarse_vec_bytes,
                       kcycles=0, smooth_iters=0, smooth_restart=0, fused=False):
     """HBM bytes of one solve whose smoother and coarsest cycles all take the s-step form (at most
-    SSTEP_STEPS and SSTEP_COARSE_STEPS steps; None for longer ones), a lower bound as solve_model_bytes is: the fine
-    stencils (with the fused A half of their vector bytes, since an application reads and writes
-    one vector for its two stencils), one coarse A-hat per coarsest iteration, and per cycle of
+    SSTEP_STEPS and SSTEP_COARSE_STEPS steps; None for longer ones), a lower bound as
+    solve_model_bytes is: the fine stencils (with the fused A half of their vector bytes, since an
+    application reads and writes one vector for its two stencils), one coarse A-hat per coarsest iteration, and per cycle of
     k steps the shift's read of each direction (k), the inner products (k + 1) and the update
     (k + 1 directions and x read, x and the residual written): 3 k + 5 vector passes.  The
     smoother's first residual reads its right-hand side once."""

@@ -90,3 +90,27 @@ def test_smoother_byte_model_worked_example():
                                   smooth_restart=5)
     assert got - base == 3 * 208 * fine_vec
 
+
+
+def test_sstep_byte_model_worked_example():
+    # 256^2 x 16 FP32: a fine vector is 16 x 65536 x 2 x 8 B, the links 2 x 65536 x 8 B an apply
+    vec, links, coarse_vec = 16_777_216, 1_048_576, 4096 * 2 * 32 * 16
+    # GCR(6): 6 shifts, 7 directions for the products, 7 and x read, x and the residual written: 23
+    # passes per 6 iterations; two fine vectors an apply, one with the fused A
+    want = 10 * (2 * vec + links) + 12 * 113_246_208 + 12 * 23 / 6 * coarse_vec
+    got = bench.sstep_model_bytes(10, 12, 6, 256, 16, 113_246_208, coarse_vec)
+    assert abs(got - want) <= 1e-6 * want
+    fused = bench.sstep_model_bytes(10, 12, 6, 256, 16, 113_246_208, coarse_vec, fused=True)
+    assert abs(got - fused - 10 * vec) <= 1e-6 * want
+    # 20 smoothing steps in cycles of 5: the right-hand side once, then 4 cycles of 3 x 5 + 5 passes
+    smoothed = bench.sstep_model_bytes(10, 12, 6, 256, 16, 113_246_208, coarse_vec, kcycles=3, smooth_iters=20,
+                                       smooth_restart=5)
+    assert smoothed - got == 3 * 81 * vec
+    # a shorter last cycle: 5 + 2 steps are 1 + 20 + 11 passes
+    short = bench.sstep_model_bytes(10, 12, 6, 256, 16, 113_246_208, coarse_vec, kcycles=1, smooth_iters=7,
+                                    smooth_restart=5)
+    assert short - got == 32 * vec
+    # longer cycles take the orthogonalising form, which it does not model
+    assert bench.sstep_model_bytes(10, 12, 7, 256, 16, 113_246_208, coarse_vec) is None
+    assert bench.sstep_model_bytes(10, 12, 6, 256, 16, 113_246_208, coarse_vec, kcycles=1, smooth_iters=9) is None
+    assert bench.sstep_model_bytes(10, 12, 6, 256, 16, 113_246_208, coarse_vec, kcycles=1, smooth_iters=8) is not None
