@@ -680,11 +680,11 @@ fine_a_kernel(const cpx<R>* __restrict__ U, const spinor<R>* __restrict__ in, sp
     }
 }
 
-// Measured (graph of 20 applications, us; two launches before): FP32 256^2 x 16: 12.5 (15.0), x 4 rhs
-// 26.8 (50.0), x 16 rhs 111 (191); 512^2 x 32 x 4 rhs 234 (377), 4.6 TB/s of 1.08 GB; 64^2 x 16 x
-// 2 rhs 5.7 (6.5); FP64 256^2 x 16 x 4 rhs 70 (127), 128^2 x 16 10.8 (11.5).  Holding the slices in
-// registers instead of four LDS boxes took it from 138 to 83 registers and 50 to 23 KB of LDS (FP32),
-// 146 to 111 us at 256^2 x 16 x 16 rhs.
+// Measured (graph of 20 applications, us; two launches in brackets): FP32 256^2 x 16: 13.1 (16.3), x 4
+// rhs 29.3 (49.1), x 16 rhs 115 (190); 512^2 x 32 x 4 rhs 233 (372), 4.6 TB/s of 1.08 GB; 64^2 x 16 x
+// 2 rhs 5.1 (6.6), 64^2 x 4 4.4 (5.3); FP64 256^2 x 16 24.4 (29.8), x 4 rhs 77 (117), 128^2 x 16 10.1
+// (11.5), 64^2 x 4 5.1 (5.7).  Holding the slices in registers instead of four LDS boxes took it
+// from 138 to 83 registers and 50 to 23 KB of LDS (FP32), 146 to 111 us at 256^2 x 16 x 16 rhs.
 
 // Launch configuration of the fine A: 0 = the two stencil launches (each with its own
 // configuration), else fused tile shape * kCfgStride + slice chunk
